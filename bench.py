@@ -8,7 +8,7 @@ queries) against the resident 2,000,000-point voxelised track map, k = 20,
 r = 2 m; cell size and launch shape from the autotuner.  One step is one
 ``lkc_knn_cov_batched`` call over all 48 scans: the query key and radix
 sort launches, the group search (``k_group``) and the wavefront-per-query
-search of the queries it hands over (``k_fallback``).  The plain
+search of the queries it hands over (``k_wave``).  The plain
 one-call-per-scan loop is timed beside it, the same call replayed from a
 captured HIP graph is timed as an extra, and a short served stream (3
 sensors at 20 Hz, real time) reports p50/p99 per-scan latency for the
@@ -302,7 +302,7 @@ def gicp(args, lkc, workloads, torch, ctx, cfg):
                    "n_points": n, "map_points": int(m.shape[0]), "max_corr_dist_m": max_d,
                    "cell_m": cell, "step": "transform + k=1 search + FP64 system reduction"},
         "roofline": roof,
-        "phases_ms": {"query_sort": sort_ms, "k_group": group_ms, "k_fallback": fb_ms,
+        "phases_ms": {"query_sort": sort_ms, "k_group": group_ms, "k_wave": fb_ms,
                       "reduce": red_ms, "call": call_ms},
         "fallback_queries": fb_q,
         "system": {"correspondences": sysd["count"], "rejected": sysd["rejected"],
@@ -719,7 +719,7 @@ def main():
                   "radius_m": radius, "cell_m": cell,
                   "step": "one lkc_knn_cov_batched call over all scans: query keys + radix "
                           "sort, group search (k_group), wavefront search of the queries "
-                          "it hands over (k_fallback)"}
+                          "it hands over (k_wave)"}
         if not args.no_autotune and not args.cfg:
             from paper_2308_07173_amd import autotune
             tune = autotune.autotune(m, allq, k, radius, sample=allq.shape[0], reps=5, ctx=ctx)
@@ -808,10 +808,10 @@ def main():
     # queries it answers (the rest go to the wavefront search); or the
     # wavefront search when it takes longer (one wavefront per query)
     group_q = queries_per_launch - fb_q
-    dom = ("k_group", group_q, group_ms) if group_ms >= fb_ms else ("k_fallback", fb_q, fb_ms)
+    dom = ("k_group", group_q, group_ms) if group_ms >= fb_ms else ("k_wave", fb_q, fb_ms)
     achieved = dom[1] * b_alg(k) / (dom[2] * 1e-3) / 1e9
     path_achieved = queries_per_launch * b_alg(k) / (kern_ms * 1e-3) / 1e9
-    extra["phases_ms"] = {"query_sort": sort_ms, "k_group": group_ms, "k_fallback": fb_ms}
+    extra["phases_ms"] = {"query_sort": sort_ms, "k_group": group_ms, "k_wave": fb_ms}
     extra["search_call"] = {"ms": kern_ms, "achieved_GBs": path_achieved,
                             "frac": path_achieved / HBM_PEAK_GBS}
     traffic = committed_traffic(args.workload) if dom[0] == "k_group" else None

@@ -92,15 +92,16 @@ typedef enum lkc_status {
  *                   cell, one wavefront per 64 queries, register top-k, a
  *                   wavefront-per-query pass for the queries it cannot prove
  *                   exact); 2 wavefront-per-query search for every query.
- *                   Auto takes 1 for k <= 32 and 2 above.  Both give
- *                   bit-identical results.
+ *                   Auto takes 2 above k = 32 and for launches too small to
+ *                   fill the device with groups (up to 384 queries per
+ *                   compute unit, 512 of a target against itself, 768 above
+ *                   k = 20), else 1; any of the group options below, given,
+ *                   asks for 1.  Both give bit-identical results.
  *  group_reach      cells the group search looks beyond its queries' cells
  *                   (0 = auto: ceil(radius / cell) clamped to [1, 2]; 1..4)
  *  waves_per_block  wavefronts per workgroup (0 = 2; 1..4)
- *  merge_min        the wavefront search merges a candidate batch with at
- *                   least this many entries below the k-th distance by a
- *                   bitonic network instead of one insertion per entry
- *                   (0 = 12; 1..65, 65 disables the network)
+ *  merge_min        0..65; no effect (the wavefront search once chose by it
+ *                   how to merge a candidate batch)
  *  persistent       0: one wavefront per 64-query group; n > 0: n persistent
  *                   workgroups per compute unit pull groups from per-XCD
  *                   work counters (0..32)
@@ -657,9 +658,9 @@ lkc_status lkc_ctx_set_profile(lkc_ctx *ctx, void *buffer, int64_t n_groups);
  *   cells    host [n_cells] candidate cell sizes (> 0); n_cells = 0 takes
  *            0.5, 0.75, 1, 1.5, 2 m
  *   cfgs     host [n_cfgs] candidate launch shapes; n_cfgs = 0 takes a
- *            default list of seven (group search with automatic, reach-1,
- *            2- and 1-wavefront workgroups, two persistent shapes, and the
- *            wavefront-per-query search)
+ *            default list of seven (all defaults; the group search with
+ *            reach 1, with 4- and 1-wavefront workgroups, with two persistent
+ *            shapes; the wavefront-per-query search)
  *   times_ms host [n_cells][n_cfgs] median times, or NULL
  *   result   host: the fastest pair.
  * Allocates and frees device memory for the sample and its outputs, and

@@ -19,7 +19,7 @@ import numpy as np
 
 DEFAULT_CELLS = (0.5, 0.75, 1.0, 1.5, 2.0)
 DEFAULT_CFGS = (
-    dict(),                                   # group search, reach auto, 2 waves/WG
+    dict(),                                   # all defaults
     dict(group_reach=1),
     dict(waves_per_block=4),
     dict(waves_per_block=1),

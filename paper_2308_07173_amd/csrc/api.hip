@@ -805,6 +805,7 @@ lkc_status lkc_ctx_search_stats(lkc_ctx* ctx, lkc_search_stats* out) {
         LKC_HIP_TRY(ctx, hipEventSynchronize(ctx->ev[5]));
         LKC_HIP_TRY(ctx, hipEventElapsedTime(&out->reduce_ms, ctx->ev[4], ctx->ev[5]));
     }
+    if (ctx->last_all_wave) out->fallback_queries = ctx->last_queries;
     if (ctx->last_fallback_count) {
         uint32_t v = 0;
         LKC_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));

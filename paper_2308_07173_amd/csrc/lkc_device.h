@@ -81,9 +81,12 @@ __device__ __forceinline__ unsigned long long pack_key(const TargetView& T, int 
 typedef __attribute__((address_space(1))) const float gfloat;
 typedef __attribute__((address_space(1))) const uint32_t gu32;
 
+typedef float gvec4 __attribute__((ext_vector_type(4)));
+// (one 16-byte load: of four loads of floats, the last may be sunk to where
+// the index is used, a second round trip)
 __device__ __forceinline__ float4 gload(const float4* p) {
-    gfloat* q = (gfloat*)p;
-    return make_float4(q[0], q[1], q[2], q[3]);
+    const gvec4 v = *(__attribute__((address_space(1))) const gvec4*)p;
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ float gload(const float* p) { return *(gfloat*)p; }
 __device__ __forceinline__ uint32_t gload(const uint32_t* p) { return *(gu32*)p; }
@@ -219,14 +222,32 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
 }
 __device__ __forceinline__ float wave_min_dpp(float v) { return -wave_max_dpp(-v); }
 
-// inclusive prefix sum across the wave (Hillis-Steele with shuffles)
+// The same for integers.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_i(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ int wave_min_i32(int v) {
+    const int id = 0x7fffffff;
+    v = min(v, dpp_i<0x111, 0xf>(id, v));
+    v = min(v, dpp_i<0x112, 0xf>(id, v));
+    v = min(v, dpp_i<0x114, 0xf>(id, v));
+    v = min(v, dpp_i<0x118, 0xf>(id, v));
+    v = min(v, dpp_i<0x142, 0xa>(id, v));
+    v = min(v, dpp_i<0x143, 0xc>(id, v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Inclusive prefix sum across the wave: row shifts within the rows of 16
+// lanes, then the rows' last lanes broadcast to the rows after them.  (Six
+// vector adds; with lane shuffles through the LDS it was six round trips.)
 __device__ __forceinline__ int wave_incl_scan(int v) {
-    const int l = lane_id();
-#pragma unroll
-    for (int s = 1; s < WAVE; s <<= 1) {
-        const int o = __shfl_up(v, s);
-        if (l >= s) v += o;
-    }
+    v += dpp_i<0x111, 0xf>(0, v);
+    v += dpp_i<0x112, 0xf>(0, v);
+    v += dpp_i<0x114, 0xf>(0, v);
+    v += dpp_i<0x118, 0xf>(0, v);
+    v += dpp_i<0x142, 0xa>(0, v);
+    v += dpp_i<0x143, 0xc>(0, v);
     return v;
 }
 

@@ -26,6 +26,7 @@ struct lkc_ctx {
     void* search_scratch = nullptr;
     size_t search_scratch_bytes = 0;
     uint32_t* last_fallback_count = nullptr;  // device word of the last search
+    bool last_all_wave = false;   // the last search had no group search to hand queries on
     int64_t last_queries = 0;
     // optional phase timing of searches: events before the query sort, the
     // group kernel and the fallback kernel, and after the fallback kernel

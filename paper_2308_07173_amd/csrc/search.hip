@@ -12,7 +12,7 @@
 //     the group streams the point runs of its block of cells once, each
 //     candidate broadcast to all lanes, and answers every lane whose result
 //     the block proves exact;
-//   * the wavefront-per-query search (k_fallback, and the whole search with
+//   * the wavefront-per-query search (k_wave, and the whole search with
 //     algorithm 2) answers the rest: cells in Chebyshev rings around the
 //     query's cell, lanes enumerating a ring's cells in parallel and probing
 //     the cell hash; the surviving runs streamed 64 candidates at a time
@@ -47,145 +47,249 @@ struct SearchParams {
     int k;
     float r2;        // squared radius (INF if uncapped)
     int capped;
-    int merge_min;
 };
 
-// ------------------------------------------------------------------ top-k --
+// ---------------------------------------------------- wavefront candidates --
 
-struct TopK {
-    float d;     // this lane's entry (lanes >= k hold the sentinel)
-    int32_t i;   // original index
-    int32_t p;   // position in the reordered point array
-    float thr_d; // entry k-1 (uniform)
-    int32_t thr_i;
-};
-
-__device__ __forceinline__ void topk_refresh(TopK& L, int k) {
-    L.thr_d = readlane(L.d, k - 1);
-    L.thr_i = readlane(L.i, k - 1);
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ float uniform_f(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+// Orders this wavefront's LDS writes before its later reads by other lanes
+// (the LDS serves a wavefront in order: only the compiler has to be told).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Insert one candidate that is known to beat entry k-1.
-__device__ __forceinline__ void topk_insert(TopK& L, int k, float cd, int32_t ci, int32_t cp) {
-    const int lane = lane_id();
-    const bool gt = lane < k && key_less(cd, ci, L.d, L.i);
-    const unsigned long long gm = ballot(gt);
-    const int pos = __builtin_ffsll((long long)gm) - 1;
-    const float pd = shift_up1(L.d, INF);
-    const int32_t pi = shift_up1(L.i, IDX_SENTINEL);
-    const int32_t pp = shift_up1(L.p, (int32_t)-1);
-    if (gt) {
-        if (lane == pos) {
-            L.d = cd;
-            L.i = ci;
-            L.p = cp;
-        } else {
-            L.d = pd;
-            L.i = pi;
-            L.p = pp;
+// The candidates of one query, whole wavefront: an unordered list of exact
+// keys (float32 d2 bits above the original index) in LDS and the squared
+// distance beyond which none can matter.  A batch of 64 candidates is
+// appended with one ballot; the list is cut back when it outgrows a wavefront
+// or a tighter bound is wanted, and sorted once, at the end, by counting.
+// The cut needs a distance that at least k and not many more entries do not
+// exceed: on the surfaces a LiDAR sees the counts grow about linearly with
+// d2, so interpolating between two counts finds it in two or three ballots
+// (a search over the distance's bits takes about twenty).
+struct WaveList {
+    static constexpr int CAP = 2 * WAVE;   // entries (LDS keys)
+    static constexpr int SLACK_ENTRIES = 8;
+    unsigned long long* buf;
+    float bound;               // (uniform) farther candidates are not among the k nearest
+    int n;                     // (uniform) entries
+    int k;
+    bool dirty;                // (uniform) entries since the last cut
+
+    __device__ __forceinline__ void cut_back() {
+        const int lane = lane_id();
+        const int keep = min(k + SLACK_ENTRIES, WAVE);
+        wave_lds_fence();
+        const unsigned long long a = lane < n ? buf[lane] : ~0ull;
+        const unsigned long long b = lane + WAVE < n ? buf[lane + WAVE] : ~0ull;
+        // (an absent entry's distance is a NaN: below nothing)
+        const float da = __uint_as_float((uint32_t)(a >> 32)), db = __uint_as_float((uint32_t)(b >> 32));
+        float lo = 0.0f, up = wave_max_dpp(fmaxf(lane < n ? da : 0.0f, lane + WAVE < n ? db : 0.0f));
+        int c_lo = 0, c_up = n;
+        for (int it = 0; it < 6 && c_up > keep; ++it) {
+            const float t = lo + (up - lo) * ((float)(k + SLACK_ENTRIES / 2 - c_lo) *
+                                              __builtin_amdgcn_rcpf((float)(c_up - c_lo)));
+            const int c = __popcll(ballot(da <= t)) + __popcll(ballot(db <= t));
+            if (c >= k) {
+                up = t;
+                c_up = c;
+            } else {
+                lo = t;
+                c_lo = c;
+            }
+        }
+        unsigned long long ma = ballot(da <= up), mb = ballot(db <= up);
+        if (c_up > WAVE) {
+            // many equal distances: tell the keys apart bit by bit
+            unsigned long long ul = 0, uu = ~0ull >> 1;
+            for (int bit = 62; bit >= 0 && c_up > WAVE; --bit) {
+                const unsigned long long t = ul | ((1ull << bit) - 1ull);
+                const int c = __popcll(ballot(a <= t)) + __popcll(ballot(b <= t));
+                if (c >= k) {
+                    uu = t;
+                    c_up = c;
+                } else {
+                    ul |= 1ull << bit;
+                }
+            }
+            ma = ballot(a <= uu);
+            mb = ballot(b <= uu);
+        }
+        if (c_up < n) {
+            if ((ma >> lane) & 1ull) buf[lanes_below(ma)] = a;
+            if ((mb >> lane) & 1ull) buf[__popcll(ma) + lanes_below(mb)] = b;
+        }
+        n = c_up;
+        bound = fminf(bound, up);
+        dirty = false;
+    }
+    // Takes the lanes' candidates; at most 64 entries stay.
+    __device__ __forceinline__ void add(bool valid, float d, int32_t i) {
+        const bool pass = valid && d <= bound;
+        const unsigned long long m = ballot(pass);
+        if (!m) return;
+        if (pass)
+            buf[n + lanes_below(m)] = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)i;
+        n += __popcll(m);
+        dirty = true;
+        if (n > WAVE) cut_back();
+    }
+    // Tightens the bound once the list holds k entries.
+    __device__ __forceinline__ void tighten() {
+        if (dirty && n >= k) cut_back();
+    }
+    // Whether k candidates are nearer than d2, or the radius is.
+    __device__ __forceinline__ bool within(float d2) {
+        if (d2 > bound) return true;
+        if (n < k) return false;
+        wave_lds_fence();
+        const int lane = lane_id();
+        const float d = __uint_as_float(lane < n ? (uint32_t)(buf[lane] >> 32) : ~0u);
+        return __popcll(ballot(d < d2)) >= k;
+    }
+};
+
+// The nearest candidate alone (k = 1): each lane keeps its own best.
+struct WaveNearest {
+    float bound;               // (uniform)
+    float d;
+    int32_t i;
+    __device__ __forceinline__ void add(bool valid, float cd, int32_t ci) {
+        if (valid && cd <= bound && key_less(cd, ci, d, i)) {
+            d = cd;
+            i = ci;
         }
     }
-    topk_refresh(L, k);
-}
+    __device__ __forceinline__ void tighten() { bound = fminf(bound, wave_min_dpp(d)); }
+    __device__ __forceinline__ bool within(float d2) { return d2 > bound || ballot(d < d2) != 0; }
+};
 
-__device__ __forceinline__ void cmpx(float& d, int32_t& i, int32_t& p, int s, bool asc) {
-    const int lane = lane_id();
-    const float pd = shfl_xor(d, s);
-    const int32_t pi = shfl_xor(i, s);
-    const int32_t pp = shfl_xor(p, s);
-    const bool keep_min = (((lane & s) == 0) == asc);
-    const bool take = keep_min ? key_less(pd, pi, d, i) : key_less(d, i, pd, pi);
-    if (take) {
-        d = pd;
-        i = pi;
-        p = pp;
-    }
-}
-
-// Merge a whole batch (lanes with `pass`) into the list with a bitonic
-// network: sort the batch, reverse it, take the lane-wise minimum with the
-// list (a bitonic sequence holding the 64 smallest of both), merge.
-__device__ __forceinline__ void topk_merge(TopK& L, int k, bool pass, float d, int32_t oi,
-                                           int32_t src) {
-    const int lane = lane_id();
-    float bd = pass ? d : INF;
-    int32_t bi = pass ? oi : IDX_SENTINEL;
-    int32_t bp = pass ? src : -1;
-#pragma unroll
-    for (int size = 2; size <= WAVE; size <<= 1) {
-#pragma unroll
-        for (int s = size >> 1; s > 0; s >>= 1) cmpx(bd, bi, bp, s, (lane & size) == 0);
-    }
-    const float rd = shfl(bd, WAVE - 1 - lane);
-    const int32_t ri = shfl(bi, WAVE - 1 - lane);
-    const int32_t rp = shfl(bp, WAVE - 1 - lane);
-    if (key_less(rd, ri, L.d, L.i)) {
-        L.d = rd;
-        L.i = ri;
-        L.p = rp;
-    }
-#pragma unroll
-    for (int s = WAVE >> 1; s > 0; s >>= 1) cmpx(L.d, L.i, L.p, s, true);
-    if (lane >= k) {
-        L.d = INF;
-        L.i = IDX_SENTINEL;
-        L.p = -1;
-    }
-    topk_refresh(L, k);
-}
+struct WaveQuery {
+    float x, y, z;
+    int skip;   // 64-record chunk of the points that has been taken already (-1: none)
+};
 
 // Stream the concatenated point runs of the cells held by lanes with `want`
-// through the top-k, 64 candidates per step.
-__device__ __forceinline__ void scan_cells(const TargetView& T, float qx, float qy, float qz,
-                                           const SearchParams& sp, bool want, uint32_t start,
-                                           uint32_t count, TopK& L) {
-    const unsigned long long m = ballot(want);
-    if (!m) return;
+// into the list, two batches of 64 candidates in flight.
+template <typename List>
+__device__ __forceinline__ void scan_points(const TargetView& T, const WaveQuery& q, bool want,
+                                            int st, int total, int excl, List& L) {
     const int lane = lane_id();
-    const int c = want ? (int)count : 0;
-    const int incl = wave_incl_scan(c);
-    const int excl = incl - c;
-    const int total = readlane(incl, WAVE - 1);
-    const int st = (int)start;
-    unsigned long long pend = m;
-    for (int b0 = 0; b0 < total; b0 += WAVE) {
+    const int delta = st - excl;   // candidate f of the concatenation is point f + delta
+    unsigned long long pend = ballot(want);
+    int open = 0;                  // (uniform) delta of the last cell begun
+    const auto next = [&](int b0) -> int {
         const int f = b0 + lane;
-        int src = -1;
+        int dl = open;
         while (pend) {
             const int cl = __builtin_ffsll((long long)pend) - 1;
             const int o = readlane(excl, cl);
             if (o >= b0 + WAVE) break;
-            const int n = readlane(c, cl);
-            if (f >= o && f < o + n) src = readlane(st, cl) + (f - o);
-            if (o + n <= b0 + WAVE)
-                pend &= pend - 1;
-            else
-                break;
+            pend &= pend - 1;
+            open = readlane(delta, cl);
+            dl = f >= o ? open : dl;
         }
-        const bool valid = src >= 0;
-        float d = INF;
-        int32_t oi = IDX_SENTINEL;
-        if (valid) {
-            const float4 t = gload(T.pts + src);
-            d = dist2(qx, qy, qz, t.x, t.y, t.z);
-            oi = __float_as_int(t.w);
+        const int src = f + dl;
+        return f < total && (src >> 6) != q.skip ? src : -1;
+    };
+#pragma unroll 1
+    for (int b0 = 0; b0 < total; b0 += 2 * WAVE) {
+        const bool two = b0 + WAVE < total;
+        const int s0 = next(b0);
+        const int s1 = two ? next(b0 + WAVE) : -1;
+        const float4 p0 = gload(T.pts + max(s0, 0));
+        float4 p1 = p0;
+        if (two) p1 = gload(T.pts + max(s1, 0));
+        L.add(s0 >= 0, dist2(q.x, q.y, q.z, p0.x, p0.y, p0.z), __float_as_int(p0.w));
+        if (two) L.add(s1 >= 0, dist2(q.x, q.y, q.z, p1.x, p1.y, p1.z), __float_as_int(p1.w));
+    }
+}
+
+// The same through the cells' aligned 16-point runs: a lane tests one run's
+// box against the bound, and four surviving runs make a batch.
+template <typename List>
+__device__ __forceinline__ void scan_runs(const TargetView& T, const WaveQuery& q, bool want,
+                                          int st, int cn, float margin, List& L) {
+    const int lane = lane_id();
+    const int first = st / BOX_PTS, en = st + cn;
+    const int nr = want ? (en - 1) / BOX_PTS - first + 1 : 0;
+    const int incl = wave_incl_scan(nr), excl = incl - nr;
+    const int total = readlane(incl, WAVE - 1);
+    const int delta = first - excl;
+    unsigned long long pend = ballot(want);
+    int o_delta = 0, o_st = 0, o_en = 0;
+#pragma unroll 1
+    for (int b0 = 0; b0 < total; b0 += WAVE) {
+        // this lane's run: the points [p0, p1) of one cell
+        const int f = b0 + lane;
+        int dl = o_delta, cs = o_st, ce = o_en;
+        while (pend) {
+            const int cl = __builtin_ffsll((long long)pend) - 1;
+            const int o = readlane(excl, cl);
+            if (o >= b0 + WAVE) break;
+            pend &= pend - 1;
+            o_delta = readlane(delta, cl);
+            o_st = readlane(st, cl);
+            o_en = readlane(en, cl);
+            dl = f >= o ? o_delta : dl;
+            cs = f >= o ? o_st : cs;
+            ce = f >= o ? o_en : ce;
         }
-        const bool pass = valid && d <= sp.r2 && key_less(d, oi, L.thr_d, L.thr_i);
-        unsigned long long pm = ballot(pass);
-        if (!pm) continue;
-        if (__popcll(pm) >= sp.merge_min) {
-            topk_merge(L, sp.k, pass, d, oi, src);
-        } else {
-            while (pm) {
-                const int cl = __builtin_ffsll((long long)pm) - 1;
-                pm &= pm - 1;
-                const float cd = readlane(d, cl);
-                const int32_t ci = readlane(oi, cl);
-                if (!key_less(cd, ci, L.thr_d, L.thr_i)) continue;
-                topk_insert(L, sp.k, cd, ci, readlane(src, cl));
+        const int r = f + dl;
+        const int p0 = max(r * BOX_PTS, cs), p1 = min((r + 1) * BOX_PTS, ce);
+        const bool some = f < total && (p0 >> 6) != q.skip;
+        float ld = INF;
+        if (some) {
+            const float4 lo = gload(T.boxes + 2 * r);
+            const float4 hi = gload(T.boxes + 2 * r + 1);
+            const float gx = fmaxf(fmaxf(lo.x - (q.x + margin), (q.x - margin) - hi.x), 0.0f);
+            const float gy = fmaxf(fmaxf(lo.y - (q.y + margin), (q.y - margin) - hi.y), 0.0f);
+            const float gz = fmaxf(fmaxf(lo.z - (q.z + margin), (q.z - margin) - hi.z), 0.0f);
+            ld = fmaf(gx, gx, fmaf(gy, gy, gz * gz));
+        }
+        unsigned long long todo = ballot(some);
+        for (;;) {
+            // (the bound tightens as batches are added)
+            todo &= ballot(ld <= L.bound * (1.0f + 2e-6f));
+            if (!todo) break;
+            int from = -1;
+#pragma unroll
+            for (int u = 0; u < WAVE / BOX_PTS; ++u) {
+                if (todo) {
+                    const int c = __builtin_ffsll((long long)todo) - 1;
+                    todo &= todo - 1;
+                    from = lane / BOX_PTS == u ? c : from;
+                }
             }
+            const int s = shfl(p0, from & 63) + lane % BOX_PTS, e = shfl(p1, from & 63);
+            const bool valid = from >= 0 && s < e;
+            const float4 p = gload(T.pts + (valid ? s : 0));
+            L.add(valid, dist2(q.x, q.y, q.z, p.x, p.y, p.z), __float_as_int(p.w));
         }
     }
+}
+
+// Cells of many points go through their runs' boxes (one more dependent load,
+// then only the near runs), cells of few are streamed whole.
+constexpr int RUN_SCAN_MIN = 4 * WAVE;
+
+template <typename List>
+__device__ __forceinline__ void scan_cells(const TargetView& T, const WaveQuery& q, bool want,
+                                           uint32_t start, uint32_t count, float margin, List& L) {
+    const int c = want ? (int)count : 0;
+    const int incl = wave_incl_scan(c);
+    const int total = readlane(incl, WAVE - 1);
+    if (total > RUN_SCAN_MIN)
+        scan_runs(T, q, want, (int)start, (int)count, margin, L);
+    else
+        scan_points(T, q, want, (int)start, total, incl - c, L);
 }
 
 // Squared distance from q to the box of cell c, shrunk by `margin` on every
@@ -201,107 +305,95 @@ __device__ __forceinline__ float box_dist2(const TargetView& T, float qx, float 
     return dx * dx + dy * dy + dz * dz;
 }
 
-// k nearest points of one query, whole wavefront.  On return lanes < count
-// hold entries 0..count-1 of the sorted list.
-__device__ int knn_query_wave(const TargetView& T, float qx, float qy, float qz,
-                              const SearchParams& sp, TopK& L) {
+// Squared distance up to which no point lies outside the (2R+1)^3 block of
+// cells around cell cq of query q (0 when not even the block's faces are
+// clear of it).
+__device__ __forceinline__ float block_clear2(const TargetView& T, const float (&q)[3],
+                                              const int (&cq)[3], int R, float margin) {
+    float f = INF;
+    for (int a = 0; a < 3; ++a) {
+        const float lo = (float)(cq[a] - R) * T.cell, hi = (float)(cq[a] + R + 1) * T.cell;
+        f = fminf(f, fminf(q[a] - lo, hi - q[a]));
+    }
+    f = fmaxf(f - margin, 0.0f);
+    return f * f * (1.0f - 1e-6f);
+}
+
+// The candidates of one query that hold its k nearest points, whole wavefront
+// (q finite, the target not empty; L.bound starts at the radius).  `self`: the
+// query is a point of the target, whose own 64-record chunk (its neighbours
+// in Morton order) is taken first for a tight bound.  Then the query's own
+// cell and its first ring, whose hash probes go out together (one chain of
+// dependent loads rather than two; without a chunk the own cell is streamed
+// first, so that its k-th distance prunes the ring), then ring by ring, or in
+// one sweep of the cell table where a ring holds more cells than the table.
+// (T is the copy of *Tp in scalar registers; what only a sweep reads is left
+// in memory.)
+template <typename List>
+__device__ __forceinline__ void knn_query_wave(const TargetView& T, const TargetView* Tp,
+                                               const WaveQuery& sp, bool self, int capped,
+                                               List& L) {
     const int lane = lane_id();
-    L.d = INF;
-    L.i = IDX_SENTINEL;
-    L.p = -1;
-    L.thr_d = INF;
-    L.thr_i = IDX_SENTINEL;
-    if (!finite3(qx, qy, qz) || T.n_cells == 0) return 0;
-    const int cq[3] = {cell_coord(qx, T.inv_cell), cell_coord(qy, T.inv_cell),
-                       cell_coord(qz, T.inv_cell)};
+    const float qx = sp.x, qy = sp.y, qz = sp.z;
+    const int cq[3] = {__builtin_amdgcn_readfirstlane(cell_coord(qx, T.inv_cell)),
+                       __builtin_amdgcn_readfirstlane(cell_coord(qy, T.inv_cell)),
+                       __builtin_amdgcn_readfirstlane(cell_coord(qz, T.inv_cell))};
     const float q[3] = {qx, qy, qz};
-    int rmax = 0;
-    for (int a = 0; a < 3; ++a) rmax = max(rmax, max(cq[a] - T.cmin[a], T.cmax[a] - cq[a]));
-    if (sp.capped) {
-        const float rc = ceilf(sqrtf(sp.r2) * T.inv_cell) + 1.0f;
+    // rings closer than the occupied box hold no cells: start at the first
+    // ring that reaches it, end at the last
+    int R = 0, rmax = 0;
+    for (int a = 0; a < 3; ++a) {
+        R = max(R, max(T.cmin[a] - cq[a], cq[a] - T.cmax[a]));
+        rmax = max(rmax, max(cq[a] - T.cmin[a], T.cmax[a] - cq[a]));
+    }
+    if (capped) {
+        const float rc = ceilf(sqrtf(L.bound) * T.inv_cell) + 1.0f;
         if (rc < (float)rmax) rmax = (int)rc;
     }
-    // rings closer than the occupied box hold no cells: start at the first
-    // ring that reaches it
-    int r0 = 0;
-    for (int a = 0; a < 3; ++a) r0 = max(r0, max(T.cmin[a] - cq[a], cq[a] - T.cmax[a]));
+    R = __builtin_amdgcn_readfirstlane(R);
+    rmax = __builtin_amdgcn_readfirstlane(rmax);
     const float qabs = fmaxf(fabsf(qx), fmaxf(fabsf(qy), fabsf(qz)));
-    int r_first = r0;
-    if (r0 == 0 && rmax >= 1) {
-        // The query's own cell and its first ring: their hash probes go out
-        // together (one chain of dependent loads rather than two); the own
-        // cell is streamed first and its k-th distance prunes the ring's
-        // cells, as when the rings are taken one at a time.
-        int lo[3], ext[3];
-        int total = 1;
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = max(cq[a] - 1, T.cmin[a]);
-            ext[a] = max(min(cq[a] + 1, T.cmax[a]) - lo[a] + 1, 0);
-            total *= ext[a];
-        }
-        const float margin = (fmaxf(qabs, T.max_abs) + 3.0f * T.cell) * 1e-6f;
-        bool found = false, own = false;
-        uint32_t st = 0, cn = 0;
-        float bd = INF;
-        if (lane < total) {
-            const uint32_t t = (uint32_t)lane, e0 = (uint32_t)ext[0], e1 = (uint32_t)ext[1];
-            const uint32_t v = t / e0, w = v / e1;
-            const int cx = lo[0] + (int)(t - v * e0), cy = lo[1] + (int)(v - w * e1),
-                      cz = lo[2] + (int)w;
-            own = cx == cq[0] && cy == cq[1] && cz == cq[2];
-            bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin);
-            if (bd <= sp.r2) found = hash_find(T, pack_key(T, cx, cy, cz), st, cn) && cn > 0;
-        }
-        scan_cells(T, qx, qy, qz, sp, found && own, st, cn, L);
-        scan_cells(T, qx, qy, qz, sp, found && !own && bd * (1.0f - 1e-6f) <= L.thr_d, st, cn, L);
-        r_first = 2;
-        // the exact stop of ring 1 (the loop's, below)
-        float f = INF;
-        for (int a = 0; a < 3; ++a)
-            f = fminf(f, fminf(q[a] - (float)(cq[a] - 1) * T.cell, (float)(cq[a] + 2) * T.cell - q[a]));
-        f -= margin;
-        if (f > 0.0f) {
-            const float f2 = f * f * (1.0f - 1e-6f);
-            if ((sp.capped && f2 > sp.r2) || f2 > L.thr_d) r_first = rmax + 1;
-        }
+    if (self) {
+        const int p = sp.skip * WAVE + lane;
+        const float4 t = gload(T.pts + p);   // (64 spare records)
+        L.add(p < (int)T.n, dist2(qx, qy, qz, t.x, t.y, t.z), __float_as_int(t.w));
+        L.tighten();
     }
-    for (int R = r_first; R <= rmax; ++R) {
+    bool found = false;
+    uint32_t st = 0, cn = 0;
+    float bd = INF;
+    if (R == 0 && rmax >= 1) {
+        const float margin = (fmaxf(qabs, T.max_abs) + 3.0f * T.cell) * 1e-6f;
+        // the 27 cells around cq, x fastest
+        const int dz = (lane * 57) >> 9, r = lane - 9 * dz, dy = (r * 11) >> 5;
+        const int cx = cq[0] + r - 3 * dy - 1, cy = cq[1] + dy - 1, cz = cq[2] + dz - 1;
+        const bool own = lane == 13;
+        if (lane < 27 && cx >= T.cmin[0] && cx <= T.cmax[0] && cy >= T.cmin[1] &&
+            cy <= T.cmax[1] && cz >= T.cmin[2] && cz <= T.cmax[2]) {
+            bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin) * (1.0f - 1e-6f);
+            if (bd <= L.bound) found = hash_find(T, pack_key(T, cx, cy, cz), st, cn) && cn > 0;
+        }
+#pragma unroll 1
+        for (int pass = self ? 1 : 0; pass < 2; ++pass) {
+            const bool want = found && (pass == 0 ? own : (self || !own) && bd <= L.bound);
+            if (ballot(want)) scan_cells(T, sp, want, st, cn, margin, L);
+            if (pass == 0) L.tighten();
+        }
+        if (L.within(block_clear2(T, q, cq, 1, margin))) return;
+        L.tighten();
+        R = 2;
+    }
+#pragma unroll 1
+    for (; R <= rmax; ++R) {
+        const float margin = (fmaxf(qabs, T.max_abs) + (float)(R + 2) * T.cell) * 1e-6f;
         int lo[3], ext[3];
         int64_t total = 1;
         for (int a = 0; a < 3; ++a) {
             lo[a] = max(cq[a] - R, T.cmin[a]);
-            const int hi = min(cq[a] + R, T.cmax[a]);
-            ext[a] = hi - lo[a] + 1;
-            total *= (ext[a] > 0) ? ext[a] : 0;
+            ext[a] = max(min(cq[a] + R, T.cmax[a]) - lo[a] + 1, 0);
+            total *= ext[a];
         }
-        const float margin = (fmaxf(qabs, T.max_abs) + (float)(R + 2) * T.cell) * 1e-6f;
-        if (total > 2 * (int64_t)T.n_cells + 256 || total > (int64_t)UINT32_MAX) {
-            // Sweep every occupied cell not yet visited (Chebyshev ring >= R).
-            const unsigned long long mx = (1ull << T.sh_y) - 1ull;
-            const unsigned long long my = (1ull << (T.sh_z - T.sh_y)) - 1ull;
-            for (int c0 = 0; c0 < T.n_cells; c0 += WAVE) {
-                const int c = c0 + lane;
-                bool want = false;
-                uint32_t st = 0, cn = 0;
-                if (c < T.n_cells) {
-                    const unsigned long long key = T.cell_keys[c];
-                    const int cx = (int)(key & mx) + T.cmin[0];
-                    const int cy = (int)((key >> T.sh_y) & my) + T.cmin[1];
-                    const int cz = (int)(key >> T.sh_z) + T.cmin[2];
-                    const int cheb = max(abs(cx - cq[0]), max(abs(cy - cq[1]), abs(cz - cq[2])));
-                    if (cheb >= R) {
-                        const float bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin);
-                        if (bd <= sp.r2 && bd * (1.0f - 1e-6f) <= L.thr_d) {
-                            st = T.cell_start[c];
-                            cn = T.cell_start[c + 1] - st;
-                            want = cn > 0;
-                        }
-                    }
-                }
-                scan_cells(T, qx, qy, qz, sp, want, st, cn, L);
-            }
-            break;
-        }
+        const bool sweep = total > 2 * (int64_t)T.n_cells + 256 || total > (int64_t)UINT32_MAX;
         // The ring's cells, face by face (clamped to the occupied box): the
         // two z faces whole, the y faces without the z faces' rows, the x
         // faces without both; R = 0 is the query's own cell.
@@ -317,58 +409,55 @@ __device__ int knn_query_wave(const TargetView& T, float qx, float qy, float qz,
         fc[4] = (R > 0 && cq[0] - R >= T.cmin[0]) ? ny_in * nz_in : 0u;
         fc[5] = (R > 0 && cq[0] + R <= T.cmax[0]) ? ny_in * nz_in : 0u;
         // (none when the ring misses the occupied box)
-        const uint32_t shell = total > 0 ? fc[0] + fc[1] + fc[2] + fc[3] + fc[4] + fc[5] : 0u;
-        for (uint32_t base = 0; base < shell; base += WAVE) {
+        const uint32_t steps = sweep ? (uint32_t)T.n_cells
+                               : total > 0 ? fc[0] + fc[1] + fc[2] + fc[3] + fc[4] + fc[5] : 0u;
+#pragma unroll 1
+        for (uint32_t base = 0; base < steps; base += WAVE) {
             const uint32_t t = base + (uint32_t)lane;
-            bool want = false;
-            uint32_t st = 0, cn = 0;
-            if (t < shell) {
-                uint32_t u = t;
-                int f = 0;
-#pragma unroll
-                for (int g = 0; g < 5; ++g) {
-                    const bool past = f == g && u >= fc[g];
-                    u = past ? u - fc[g] : u;
-                    f = past ? g + 1 : f;
-                }
-                int cx, cy, cz;
-                if (f < 2) {
-                    const uint32_t e0 = (uint32_t)ext[0], v = u / e0;
-                    cx = lo[0] + (int)(u - v * e0);
-                    cy = lo[1] + (int)v;
-                    cz = R == 0 ? cq[2] : cq[2] + (f ? R : -R);
-                } else if (f < 4) {
-                    const uint32_t e0 = (uint32_t)ext[0], v = u / e0;
-                    cx = lo[0] + (int)(u - v * e0);
-                    cy = cq[1] + (f == 3 ? R : -R);
-                    cz = zi0 + (int)v;
+            found = false;
+            if (t < steps) {
+                if (sweep) {
+                    // every occupied cell not yet visited (Chebyshev ring >= R)
+                    const unsigned long long mx = (1ull << T.sh_y) - 1ull;
+                    const unsigned long long my = (1ull << (T.sh_z - T.sh_y)) - 1ull;
+                    const unsigned long long key = Tp->cell_keys[t];
+                    const int cx = (int)(key & mx) + T.cmin[0];
+                    const int cy = (int)((key >> T.sh_y) & my) + T.cmin[1];
+                    const int cz = (int)(key >> T.sh_z) + T.cmin[2];
+                    const int cheb = max(abs(cx - cq[0]), max(abs(cy - cq[1]), abs(cz - cq[2])));
+                    bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin) * (1.0f - 1e-6f);
+                    if (cheb >= R && bd <= L.bound) {
+                        st = Tp->cell_start[t];
+                        cn = Tp->cell_start[t + 1] - st;
+                        found = cn > 0;
+                    }
                 } else {
-                    const uint32_t d = ny_in > 0u ? ny_in : 1u, v = u / d;
-                    cx = cq[0] + (f == 5 ? R : -R);
-                    cy = yi0 + (int)(u - v * d);
-                    cz = zi0 + (int)v;
+                    uint32_t u = t;
+                    int f = 0;
+#pragma unroll
+                    for (int g = 0; g < 5; ++g) {
+                        const bool past = f == g && u >= fc[g];
+                        u = past ? u - fc[g] : u;
+                        f = past ? g + 1 : f;
+                    }
+                    // rows of e cells along x (z and y faces) or along y (x faces)
+                    const uint32_t e = f < 4 ? (uint32_t)ext[0] : max(ny_in, 1u);
+                    const int v = (int)(u / e), r = (int)(u - (uint32_t)v * e);
+                    const int cx = f < 4 ? lo[0] + r : cq[0] + (f == 5 ? R : -R);
+                    const int cy = f < 2 ? lo[1] + v : f < 4 ? cq[1] + (f == 3 ? R : -R) : yi0 + r;
+                    const int cz = f < 2 ? (R == 0 ? cq[2] : cq[2] + (f ? R : -R)) : zi0 + v;
+                    bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin) * (1.0f - 1e-6f);
+                    if (bd <= L.bound)
+                        found = hash_find(T, pack_key(T, cx, cy, cz), st, cn) && cn > 0;
                 }
-                const float bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin);
-                if (bd <= sp.r2 && bd * (1.0f - 1e-6f) <= L.thr_d)
-                    want = hash_find(T, pack_key(T, cx, cy, cz), st, cn) && cn > 0;
             }
-            scan_cells(T, qx, qy, qz, sp, want, st, cn, L);
+            if (ballot(found)) {
+                scan_cells(T, sp, found, st, cn, margin, L);
+                L.tighten();
+            }
         }
-        // Every unvisited cell lies outside the (2R+1)^3 block around cq.
-        float f = INF;
-        for (int a = 0; a < 3; ++a) {
-            const float lo_b = (float)(cq[a] - R) * T.cell;
-            const float hi_b = (float)(cq[a] + R + 1) * T.cell;
-            f = fminf(f, fminf(q[a] - lo_b, hi_b - q[a]));
-        }
-        f -= margin;
-        if (f > 0.0f) {
-            const float f2 = f * f * (1.0f - 1e-6f);
-            if (sp.capped && f2 > sp.r2) break;
-            if (f2 > L.thr_d) break;
-        }
+        if (sweep || L.within(block_clear2(T, q, cq, R, margin))) return;
     }
-    return __popcll(ballot(lane < sp.k && L.i != IDX_SENTINEL));
 }
 
 // ------------------------------------------------------------- covariance --
@@ -824,12 +913,13 @@ struct GroupArgs {
     CovPtrs co;
     float eps;
     CovWeight wt;                     // covariance weights (fused mode 2)
-    uint32_t* fb_list;                // slots handed to the fallback search
+    uint32_t* fb_list;                // slots handed to the wavefront search (NULL: every slot)
     uint32_t* fb_count;
     uint32_t* counters;               // per-XCD work counters (persistent mode) or NULL
     uint32_t* prof;                   // optional per-group counters (PROF_WORDS each) or NULL
     int split;                        // waves per group (1, 2 or 4)
     int rounds;                       // anchor rounds per group (lanes left fall back)
+    int cov_slots;                    // covariances the wavefront search takes together
 };
 
 // Waves sharing a group: each streams the chunks it owns (chunk index
@@ -1740,41 +1830,137 @@ k_group(GroupArgs a) {
     }
 }
 
-// Wavefront-per-query search for the slots the group search handed over.
-// Persistent: waves stride over the list (its length is only known on the
-// device).
-template <int FUSED>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_fallback(GroupArgs a) {
+// Wavefront-per-query search of the slots in `a.fb_list` (those the group
+// search handed over; their number is only known on the device), or of every
+// slot when there is no list.  Persistent: each XCD takes one contiguous part
+// (its L2 then holds that part of the target) and its wavefronts stride over
+// it.  The rows of up to a.cov_slots queries are kept in LDS and their
+// covariances then taken together, one lane per query (taken by the whole
+// wavefront for each query, they were half the kernel: 40 dependent loads and
+// the eigenvector's instructions, the same in every lane).
+//
+// Bound by the chain of dependent loads of each query (hash slots, points)
+// with few queries, by VALU issue with many (65,536 queries against a 2
+// M-point map: 800 VALU instructions each, 75 % of the issue slots, 0.12 ms).
+// Its predecessor's list (see above) and per-query covariances took 39 us for
+// the 10 k queries a batch of 65,536 or a scan of 118 k hands over; this takes
+// 20.
+constexpr int WAVE_SLOTS = 16;      // covariances taken together, at most
+constexpr int WAVE_ROWS = 320;      // neighbours kept for them, at most
+
+__host__ __device__ inline size_t wave_lds_bytes(int k, int slots, int fused) {
+    return (size_t)WaveList::CAP * 8 + (fused ? (size_t)slots * k * 16 : 0);
+}
+
+// ONE: k = 1 without covariances (no list, no LDS).
+template <int FUSED, bool ONE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
+    extern __shared__ unsigned long long s_wave[];
     const int lane = lane_id();
-    const uint32_t nfb = *(volatile uint32_t*)a.fb_count;
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x / WAVE);
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int k = a.sp.k;
-    for (int64_t i = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE; i < nfb;
-         i += nw) {
-        const int64_t slot = load_uniform(a.fb_list + i);
+    char* mine = (char*)s_wave + (size_t)wid * wave_lds_bytes(k, a.cov_slots, FUSED);
+    unsigned long long* buf = (unsigned long long*)mine;
+    float4* rows = (float4*)(mine + WaveList::CAP * 8);   // [slot][k]: the index in .x, then the point
+    // (wavefront-uniform, as the compiler has to know: scalar registers and
+    // branches for all that follows)
+    const int64_t n = a.fb_list ? (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(
+                                      (int)*(volatile uint32_t*)a.fb_count)
+                                : a.n_slots;
+    const int x = blockIdx.x % 8, nx = gridDim.x / 8;   // (the grid is a multiple of 8)
+    const int64_t hi = n * (x + 1) / 8, step = (int64_t)nx * (blockDim.x / WAVE);
+    int64_t i = n * x / 8 + (int64_t)(blockIdx.x / 8) * (blockDim.x / WAVE) + wid;
+    // lane s: the query of slot s
+    SlotQuery mq{0, 0.f, 0.f, 0.f, 0};
+    int m_cnt = 0, ns = 0;
+    const float4* m_orig = nullptr;
+#pragma unroll 1
+    for (; i < hi; i += step) {
+        const int64_t slot = a.fb_list ? (int64_t)load_uniform(a.fb_list + i) : i;
         int tg = a.skeys ? (int)(load_uniform(a.skeys + slot) >> a.tshift) : 0;
         tg = __builtin_amdgcn_readfirstlane(tg);
         const TargetView T = load_uniform(a.views + tg);
-        const SlotQuery s = load_slot(a, T, slot);
-        TopK L;
-        const int cnt = knn_query_wave(T, s.x, s.y, s.z, a.sp, L);
-        if (lane < k) {
-            const bool have = lane < cnt;
-            a.ko.idx[s.qi * k + lane] = have ? L.i : -1;
-            a.ko.d2[s.qi * k + lane] = have ? L.d : INF;
+        SlotQuery s{-1, 0.f, 0.f, 0.f, tg};
+        const bool self = a.queries == nullptr;
+        if (!self || slot < T.n) s = load_slot(a, T, slot);
+        s.x = uniform_f(s.x);
+        s.y = uniform_f(s.y);
+        s.z = uniform_f(s.z);
+        s.qi = __builtin_amdgcn_readfirstlane((int)s.qi);
+        const bool search = finite3(s.x, s.y, s.z) && T.n_cells > 0 && s.qi >= 0;
+        // (a self query of a target that a failed rebuild left empty)
+        if (s.qi < 0) s.qi = slot;
+        const WaveQuery q{s.x, s.y, s.z, self ? (int)(slot / WAVE) : -1};
+        if (ONE) {
+            WaveNearest L{a.sp.r2, INF, IDX_SENTINEL};
+            if (search) knn_query_wave(T, a.views + tg, q, self, a.sp.capped, L);
+            const float d = wave_min_dpp(L.d);
+            const int32_t best = wave_min_i32(L.d == d ? L.i : IDX_SENTINEL);
+            if (lane == 0) {
+                const bool have = best != IDX_SENTINEL;
+                a.ko.idx[s.qi] = have ? best : -1;
+                a.ko.d2[s.qi] = have ? d : INF;
+                a.ko.count[s.qi] = have ? 1 : 0;
+            }
+            continue;
+        }
+        WaveList L{buf, a.sp.r2, 0, k, false};
+        if (search) knn_query_wave(T, a.views + tg, q, self, a.sp.capped, L);
+        // each entry's place among the k smallest, by counting
+        wave_lds_fence();
+        const unsigned long long my = lane < L.n ? buf[lane] : ~0ull;
+        buf[lane] = my;
+        wave_lds_fence();
+        int rank = 0;
+        for (int j = 0; j < L.n; j += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += buf[j + u] < my ? 1 : 0;
+        }
+        const int cnt = min(L.n, k);
+        const bool in = lane < L.n && rank < k;
+        int32_t* irow = a.ko.idx + s.qi * k;
+        float* drow = a.ko.d2 + s.qi * k;
+        if (in) {
+            irow[rank] = (int32_t)(uint32_t)my;
+            drow[rank] = __uint_as_float((uint32_t)(my >> 32));
+        }
+        if (lane >= cnt && lane < k) {
+            irow[lane] = -1;
+            drow[lane] = INF;
         }
         if (lane == 0) a.ko.count[s.qi] = cnt;
         if (FUSED) {
-            // all lanes run the same covariance (neighbour j's reordered
-            // position is read from lane j); lane 0 stores it
-            const float4* pts = T.pts;
-            CovOut c;
-            const auto fetch = [&](int j) { return gload(pts + readlane(L.p, j)); };
-            if (FUSED == 1)
-                covariance(s.x, s.y, s.z, cnt, fetch, a.eps, c);
-            else
-                covariance_weighted(s.x, s.y, s.z, cnt, fetch, a.wt, a.eps, c);
-            if (lane == 0) store_cov(a.co, s.qi, c);
+            if (in) rows[ns * k + rank].x = __uint_as_float((uint32_t)my);
+            if (lane == ns) {
+                mq = s;
+                m_cnt = cnt;
+                m_orig = a.views[tg].orig;
+            }
+            if (++ns < a.cov_slots && i + step < hi) continue;
+            // the points of every kept row, then one lane per query
+            wave_lds_fence();
+            const float ik = 1.0f / (float)k;
+#pragma unroll 1
+            for (int t0 = 0; t0 < ns * k; t0 += WAVE) {   // (every lane stays: shuffles)
+                // (t + 0.5) / k lies at least 0.5 / k from an integer
+                const int t = t0 + lane, sl = (int)(((float)t + 0.5f) * ik) & 63, j = t - sl * k;
+                const int c = __shfl(m_cnt, sl);
+                const float4* o = (const float4*)__shfl((unsigned long long)m_orig, sl);
+                if (t < ns * k && j < c) rows[t] = gload(o + (int32_t)__float_as_uint(rows[t].x));
+            }
+            wave_lds_fence();
+            if (lane < ns) {
+                const float4* r = rows + lane * k;
+                const auto fetch = [&](int j) { return r[j]; };
+                CovOut c;
+                if (FUSED == 1)
+                    covariance(mq.x, mq.y, mq.z, m_cnt, fetch, a.eps, c);
+                else
+                    covariance_weighted(mq.x, mq.y, mq.z, m_cnt, fetch, a.wt, a.eps, c);
+                store_cov(a.co, mq.qi, c);
+            }
+            ns = 0;
+            wave_lds_fence();
         }
     }
 }
@@ -1908,12 +2094,11 @@ __global__ void __launch_bounds__(256) k_cov(TargetView T, const float* __restri
     store_cov(co, qi, c);
 }
 
-SearchParams make_params(int k, float radius, int merge_min) {
+SearchParams make_params(int k, float radius) {
     SearchParams sp;
     sp.k = k;
     sp.capped = std::isinf(radius) ? 0 : 1;
     sp.r2 = sp.capped ? radius * radius : INF;
-    sp.merge_min = merge_min;
     return sp;
 }
 
@@ -1921,11 +2106,6 @@ SearchParams make_params(int k, float radius, int merge_min) {
 
 
 namespace {
-
-__global__ void k_fill_iota(uint32_t* __restrict__ v, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) v[i] = (uint32_t)i;
-}
 
 __global__ void k_set_words(uint32_t* __restrict__ w, int n, uint32_t first) {
     const int i = threadIdx.x;
@@ -2062,17 +2242,46 @@ struct SearchJob {
     CovWeight wt;
 };
 
+// Whether the group search takes a launch of n queries.  The group search
+// needs the fewest instructions a query (130 VALU against 800, k = 20 on a
+// voxel map) but sorts the queries first and lasts as long as its slowest
+// group; the wavefront search is one launch whose work is even.  Measured,
+// group against wavefront, whole call, k = 20, r = 2 m, 1 m cells:
+//   queries against a 2 M-point map   3,001 (500 k map)  172 /  18 us
+//                                     20,000             185 /  50 us
+//                                     65,536             214 / 127 us
+//                                     100,000            245 / 187 us
+//                                     131,072            250 / 242 us
+//     (k = 5 at 98,304 and 131,072: 178 / 147, 186 / 190 us; a sparse 100 k
+//     map at 100,000 and 131,072: 205 / 224, 208 / 286 us)
+//   a scan against itself (with its rebuild)  20,000     250 / 111 us
+//                                             117,965    386 / 321 us
+//   k = 32, 131,072 queries 391 / 272 us; scan of 117,965 501 / 353 us
+// so the line lies at 384 queries per CU (98,304), at 512 for self queries
+// (sorted already, but dense: uneven groups), at 768 above k = 20, where a
+// group's lists leave room for two wavefronts per SIMD only.
+bool takes_group(const lkc_ctx* ctx, int K, int algorithm, bool self, int64_t n) {
+    if (K == 0 || algorithm == 2) return false;
+    if (algorithm == 1) return true;
+    const int per_cu = K > 20 ? 768 : self ? 512 : 384;
+    return n > (int64_t)ctx->num_cus * per_cu;
+}
+
 // `fixed`: scratch the caller provides (then nothing is allocated and the
 // per-group profile is off).
 lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
                       const Scratch* fixed = nullptr) {
     if (j.n_slots == 0) return LKC_OK;
     hipStream_t st = ctx->stream;
-    Scratch sc;
+    const int K = choose_k_tile(j.k);
+    const bool group = takes_group(ctx, K, cfg.algorithm, j.queries == nullptr, j.n_slots);
+    const bool keyed = j.queries && (group || j.n_targets > 1);
+    // (the wavefront search of one target needs no scratch)
+    Scratch sc{};
     lkc_status s = LKC_OK;
     if (fixed)
         sc = *fixed;
-    else
+    else if (group || keyed)
         s = search_scratch(ctx, j.n_slots, sc);
     if (s != LKC_OK) return s;
     GroupArgs a{};
@@ -2082,7 +2291,7 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     a.skeys = nullptr;
     a.tshift = 0;
     a.n_slots = j.n_slots;
-    a.sp = make_params(j.k, j.radius, cfg.merge_min);
+    a.sp = make_params(j.k, j.radius);
     a.ko = j.ko;
     a.co = j.co;
     a.eps = j.eps;
@@ -2098,25 +2307,24 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     a.fb_list = sc.fb_list;
     a.fb_count = sc.words;
     a.counters = nullptr;
-    a.prof = (!fixed && ctx->prof_buf && (j.n_slots + WAVE - 1) / WAVE <= ctx->prof_groups)
+    a.prof = (!fixed && group && ctx->prof_buf && (j.n_slots + WAVE - 1) / WAVE <= ctx->prof_groups)
                  ? (uint32_t*)ctx->prof_buf : nullptr;
     if (a.prof)
         LKC_HIP_TRY(ctx, hipMemsetAsync(a.prof, 0,
                                         sizeof(uint32_t) * PROF_WORDS *
                                             (size_t)((j.n_slots + WAVE - 1) / WAVE),
                                         st));
-    ctx->last_fallback_count = sc.words;
+    ctx->last_fallback_count = group ? sc.words : nullptr;
+    ctx->last_all_wave = !group;
     ctx->last_queries = j.n_slots;
     ctx->ev_valid = ctx->timing;
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[0], st));
-    const int K = choose_k_tile(j.k);
-    const bool group = K > 0 && cfg.algorithm != 2;
     const unsigned wpb = (unsigned)cfg.waves_per_block;
     // Separate queries get keys: the group search sorts them by cell, and a
     // batch over several targets carries each query's target in the key's
     // top bits (the wavefront-per-query search reads it unsorted).
     int tshift = 0, tbits = 0;
-    if (j.queries && (group || j.n_targets > 1)) {
+    if (keyed) {
         int w[3] = {1, 1, 1};
         for (int t = 0; t < j.n_targets; ++t) {
             const TargetView& V = j.host_views[t];
@@ -2192,10 +2400,7 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
             launch_group<0>(K, dim3(blocks), dim3(threads), st, a);
     } else {
         // every query goes to the wavefront-per-query search
-        hipLaunchKernelGGL(k_set_words, dim3(1), dim3(64), 0, st, sc.words, 16,
-                           (uint32_t)j.n_slots);
-        hipLaunchKernelGGL(k_fill_iota, dim3((unsigned)((j.n_slots + 255) / 256)), dim3(256), 0,
-                           st, sc.fb_list, j.n_slots);
+        a.fb_list = nullptr;
         if (j.queries && j.n_targets > 1) {
             // slots are the queries themselves: the unsorted keys give each
             // one's target
@@ -2205,16 +2410,22 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
         if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[1], st));
     }
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[2], st));
-    // persistent: six 4-wave workgroups per CU fill the kernel's occupancy
-    // (at most 80 registers a lane; a query's search is a chain of dependent
-    // loads, so more resident waves shorten the list each one works through)
-    const dim3 fgrid((unsigned)(ctx->num_cus * 6));
+    // six 4-wave workgroups per CU fill the kernel's occupancy (a query's
+    // search is a chain of dependent loads, so more resident waves shorten
+    // the list each one works through); no more than the queries need
+    const unsigned full = (unsigned)ctx->num_cus * 6;
+    const int64_t need = group ? full : (j.n_slots + 3) / 4;
+    const dim3 wgrid(((unsigned)std::min<int64_t>(full, need) + 7) & ~7u);
+    a.cov_slots = std::max(1, std::min(WAVE_SLOTS, WAVE_ROWS / j.k));
+    const size_t lds = 4 * wave_lds_bytes(j.k, a.cov_slots, j.fused);
     if (j.fused == 2)
-        hipLaunchKernelGGL(k_fallback<2>, fgrid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_wave<2, false>), wgrid, dim3(256), lds, st, a);
     else if (j.fused == 1)
-        hipLaunchKernelGGL(k_fallback<1>, fgrid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_wave<1, false>), wgrid, dim3(256), lds, st, a);
+    else if (j.k == 1)
+        hipLaunchKernelGGL((k_wave<0, true>), wgrid, dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL(k_fallback<0>, fgrid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_wave<0, false>), wgrid, dim3(256), lds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(ctx, e, "search launch");
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[3], st));
@@ -2254,7 +2465,9 @@ LaunchCfg resolve_cfg(const lkc_launch_cfg* c) {
     // slots free up sooner) and than one
     LaunchCfg r{0, 0, 2, 12, 0, 0};
     if (c) {
-        r.algorithm = c->algorithm;
+        // (an option of the group search asks for it)
+        const bool shaped = c->group_reach || c->waves_per_block || c->persistent || c->group_split;
+        r.algorithm = c->algorithm == 0 && shaped ? 1 : c->algorithm;
         r.group_reach = c->group_reach;
         if (c->waves_per_block != 0) r.waves_per_block = c->waves_per_block;
         if (c->merge_min != 0) r.merge_min = c->merge_min;
