@@ -8,10 +8,11 @@
 //   T <- exp(delta^) T, delta = (omega, v)),
 //   H = sum J^T W J,  b = sum J^T W d.
 //
-// One linearisation is four launches on the context's stream:
-//   1. transform the source by T (float32, for the search only);
-//   2. nearest target point of each transformed point (the group search
-//      with k = 1 and the correspondence radius);
+// One linearisation is three or four launches on the context's stream:
+//   1. transform the source by T (float32, for the search only; a launch of
+//      its own only when the search sorts its queries);
+//   2. nearest target point of each transformed point (the search with k = 1
+//      and the correspondence radius);
 //   3. per source point, in FP64: the residual, the 3x3 combined covariance
 //      and its inverse (adjugate), and the point's share of H (upper
 //      triangle), b, E; summed per thread (grid-stride), per wavefront
@@ -48,16 +49,14 @@ struct GicpArgs {
 };
 
 __global__ void __launch_bounds__(256) k_gicp_transform(const float* __restrict__ src, int64_t n,
-                                                        float r00, float r01, float r02, float r10,
-                                                        float r11, float r12, float r20, float r21,
-                                                        float r22, float t0, float t1, float t2,
-                                                        float* __restrict__ out) {
+                                                        RigidF X, float* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float x = src[3 * i], y = src[3 * i + 1], z = src[3 * i + 2];
-    out[3 * i] = fmaf(r02, z, fmaf(r01, y, fmaf(r00, x, t0)));
-    out[3 * i + 1] = fmaf(r12, z, fmaf(r11, y, fmaf(r10, x, t1)));
-    out[3 * i + 2] = fmaf(r22, z, fmaf(r21, y, fmaf(r20, x, t2)));
+    float x = src[3 * i], y = src[3 * i + 1], z = src[3 * i + 2];
+    rigid_apply(X, x, y, z);
+    out[3 * i] = x;
+    out[3 * i + 1] = y;
+    out[3 * i + 2] = z;
 }
 
 // Adds source point i's share of H, b and E to acc[0..27]; returns 0 (no
@@ -181,22 +180,42 @@ __global__ void __launch_bounds__(GICP_THREADS) k_gicp_reduce(GicpArgs a) {
     }
 }
 
-// system: H [6][6] row-major, b [6], E, count, rejected (45 doubles)
-__global__ void k_gicp_final(const double* __restrict__ partials, int blocks,
-                             double* __restrict__ system) {
-    const int e = threadIdx.x;
-    if (e >= GICP_ACC) return;
+// system: H [6][6] row-major, b [6], E, count, rejected (45 doubles).  One
+// workgroup: 32 threads per accumulator share the partial rows (thread c takes
+// rows c, c + 32, ... in order, at most 32 of them, loaded together), then
+// the 32 sums are added pairwise.  Bound by the latency of one round of loads;
+// one thread per accumulator adding every row took 62 us for 256 rows, this
+// takes 5.
+constexpr int FINAL_PARTS = 32;
+
+__global__ void __launch_bounds__(1024) k_gicp_final(const double* __restrict__ partials,
+                                                     int blocks, double* __restrict__ system) {
+    __shared__ double sum[FINAL_PARTS][GICP_ACC + 1];
+    const int e = threadIdx.x % 32, c = threadIdx.x / 32;
     double s = 0.0;
-    for (int b = 0; b < blocks; ++b) s += partials[(int64_t)b * GICP_ACC + e];
+    if (e < GICP_ACC) {
+#pragma unroll 8
+        for (int b = c; b < blocks; b += FINAL_PARTS) s += partials[(int64_t)b * GICP_ACC + e];
+        sum[c][e] = s;
+    }
+#pragma unroll
+    for (int h = FINAL_PARTS / 2; h > 0; h >>= 1) {
+        __syncthreads();
+        if (e < GICP_ACC && c < h) {
+            s += sum[c + h][e];
+            sum[c][e] = s;
+        }
+    }
+    if (c != 0 || e >= GICP_ACC) return;
     if (e < 21) {
         int r = 0, k = e;
         while (k >= 6 - r) {
             k -= 6 - r;
             ++r;
         }
-        const int c = r + k;
-        system[6 * r + c] = s;
-        system[6 * c + r] = s;
+        const int col = r + k;
+        system[6 * r + col] = s;
+        system[6 * col + r] = s;
     } else {
         system[36 + (e - 21)] = s;
     }
@@ -251,12 +270,21 @@ lkc_status launch_gicp_linearize(lkc_ctx* ctx, const lkc_target* t, const float*
     hipStream_t st = ctx->stream;
     int32_t* cidx = corr ? corr : g.idx;
     if (n > 0) {
-        const unsigned tb = (unsigned)((n + 255) / 256);
-        hipLaunchKernelGGL(k_gicp_transform, dim3(tb), dim3(256), 0, st, src, n, (float)T[0],
-                           (float)T[1], (float)T[2], (float)T[4], (float)T[5], (float)T[6],
-                           (float)T[8], (float)T[9], (float)T[10], (float)T[3], (float)T[7],
-                           (float)T[11], g.queries);
-        s = launch_knn(ctx, t, g.queries, n, 1, max_dist, cidx, g.d2, g.count, cfg);
+        // the search's float32 rows of T; the wavefront search applies them as
+        // it loads a query, the group search (which sorts the queries first)
+        // reads the transformed source
+        RigidF X;
+        for (int r = 0; r < 3; ++r) {
+            for (int c = 0; c < 3; ++c) X.r[3 * r + c] = (float)T[4 * r + c];
+            X.t[r] = (float)T[4 * r + 3];
+        }
+        if (knn_takes_group(ctx, 1, n, cfg)) {
+            hipLaunchKernelGGL(k_gicp_transform, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
+                               st, src, n, X, g.queries);
+            s = launch_knn(ctx, t, g.queries, n, 1, max_dist, cidx, g.d2, g.count, cfg);
+        } else {
+            s = launch_knn(ctx, t, src, n, 1, max_dist, cidx, g.d2, g.count, cfg, &X);
+        }
         if (s != LKC_OK) return s;
     }
     GicpArgs a{};
@@ -276,7 +304,7 @@ lkc_status launch_gicp_linearize(lkc_ctx* ctx, const lkc_target* t, const float*
     ctx->ev_reduce_valid = ctx->timing;
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[4], st));
     hipLaunchKernelGGL(k_gicp_reduce, dim3(blocks), dim3(GICP_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_gicp_final, dim3(1), dim3(64), 0, st, (const double*)g.partials, blocks,
+    hipLaunchKernelGGL(k_gicp_final, dim3(1), dim3(32 * FINAL_PARTS), 0, st, (const double*)g.partials, blocks,
                        system ? system : g.system);
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[5], st));
     hipError_t e = hipGetLastError();
@@ -377,10 +405,9 @@ lkc_status gicp_align(lkc_ctx* ctx, const lkc_target* t, const float* tcov, cons
     for (int i = 0; i < 16; ++i) T[i] = T0[i];
     lkc_gicp_stats st{};
     for (int it = 0; it < max_iters; ++it) {
-        s = launch_gicp_linearize(ctx, t, tcov, src, scov, n, T, max_dist, nullptr, g.system, cfg);
+        // (the last kernel writes the system into the pinned host words: no copy launch)
+        s = launch_gicp_linearize(ctx, t, tcov, src, scov, n, T, max_dist, nullptr, sys, cfg);
         if (s != LKC_OK) return s;
-        LKC_HIP_TRY(ctx, hipMemcpyAsync(sys, g.system, 8 * LKC_GICP_SYSTEM_WORDS,
-                                        hipMemcpyDeviceToHost, ctx->stream));
         LKC_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         st.iterations = it + 1;
         st.error = sys[42];

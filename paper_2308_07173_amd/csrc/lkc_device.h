@@ -121,6 +121,19 @@ __device__ __forceinline__ float dist2(float qx, float qy, float qz, float tx, f
     return fmaf(dz, dz, fmaf(dy, dy, dx * dx));
 }
 
+// A rigid transform in float32, applied in one order everywhere.
+struct RigidF {
+    float r[9], t[3];
+};
+__device__ __forceinline__ void rigid_apply(const RigidF& X, float& x, float& y, float& z) {
+    const float a = fmaf(X.r[2], z, fmaf(X.r[1], y, fmaf(X.r[0], x, X.t[0])));
+    const float b = fmaf(X.r[5], z, fmaf(X.r[4], y, fmaf(X.r[3], x, X.t[1])));
+    const float c = fmaf(X.r[8], z, fmaf(X.r[7], y, fmaf(X.r[6], x, X.t[2])));
+    x = a;
+    y = b;
+    z = c;
+}
+
 // Lexicographic order on (squared distance, original index): the lower index
 // wins an exact tie.
 __device__ __forceinline__ bool key_less(float da, int32_t ia, float db, int32_t ib) {

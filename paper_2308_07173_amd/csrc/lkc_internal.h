@@ -213,9 +213,12 @@ struct CovWeight {
     int kind;     // LKC_WEIGHT_*
     float scale;  // RBF sigma; Gaussian 1 / (2 sigma^2); Laplacian 1 / sigma
 };
+// `move`: the queries are moved by it first (only where knn_takes_group says
+// that the launch does not go to the group search).
 lkc_status launch_knn(lkc_ctx* ctx, const lkc_target* t, const float* queries, int64_t q,
                       int32_t k, float radius, int32_t* idx, float* d2, int32_t* count,
-                      const LaunchCfg& cfg);
+                      const LaunchCfg& cfg, const RigidF* move = nullptr);
+bool knn_takes_group(const lkc_ctx* ctx, int32_t k, int64_t q, const LaunchCfg& cfg);
 lkc_status launch_knn_self(lkc_ctx* ctx, const lkc_target* t, int32_t k, float radius,
                            float eps, int32_t* idx, float* d2, int32_t* count, float* mean,
                            float* cov, float* reg, uint8_t* valid, const LaunchCfg& cfg);

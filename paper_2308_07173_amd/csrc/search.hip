@@ -920,6 +920,8 @@ struct GroupArgs {
     int split;                        // waves per group (1, 2 or 4)
     int rounds;                       // anchor rounds per group (lanes left fall back)
     int cov_slots;                    // covariances the wavefront search takes together
+    int moved;                        // the wavefront search moves its queries by `move`
+    RigidF move;
 };
 
 // Waves sharing a group: each streams the chunks it owns (chunk index
@@ -1883,6 +1885,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         SlotQuery s{-1, 0.f, 0.f, 0.f, tg};
         const bool self = a.queries == nullptr;
         if (!self || slot < T.n) s = load_slot(a, T, slot);
+        if (ONE && a.moved) rigid_apply(a.move, s.x, s.y, s.z);
         s.x = uniform_f(s.x);
         s.y = uniform_f(s.y);
         s.z = uniform_f(s.z);
@@ -2240,6 +2243,7 @@ struct SearchJob {
     KnnPtrs ko;
     CovPtrs co;
     CovWeight wt;
+    const RigidF* move;   // k = 1 without covariances, wavefront search: moves the queries
 };
 
 // Whether the group search takes a launch of n queries.  The group search
@@ -2296,6 +2300,8 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     a.co = j.co;
     a.eps = j.eps;
     a.wt = j.wt;
+    a.moved = j.move != nullptr;
+    if (j.move) a.move = *j.move;
     // Self queries: a group of consecutive target points that straddles two
     // clusters is cheap to serve in a second round (measured: fewer
     // wavefront-per-query searches and a shorter search); past three rounds
@@ -2477,13 +2483,18 @@ LaunchCfg resolve_cfg(const lkc_launch_cfg* c) {
     return r;
 }
 
+bool knn_takes_group(const lkc_ctx* ctx, int32_t k, int64_t q, const LaunchCfg& cfg) {
+    return takes_group(ctx, choose_k_tile(k), cfg.algorithm, false, q);
+}
+
 lkc_status launch_knn(lkc_ctx* ctx, const lkc_target* t, const float* queries, int64_t q,
                       int32_t k, float radius, int32_t* idx, float* d2, int32_t* count,
-                      const LaunchCfg& cfg) {
+                      const LaunchCfg& cfg, const RigidF* move) {
     lkc_status s = check_cfg(ctx, cfg);
     if (s != LKC_OK) return s;
     SearchJob j{t->view_dev, &t->view, 1, queries, q, nullptr, nullptr, k, radius, 0.0f, 0,
                 KnnPtrs{idx, d2, count}, CovPtrs{nullptr, nullptr, nullptr, nullptr}};
+    j.move = move;
     return run_search(ctx, j, cfg);
 }
 
