@@ -15,10 +15,11 @@
 // points closer than eps (d2 <= eps^2, float32, the search's fma order).
 // The points are bucketed in a grid of 1.25 eps cells (built with the target
 // build, so every pair within eps lies in adjacent cells even after float32
-// rounding of the cell coordinates); one thread per point tests the points
-// of the 27 surrounding cells with a smaller original index and joins the
-// two components in a lock-free union-find (the larger root is hooked under
-// the smaller with a compare-and-swap, parent reads bypass the per-CU cache).
+// rounding of the cell coordinates); the points of the 27 surrounding cells
+// with a smaller original index are tested twice: first for the smallest of
+// them, which becomes the point's parent, then to join the two trees of every
+// pair in a lock-free union-find (the larger root is hooked under the smaller
+// with a compare-and-swap, parent reads bypass the per-CU cache).
 // Roots are therefore the smallest index of their component; a final pass
 // writes every point's root as its label.
 #include <algorithm>
@@ -132,13 +133,19 @@ __device__ __forceinline__ int32_t parent_load(const int32_t* par, int32_t x) {
 
 // Root of x, reading the parents coherently (the union phase runs
 // concurrently with other hooks).  Parents only ever point to smaller
-// indices, so the walk ends.
+// indices, so the walk ends.  Every node passed is pointed at its grandparent:
+// only roots are ever hooked, so a node that has a parent may be given any
+// ancestor at any time.
 __device__ __forceinline__ int32_t uf_root(int32_t* par, int32_t x) {
-    for (;;) {
-        const int32_t p = parent_load(par, x);
-        if (p == x) return x;
+    int32_t p = parent_load(par, x);
+    while (p != x) {
+        const int32_t g = parent_load(par, p);
+        if (g == p) return p;
+        __hip_atomic_store(par + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         x = p;
+        p = g;
     }
+    return x;
 }
 
 // Join the components of a and b: hook the larger root under the smaller.
@@ -158,87 +165,225 @@ __device__ __forceinline__ void uf_union(int32_t* par, int32_t a, int32_t b, UvM
     atomicAdd(&m->spins, 1u);
 }
 
-__global__ void k_parent_init(int32_t* __restrict__ par, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) par[i] = (int32_t)i;
-}
+// Both passes over the pairs take 32 lanes per reordered point, one to each of
+// the 27 surrounding cells, and test the points of that cell with a smaller
+// original index.  With `mask` (the grid then holds every point, indexed by
+// original index) only kept points join.
+constexpr int UNION_LANES = 32;
 
-// One thread per reordered point: join it with every point of the 27
-// surrounding cells that has a smaller original index and lies within eps.
-// With `mask` (the grid then holds every point, indexed by original index)
-// only kept points join.
-__global__ void __launch_bounds__(WT) k_cluster_union(const TargetView* __restrict__ Tp,
-                                                      float e2, const uint8_t* __restrict__ mask,
-                                                      int32_t* __restrict__ par,
-                                                      UvMeta* __restrict__ m) {
-    const TargetView T = load_uniform(Tp);
-    const int64_t s = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x;
-    if (s >= T.n) return;
-    const float4 p = T.pts[s];
+struct ClusterArgs {
+    const TargetView* views;
+    float e2;
+    const uint8_t* mask;
+    int32_t* par;
+    UvMeta* m;
+    int64_t n;
+};
+
+// Calls f(i, j) for this lane's pairs within eps (j < i); returns the lane's
+// point, -1 when there is none.
+template <typename F>
+__device__ __forceinline__ int32_t cluster_pairs(const ClusterArgs& a, F f) {
+    const TargetView T = load_uniform(a.views);
+    const int64_t s = ((int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x) / UNION_LANES;
+    const int c = threadIdx.x % UNION_LANES;
+    if (s >= T.n) return -1;
+    const float4 p = gload(T.pts + s);
     const int32_t i = __float_as_int(p.w);
-    if (mask && !mask[i]) return;
-    const int cx = cell_coord(p.x, T.inv_cell), cy = cell_coord(p.y, T.inv_cell),
-              cz = cell_coord(p.z, T.inv_cell);
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int x = cx + dx, y = cy + dy, z = cz + dz;
-                if (x < T.cmin[0] || x > T.cmax[0] || y < T.cmin[1] || y > T.cmax[1] ||
-                    z < T.cmin[2] || z > T.cmax[2])
-                    continue;
-                uint32_t st, cn;
-                if (!hash_find(T, pack_key(T, x, y, z), st, cn)) continue;
-                for (uint32_t t = st; t < st + cn; ++t) {
-                    const float4 q = T.pts[t];
-                    const int32_t j = __float_as_int(q.w);
-                    if (j < i && (!mask || mask[j]) && dist2(p.x, p.y, p.z, q.x, q.y, q.z) <= e2)
-                        uf_union(par, i, j, m);
-                }
-            }
+    const int dz = (c * 57) >> 9, r = c - 9 * dz, dy = (r * 11) >> 5;   // c / 9, r / 3
+    const int x = cell_coord(p.x, T.inv_cell) + r - 3 * dy - 1;
+    const int y = cell_coord(p.y, T.inv_cell) + dy - 1;
+    const int z = cell_coord(p.z, T.inv_cell) + dz - 1;
+    uint32_t st, cn;
+    if (c < 27 && !(a.mask && !a.mask[i]) && x >= T.cmin[0] && x <= T.cmax[0] &&
+        y >= T.cmin[1] && y <= T.cmax[1] && z >= T.cmin[2] && z <= T.cmax[2] &&
+        hash_find(T, pack_key(T, x, y, z), st, cn)) {
+        for (uint32_t t = st; t < st + cn; ++t) {
+            const float4 q = gload(T.pts + t);
+            const int32_t j = __float_as_int(q.w);
+            if (j < i && (!a.mask || a.mask[j]) &&
+                dist2(p.x, p.y, p.z, q.x, q.y, q.z) <= a.e2)
+                f(i, j);
+        }
+    }
+    return i;
 }
 
-// mask compaction: flags, then (after the exclusive scan) the kept points
-// and their indices in ascending order
-__global__ void __launch_bounds__(WT) k_mask_flags(const uint8_t* __restrict__ mask, int64_t n,
-                                                   uint32_t* __restrict__ flags) {
+// First pass: every point's parent is the smallest of its neighbours (or
+// itself).  No two threads write the same word, so nothing contends, and most
+// of the pairs are then in one tree already.
+__global__ void __launch_bounds__(WT) k_cluster_seed(ClusterArgs a) {
+    if (load_uniform(a.views).n == 0) {
+        // (a rebuild that failed on the device left the grid empty: every
+        // point its own root)
+        const int64_t g = (int64_t)blockIdx.x * WT + threadIdx.x;
+        if (g < a.n) a.par[g] = (int32_t)g;
+        return;
+    }
+    int32_t least = INT32_MAX;
+    const int32_t i = cluster_pairs(a, [&](int32_t, int32_t j) { least = min(least, j); });
+#pragma unroll
+    for (int h = UNION_LANES / 2; h > 0; h >>= 1) least = min(least, __shfl_xor(least, h));
+    if (i >= 0 && threadIdx.x % UNION_LANES == 0) a.par[i] = min(least, i);
+}
+
+// Points every node at its root: each thread takes its node's grandparent for
+// parent until that is a root, and as all do so at once the chains halve with
+// every step.
+__global__ void __launch_bounds__(WT) k_cluster_flatten(int32_t* __restrict__ par, int64_t n,
+                                                        const uint8_t* __restrict__ mask) {
     const int64_t i = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (i < n) flags[i] = mask[i] ? 1u : 0u;
+    if (i >= n || (mask && !mask[i])) return;
+    int32_t p = parent_load(par, (int32_t)i);
+    for (;;) {
+        const int32_t g = parent_load(par, p);
+        if (g == p) return;
+        __hip_atomic_store(par + i, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        p = g;
+    }
+}
+
+// Second pass, on flattened trees: of every pair in two trees, the larger
+// root is given the smallest of the roots that it meets for parent (an atomic
+// minimum: nothing is retried, and a root that another pair already gave a
+// smaller one is left alone).
+__global__ void __launch_bounds__(WT) k_cluster_hook(ClusterArgs a) {
+    cluster_pairs(a, [&](int32_t i, int32_t j) {
+        const int32_t u = a.par[i], v = a.par[j];
+        const int32_t hi = max(u, v), lo = min(u, v);
+        if (lo != hi && a.par[hi] > lo) atomicMin(a.par + hi, lo);
+    });
+}
+
+// Last pass: joins the trees of every pair that are still two.  Two nodes that
+// ever had one parent are in one tree: an ordinary load, old as the caches may
+// have it, settles nearly every pair.
+//
+// The passes are bound by latency: the chains of probes, candidates and parent
+// walks.  One pass of joins over single points, one thread per point (a few
+// thousand kept points of a scan leave most of the chip idle), took 323 us for
+// the 30,011 voxels of a scan; the same with 32 lanes per point and its chains
+// halved 104, nearly all of it parent walks; seeded and flattened first, with
+// the test of the parents, 85; with a hook before the joins 54 (10
+// seed, 5 + 5 flatten, 13 hook, 21 joins).
+__global__ void __launch_bounds__(WT) k_cluster_union(ClusterArgs a) {
+    cluster_pairs(a, [&](int32_t i, int32_t j) {
+        if (a.par[i] != a.par[j]) uf_union(a.par, i, j, a.m);
+    });
+}
+
+// All passes: the parents of the grid's points, at most two or three joins
+// from their roots.
+void launch_cluster(hipStream_t st, const ClusterArgs& a) {
+    const int64_t n = a.n;
+    const dim3 pairs(grid_of(n * UNION_LANES, WT)), points(grid_of(n, WT));
+    hipLaunchKernelGGL(k_cluster_seed, pairs, dim3(WT), 0, st, a);
+    hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
+    hipLaunchKernelGGL(k_cluster_hook, pairs, dim3(WT), 0, st, a);
+    hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
+    hipLaunchKernelGGL(k_cluster_union, pairs, dim3(WT), 0, st, a);
+}
+
+// Mask compaction in ascending order, in two launches: kept points per tile,
+// then every tile adds up the tiles before it and writes its own points (the
+// labels of the points left out too).  Up to RAW_MASK_TILES tiles; past that
+// their counts are scanned in between.
+constexpr int MASK_TILE = 1024;
+constexpr int RAW_MASK_TILES = 4096;
+
+__global__ void __launch_bounds__(WT) k_mask_count(const uint8_t* __restrict__ mask, int64_t n,
+                                                   uint32_t* __restrict__ counts) {
+    __shared__ uint32_t s_c[WT / WAVE];
+    const int64_t b = (int64_t)blockIdx.x * MASK_TILE;
+    uint32_t c = 0;
+#pragma unroll
+    for (int u = 0; u < MASK_TILE / WT; ++u) {
+        const int64_t i = b + u * WT + threadIdx.x;
+        c += (uint32_t)__popcll(ballot(i < n && mask[i] != 0));
+    }
+    if (threadIdx.x % WAVE == 0) s_c[threadIdx.x / WAVE] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) counts[blockIdx.x] = s_c[0] + s_c[1] + s_c[2] + s_c[3];
 }
 
 __global__ void __launch_bounds__(WT) k_mask_compact(const float* __restrict__ pts,
                                                      const uint8_t* __restrict__ mask, int64_t n,
-                                                     const uint32_t* __restrict__ offs,
+                                                     const uint32_t* __restrict__ counts, int raw,
                                                      float* __restrict__ cpts,
                                                      int32_t* __restrict__ cidx,
+                                                     int32_t* __restrict__ label,
                                                      UvMeta* __restrict__ m) {
-    const int64_t i = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (i >= n) return;
-    const bool in = mask[i] != 0;
-    const uint32_t o = offs[i];
-    if (in) {
-        cpts[3 * (int64_t)o] = pts[3 * i];
-        cpts[3 * (int64_t)o + 1] = pts[3 * i + 1];
-        cpts[3 * (int64_t)o + 2] = pts[3 * i + 2];
-        cidx[o] = (int32_t)i;
+    constexpr int U = MASK_TILE / WT, NW = WT / WAVE;
+    __shared__ uint32_t s_c[U][NW], s_b[NW];
+    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+    const int64_t b = (int64_t)blockIdx.x * MASK_TILE;
+    uint32_t before = 0;
+    if (raw) {
+        for (int j = threadIdx.x; j < (int)blockIdx.x; j += WT) before += counts[j];
+        before = (uint32_t)readlane(wave_incl_scan((int)before), WAVE - 1);
     }
-    if (i == n - 1) m->kept = o + (in ? 1u : 0u);
+    if (l == 0) s_b[w] = before;
+    uint32_t in = 0;   // bit u: item u is kept
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t i = b + u * WT + threadIdx.x;
+        const bool k = i < n && mask[i] != 0;
+        in |= k ? 1u << u : 0u;
+        if (i < n && !k) label[i] = -1;
+        const uint32_t c = (uint32_t)__popcll(ballot(k));
+        if (l == 0) s_c[u][w] = c;
+    }
+    __syncthreads();
+    uint32_t o = raw ? s_b[0] + s_b[1] + s_b[2] + s_b[3] : counts[blockIdx.x];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool k = (in >> u) & 1u;
+        const unsigned long long bal = ballot(k);
+        uint32_t at = o + (uint32_t)__popcll(bal & ((1ull << l) - 1ull));
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            at += v < w ? s_c[u][v] : 0u;
+            o += s_c[u][v];
+        }
+        if (k) {
+            const int64_t i = b + u * WT + threadIdx.x;
+            cpts[3 * (int64_t)at] = pts[3 * i];
+            cpts[3 * (int64_t)at + 1] = pts[3 * i + 1];
+            cpts[3 * (int64_t)at + 2] = pts[3 * i + 2];
+            cidx[at] = (int32_t)i;
+        }
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) m->kept = o;
 }
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+// The status of a grid rebuilt on the device: the rebuild's own, then the
+// range of its cells.
+__device__ __forceinline__ int32_t cluster_grid_status(const TargetView* views,
+                                                       const int32_t* build_status) {
+    const int32_t st = build_status ? build_status[0] : (int32_t)LKC_OK;
+    if (st != (int32_t)LKC_OK || !views) return st;
+    return views->max_abs * views->inv_cell < (float)((1 << 20) - 4) ? (int32_t)LKC_OK
+                                                                     : (int32_t)LKC_ERR_INVALID_ARG;
 }
 
 // labels: every point's root (full path compression), roots counted; with
 // a mask, compacted point c labels its original index cidx[c] with the
 // original index of its root (compaction keeps the order, so that is the
-// smallest original index of the component)
+// smallest original index of the component).  With build_status, the grid's
+// status goes into m->bad.
 __global__ void __launch_bounds__(WT) k_cluster_labels(int32_t* __restrict__ par, int64_t n,
                                                        const int32_t* __restrict__ cidx,
                                                        int32_t* __restrict__ label,
                                                        UvMeta* __restrict__ m,
-                                                       const uint8_t* __restrict__ mask) {
+                                                       const uint8_t* __restrict__ mask,
+                                                       const TargetView* __restrict__ views,
+                                                       const int32_t* __restrict__ build_status) {
     const int64_t i = (int64_t)blockIdx.x * WT + threadIdx.x;
+    if (build_status) {
+        const int32_t bad = cluster_grid_status(views, build_status);
+        if (i == 0) m->bad = (uint32_t)bad;
+        if (bad != (int32_t)LKC_OK) return;   // (the call does it over or fails)
+    }
     bool root = false;
     if (i < n && mask && !mask[i]) {
         label[i] = -1;   // (uncompacted masked call: a point left out)
@@ -263,11 +408,7 @@ __global__ void k_cluster_status(const TargetView* __restrict__ Tp,
                                  const UvMeta* __restrict__ m, int64_t* __restrict__ n_clusters,
                                  int32_t* __restrict__ status) {
     if (threadIdx.x != 0) return;
-    int32_t st = build_status ? build_status[0] : (int32_t)LKC_OK;
-    if (st == (int32_t)LKC_OK && Tp) {
-        const TargetView T = *Tp;
-        if (!(T.max_abs * T.inv_cell < (float)((1 << 20) - 4))) st = (int32_t)LKC_ERR_INVALID_ARG;
-    }
+    int32_t st = cluster_grid_status(Tp, build_status);
     if (st == (int32_t)LKC_OK && m->spins) st = (int32_t)LKC_ERR_HIP;
     *status = st;
     *n_clusters = st == (int32_t)LKC_OK ? (int64_t)m->n_clusters : 0;
@@ -311,8 +452,9 @@ lkc_status euclid_cluster(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
         off += align256(b);
         return o;
     };
-    const size_t o_par = carve(4 * (size_t)n), o_fl = carve(mask ? 4 * (size_t)n : 0),
-                 o_tmp = carve(mask ? 4 * ((size_t)n / 4096 + 2) : 0),
+    const int64_t tiles = (n + MASK_TILE - 1) / MASK_TILE;
+    const size_t o_par = carve(4 * (size_t)n), o_fl = carve(mask ? 4 * (size_t)tiles : 0),
+                 o_tmp = carve(mask ? 4 * ((size_t)tiles / 4096 + 2) : 0),
                  o_cp = carve(mask ? 12 * (size_t)n : 0), o_ci = carve(mask ? 4 * (size_t)n : 0);
     lkc_status s;
     char* sb = (char*)aux_scratch(ctx, off, &s);
@@ -320,20 +462,19 @@ lkc_status euclid_cluster(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
     auto* par = (int32_t*)(sb + o_par);
     UvMeta* md = uv_meta_dev(ctx);
     UvMeta* mh = uv_meta_host(ctx);
-    hipLaunchKernelGGL(k_uv_init, dim3(1), dim3(64), 0, st, md);
     const float* cp = pts;
     const int32_t* cidx = nullptr;
     int64_t m = n;
     if (mask) {
         // the kept points, compacted in ascending order
-        auto* flags = (uint32_t*)(sb + o_fl);
+        auto* counts = (uint32_t*)(sb + o_fl);
         auto* cpts = (float*)(sb + o_cp);
         auto* ci = (int32_t*)(sb + o_ci);
-        hipLaunchKernelGGL(k_mask_flags, dim3(grid_of(n, WT)), dim3(WT), 0, st, mask, n, flags);
-        scan_words(st, flags, n, (uint32_t*)(sb + o_tmp));
-        hipLaunchKernelGGL(k_mask_compact, dim3(grid_of(n, WT)), dim3(WT), 0, st, pts, mask, n,
-                           (const uint32_t*)flags, cpts, ci, md);
-        hipLaunchKernelGGL(k_fill_i32, dim3(grid_of(n, WT)), dim3(WT), 0, st, labels, n, -1);
+        const int raw = tiles <= RAW_MASK_TILES ? 1 : 0;
+        hipLaunchKernelGGL(k_mask_count, dim3((unsigned)tiles), dim3(WT), 0, st, mask, n, counts);
+        if (!raw) scan_words(st, counts, tiles, (uint32_t*)(sb + o_tmp));
+        hipLaunchKernelGGL(k_mask_compact, dim3((unsigned)tiles), dim3(WT), 0, st, pts, mask, n,
+                           (const uint32_t*)counts, raw, cpts, ci, labels, md);
         LKC_HIP_TRY(ctx, hipGetLastError());
         LKC_HIP_TRY(ctx, hipMemcpyAsync(mh, md, sizeof(UvMeta), hipMemcpyDeviceToHost, st));
         LKC_HIP_TRY(ctx, hipStreamSynchronize(st));
@@ -344,34 +485,37 @@ lkc_status euclid_cluster(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
     }
     lkc_target& grid = *ctx->cluster_grid;
     grid.cell_size = 1.25f * eps;
-    s = build_into(ctx, &grid, cp, m);
-    if (s == LKC_OK) {
+    // The grid is rebuilt without a wait where its memory and sort passes
+    // allow it; what such a rebuild finds wrong (a cell key that needs more
+    // passes, a coordinate or a range to refuse) is built once more with one,
+    // which sorts in full or gives the error.
+    for (int attempt = 0;; ++attempt) {
+        s = build_into(ctx, &grid, cp, m, attempt == 0);
+        if (s != LKC_OK) return s;
+        const bool on_device = grid.host_stale;
         const float reach = grid.view.max_abs * grid.view.inv_cell;
-        if (!(reach < (float)((1 << 20) - 4)))
-            s = set_error(ctx, LKC_ERR_INVALID_ARG,
-                          "eps %g is too small for the cloud's extent (|p| up to %g)",
-                          (double)eps, (double)grid.view.max_abs);
-    }
-    if (s == LKC_OK) {
-        hipLaunchKernelGGL(k_parent_init, dim3(grid_of(m, WT)), dim3(WT), 0, st, par, m);
-        hipLaunchKernelGGL(k_cluster_union, dim3(grid_of(m, WT)), dim3(WT), 0, st,
-                           (const TargetView*)grid.view_dev, eps * eps, (const uint8_t*)nullptr,
-                           par, md);
+        if (!on_device && !(reach < (float)((1 << 20) - 4)))
+            return set_error(ctx, LKC_ERR_INVALID_ARG,
+                             "eps %g is too small for the cloud's extent (|p| up to %g)",
+                             (double)eps, (double)grid.view.max_abs);
+        hipLaunchKernelGGL(k_uv_init, dim3(1), dim3(64), 0, st, md);
+        launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, nullptr, par, md, m});
         hipLaunchKernelGGL(k_cluster_labels, dim3(grid_of(m, WT)), dim3(WT), 0, st, par, m,
-                           cidx, labels, md, (const uint8_t*)nullptr);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = hipMemcpyAsync(mh, md, sizeof(UvMeta), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) {
-            s = hip_error(ctx, e, "clustering");
-        } else if (mh->spins) {
-            s = set_error(ctx, LKC_ERR_HIP, "%u union-find joins exceeded the retry limit",
-                          mh->spins);
-        } else {
-            *n_clusters = mh->n_clusters;
-        }
+                           cidx, labels, md, (const uint8_t*)nullptr,
+                           (const TargetView*)grid.view_dev,
+                           on_device ? (const int32_t*)((const char*)grid.view_dev +
+                                                        view_status_offset())
+                                     : nullptr);
+        LKC_HIP_TRY(ctx, hipGetLastError());
+        LKC_HIP_TRY(ctx, hipMemcpyAsync(mh, md, sizeof(UvMeta), hipMemcpyDeviceToHost, st));
+        LKC_HIP_TRY(ctx, hipStreamSynchronize(st));
+        if (on_device && mh->bad && attempt == 0) continue;
+        if (mh->spins)
+            return set_error(ctx, LKC_ERR_HIP, "%u union-find joins exceeded the retry limit",
+                             mh->spins);
+        *n_clusters = mh->n_clusters;
+        return LKC_OK;
     }
-    return s;
 }
 
 lkc_status euclid_cluster_async(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
@@ -408,11 +552,10 @@ lkc_status euclid_cluster_async(lkc_ctx* ctx, const float* pts, int64_t n, float
     const int32_t* bst =
         grid.host_stale ? (const int32_t*)((const char*)grid.view_dev + view_status_offset())
                         : nullptr;
-    hipLaunchKernelGGL(k_parent_init, dim3(grid_of(n, WT)), dim3(WT), 0, st, par, n);
-    hipLaunchKernelGGL(k_cluster_union, dim3(grid_of(n, WT)), dim3(WT), 0, st,
-                       (const TargetView*)grid.view_dev, eps * eps, mask, par, md);
+    launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, mask, par, md, n});
     hipLaunchKernelGGL(k_cluster_labels, dim3(grid_of(n, WT)), dim3(WT), 0, st, par, n,
-                       (const int32_t*)nullptr, labels, md, mask);
+                       (const int32_t*)nullptr, labels, md, mask,
+                       (const TargetView*)nullptr, (const int32_t*)nullptr);
     hipLaunchKernelGGL(k_cluster_status, dim3(1), dim3(64), 0, st,
                        (const TargetView*)grid.view_dev, bst, (const UvMeta*)md, n_clusters,
                        status);
