@@ -26,6 +26,7 @@
 // order (the sort is stable), so the layout is deterministic.
 #include <climits>
 #include <cstring>
+#include <type_traits>
 
 #include "lkc_internal.h"
 
@@ -34,7 +35,9 @@ namespace lkc {
 namespace {
 
 constexpr int BT = 256;          // threads per block for the build kernels
-constexpr int RS_ITEMS = 8;      // radix items per thread per tile
+// Radix items per thread (16 halve the counts to scan, but hold so many
+// registers that the scatter of 1 M 8-byte keys takes 14.7 us against 12.2).
+constexpr int RS_ITEMS = 8;
 constexpr int RS_TILE = BT * RS_ITEMS;
 constexpr int RADIX = 256;
 constexpr int SCAN_TILE = 4096;  // entries per workgroup of the multi-block scan
@@ -255,9 +258,10 @@ __global__ void __launch_bounds__(1024) k_meta_reduce(const MetaPart* __restrict
 
 // Sort keys; the threads also clear the hash's slots (all `cap` of them,
 // ahead of the insert, which uses the first 2^hash_bits).
+template <typename Key>
 __global__ void __launch_bounds__(BT) k_make_keys(const float4* __restrict__ orig, int64_t n,
                                                   float inv_cell, const BuildMeta* __restrict__ meta,
-                                                  unsigned long long* __restrict__ keys,
+                                                  Key* __restrict__ keys,
                                                   uint32_t* __restrict__ vals,
                                                   HashSlot* __restrict__ hash, int64_t cap) {
     const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
@@ -271,29 +275,80 @@ __global__ void __launch_bounds__(BT) k_make_keys(const float4* __restrict__ ori
     const unsigned long long sub =
         morton3(sub_cell(p.x, inv_cell, sb), sub_cell(p.y, inv_cell, sb),
                 sub_cell(p.z, inv_cell, sb));
-    keys[i] = (morton3(cx, cy, cz) << (3 * sb)) | sub;
+    keys[i] = (Key)((morton3(cx, cy, cz) << (3 * sb)) | sub);
     vals[i] = (uint32_t)i;
 }
 
 // Per-tile digit histogram, stored digit-major: counts[d * nblocks + b].
-__global__ void __launch_bounds__(BT) k_radix_hist(const unsigned long long* __restrict__ keys,
-                                                   int64_t n, int shift,
-                                                   uint32_t* __restrict__ counts, int nblocks,
-                                                   int tile_major) {
+template <typename Key>
+__global__ void __launch_bounds__(BT) k_radix_hist(const Key* __restrict__ keys, int64_t n,
+                                                   int shift, uint32_t* __restrict__ counts,
+                                                   int nblocks, int tile_major) {
     __shared__ uint32_t hist[RADIX];
     hist[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
+    Key key[RS_ITEMS];
 #pragma unroll
     for (int it = 0; it < RS_ITEMS; ++it) {
         const int64_t i = base + it * BT + threadIdx.x;
-        if (i < n) atomicAdd(&hist[(uint32_t)(keys[i] >> shift) & (RADIX - 1)], 1u);
+        key[it] = i < n ? keys[i] : (Key)0;
+    }
+#pragma unroll
+    for (int it = 0; it < RS_ITEMS; ++it) {
+        // the lanes that share the first lane's digit add up first: adds to one
+        // word serialise, and neighbours often share the top digits
+        const bool valid = base + it * BT + threadIdx.x < n;
+        const uint32_t d = (uint32_t)(key[it] >> shift) & (RADIX - 1);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        const unsigned long long same = ballot(valid && d == d0);
+        if (threadIdx.x % WAVE == 0 && same) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
+        if (valid && d != d0) atomicAdd(&hist[d], 1u);
     }
     __syncthreads();
-    // digit-major for the global scan, tile-major for the scatter's own
-    // offset derivation (one coalesced row per tile)
+    // digit-major for the row scan, tile-major for the scatter's own offset
+    // derivation (one coalesced row per tile)
     counts[tile_major ? (int64_t)blockIdx.x * RADIX + threadIdx.x
                       : (int64_t)threadIdx.x * nblocks + blockIdx.x] = hist[threadIdx.x];
+}
+
+// Exclusive prefix sums of the rows of the digit-major histograms, one
+// workgroup per digit, and the rows' totals: the scatter adds the totals of
+// the smaller digits itself.  (A scan of all of them as one array was three
+// launches.)
+__global__ void __launch_bounds__(BT) k_radix_rows(uint32_t* __restrict__ counts, int nblocks,
+                                                   uint32_t* __restrict__ totals) {
+    constexpr int U = 4;
+    __shared__ uint32_t s_w[2][BT / WAVE];
+    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+    uint32_t* row = counts + (int64_t)blockIdx.x * nblocks;
+    uint32_t carry = 0;
+    int turn = 0;
+    for (int b = 0; b < nblocks; b += BT * U, turn ^= 1) {
+        const int i = b + (int)threadIdx.x * U;
+        uint32_t v[U], sum = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[u] = i + u < nblocks ? row[i + u] : 0u;
+            sum += v[u];
+        }
+        const uint32_t incl = (uint32_t)wave_incl_scan((int)sum);
+        if (l == WAVE - 1) s_w[turn][w] = incl;
+        __syncthreads();   // (the other buffer may still be read from the turn before)
+        uint32_t run = carry + incl - sum, all = 0;
+#pragma unroll
+        for (int j = 0; j < BT / WAVE; ++j) {
+            run += j < w ? s_w[turn][j] : 0u;
+            all += s_w[turn][j];
+        }
+        carry += all;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i + u < nblocks) row[i + u] = run;
+            run += v[u];
+        }
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
 // Exclusive prefix sum of m words in place, one workgroup of 1024 threads.
@@ -362,43 +417,54 @@ __global__ void __launch_bounds__(BT) k_scan_add(uint32_t* __restrict__ data, in
 }
 
 // Stable scatter of one 8-bit digit.  A tile is read whole up front (every
-// thread holds its RS_ITEMS items, so the loads overlap); items are ordered
-// by (step, wavefront, lane), i.e. by index.  Each wavefront ranks each of
-// its steps' items among equal digits by ballots and records the digit
-// counts per (step, wavefront) in LDS; one thread per digit then turns its
-// column into exclusive offsets in item order, starting at the digit's
-// global offset, and every item lands at (its column entry) + (its rank).
+// thread holds its ITEMS items, so the loads overlap); items are ordered by
+// (step, wavefront, lane), i.e. by index.  Each wavefront ranks each of its
+// steps' items among equal digits by ballots and records the digit counts per
+// (step, wavefront) in LDS; one thread per digit then turns its column into
+// exclusive offsets in item order, starting at the digit's first place in the
+// tile.  STAGED, where there are many tiles, it is put into that order in LDS, keys and values one after the
+// other in the memory of the counts, and leaves it in runs of equal digits:
+// whole lines, where a store of every item to its own place touched 64 lines
+// per instruction.
 //
-// With `raw` = 1, `offsets` holds the unscanned per-tile histograms, tile
-// by tile, and each workgroup derives its own offsets (digit totals scanned
-// across the workgroup, plus the counts of the earlier tiles); used when
-// there are few tiles, so the separate scan launch is saved.  With `raw` =
-// 2 (a single tile) the workgroup takes the digit totals from its own
-// ranking counts, so no histogram is launched either.
+// `raw` = 0: `offsets` holds the row-scanned histograms and `totals` the
+// digits' totals.  `raw` = 1: the unscanned histograms, tile by tile, and each
+// workgroup derives its own offsets (the counts of the earlier tiles); used
+// when there are few tiles, so the separate scan launch is saved.  `raw` = 2
+// (a single tile): no histogram is launched either.
+//
+// Bound by memory traffic with many tiles, by latency with few.  A pass over
+// 3.76 M items (8-byte keys, unstaged, three scan launches) took 54 us, with
+// 4-byte keys 36: 10 histogram, 5 rows, 21 scatter.
+template <typename Key, bool STAGED>
 __global__ void __launch_bounds__(BT) k_radix_scatter(
-    const unsigned long long* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-    unsigned long long* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t n,
-    int shift, const uint32_t* __restrict__ offsets, int nblocks, int raw) {
+    const Key* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
+    Key* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t n, int shift,
+    const uint32_t* __restrict__ offsets, const uint32_t* __restrict__ totals, int nblocks,
+    int raw) {
     constexpr int NW = BT / WAVE;
     constexpr int COLS = RS_ITEMS * NW;
-    __shared__ uint32_t s_tot[NW];
-    __shared__ uint32_t cnt[COLS][RADIX];
+    constexpr size_t CNT = sizeof(uint16_t) * COLS * RADIX, STAGE = STAGED ? sizeof(Key) * RS_TILE : 0;
+    __shared__ uint32_t s_tot[2][NW];
+    __shared__ uint32_t s_to[RADIX];   // first output position of a digit less its first in the tile
+    __shared__ __align__(16) unsigned char s_mem[CNT > STAGE ? CNT : STAGE];
+    uint16_t(*cnt)[RADIX] = (uint16_t(*)[RADIX])s_mem;
     const int tid = threadIdx.x, w = tid / WAVE, l = tid % WAVE;
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-    unsigned long long key[RS_ITEMS];
+    Key key[RS_ITEMS];
     uint32_t val[RS_ITEMS];
 #pragma unroll
     for (int it = 0; it < RS_ITEMS; ++it) {
         const int64_t i = base + it * BT + tid;
-        key[it] = i < n ? keys_in[i] : 0ull;
+        key[it] = i < n ? keys_in[i] : (Key)0;
         val[it] = i < n ? vals_in[i] : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < COLS; ++j) cnt[j][tid] = 0;
-    // thread tid owns digit tid: its first output position in this tile
-    uint32_t off;
+    for (int j = 0; j < COLS / 2; ++j) ((uint32_t*)s_mem)[j * BT + tid] = 0;
+    // thread tid owns digit tid: the items of the earlier tiles with it, and
+    // of all tiles
+    uint32_t pre = 0, tot = 0;
     if (raw == 1) {
-        uint32_t tot = 0, pre = 0;
         constexpr int U = 16;   // rows in flight
         for (int b0 = 0; b0 < nblocks; b0 += U) {
             uint32_t c[U];
@@ -411,20 +477,11 @@ __global__ void __launch_bounds__(BT) k_radix_scatter(
                 tot += c[u];
             }
         }
-        // exclusive scan of the digit totals across the workgroup
-        const int incl = wave_incl_scan((int)tot);
-        if (l == WAVE - 1) s_tot[w] = (uint32_t)incl;
-        __syncthreads();
-        uint32_t wo = 0;
-        for (int j = 0; j < w; ++j) wo += s_tot[j];
-        off = wo + (uint32_t)incl - tot + pre;
-    } else if (raw == 2) {
-        off = 0;           // one tile: its own counts, after the ranking
-        __syncthreads();   // the count table is cleared
-    } else {
-        off = offsets[(int64_t)tid * nblocks + blockIdx.x];
-        __syncthreads();   // the count table is cleared
+    } else if (raw == 0) {
+        pre = offsets[(int64_t)tid * nblocks + blockIdx.x];
+        tot = totals[tid];
     }
+    __syncthreads();   // the count table is cleared
     const unsigned long long lt_mask = (1ull << l) - 1ull;
     uint32_t rank[RS_ITEMS];
 #pragma unroll
@@ -439,40 +496,78 @@ __global__ void __launch_bounds__(BT) k_radix_scatter(
             peers &= b ? bal : ~bal;
         }
         rank[it] = (uint32_t)__popcll(peers & lt_mask);
-        if (valid && rank[it] == 0) cnt[it * NW + w][d] = (uint32_t)__popcll(peers);
+        if (valid && rank[it] == 0) cnt[it * NW + w][d] = (uint16_t)__popcll(peers);
     }
     __syncthreads();
-    if (raw == 2) {
-        // a single tile: digit tid starts after the smaller digits' counts
-        uint32_t tot = 0;
+    // where the digits start in the output, and STAGED in the tile (from the
+    // tile's own counts, which are also the totals of a single tile)
+    uint32_t mine = 0;
+    if (STAGED || raw == 2) {
 #pragma unroll
-        for (int j = 0; j < COLS; ++j) tot += cnt[j][tid];
-        const int incl = wave_incl_scan((int)tot);
-        if (l == WAVE - 1) s_tot[w] = (uint32_t)incl;
-        __syncthreads();
-        uint32_t wo = 0;
-        for (int j = 0; j < w; ++j) wo += s_tot[j];
-        off = wo + (uint32_t)incl - tot;
+        for (int j = 0; j < COLS; ++j) mine += cnt[j][tid];
+        if (raw == 2) tot = mine;
     }
-    {
-        uint32_t r = off;
+    const uint32_t i_mine = STAGED ? (uint32_t)wave_incl_scan((int)mine) : 0u;
+    const uint32_t i_tot = (uint32_t)wave_incl_scan((int)tot);
+    if (l == WAVE - 1) {
+        s_tot[0][w] = i_mine;
+        s_tot[1][w] = i_tot;
+    }
+    __syncthreads();
+    uint32_t at = STAGED ? i_mine - mine : 0u, to = i_tot - tot + pre;
+    for (int j = 0; j < w; ++j) {
+        if (STAGED) at += s_tot[0][j];
+        to += s_tot[1][j];
+    }
+    s_to[tid] = to - at;
 #pragma unroll
-        for (int j = 0; j < COLS; ++j) {
-            const uint32_t c = cnt[j][tid];
-            cnt[j][tid] = r;
-            r += c;
+    for (int j = 0; j < COLS; ++j) {
+        const uint32_t c = cnt[j][tid];
+        cnt[j][tid] = (uint16_t)at;
+        at += c;
+    }
+    __syncthreads();
+    // every item's place in the tile (not STAGED: among the tile's items with its digit)
+#pragma unroll
+    for (int it = 0; it < RS_ITEMS; ++it) {
+        const uint32_t d = (uint32_t)(key[it] >> shift) & (RADIX - 1);
+        rank[it] += cnt[it * NW + w][d];
+    }
+    if (!STAGED) {
+#pragma unroll
+        for (int it = 0; it < RS_ITEMS; ++it) {
+            if (base + it * BT + tid >= n) continue;
+            const uint32_t to = s_to[(uint32_t)(key[it] >> shift) & (RADIX - 1)] + rank[it];
+            keys_out[to] = key[it];
+            vals_out[to] = val[it];
         }
+        return;
     }
+    __syncthreads();   // the counts are read: their memory takes the keys
+    Key* sk = (Key*)s_mem;
+    uint32_t* sv = (uint32_t*)s_mem;
+    const int here = (int)min((int64_t)RS_TILE, n - base);
+#pragma unroll
+    for (int it = 0; it < RS_ITEMS; ++it)
+        if (base + it * BT + tid < n) sk[rank[it]] = key[it];
+    __syncthreads();
+    uint32_t pos[RS_ITEMS];
+#pragma unroll
+    for (int it = 0; it < RS_ITEMS; ++it) {
+        const int j = it * BT + tid;
+        const Key k = sk[j < here ? j : 0];
+        pos[it] = s_to[(uint32_t)(k >> shift) & (RADIX - 1)] + (uint32_t)j;
+        if (j < here) keys_out[pos[it]] = k;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < RS_ITEMS; ++it)
+        if (base + it * BT + tid < n) sv[rank[it]] = val[it];
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < RS_ITEMS; ++it) {
-        const int64_t i = base + it * BT + tid;
-        if (i < n) {
-            const uint32_t d = (uint32_t)(key[it] >> shift) & (RADIX - 1);
-            const uint32_t pos = cnt[it * NW + w][d] + rank[it];
-            keys_out[pos] = key[it];
-            vals_out[pos] = val[it];
-        }
+        const int j = it * BT + tid;
+        if (j < here) vals_out[pos[it]] = sv[j];
     }
 }
 
@@ -482,7 +577,8 @@ __global__ void __launch_bounds__(BT) k_radix_scatter(
 // count and the hash size.  `boff` holds the blocks' first cell ids, or with
 // `raw` the blocks' run counts, which each block then sums itself (for up
 // to RAW_RUN_BLOCKS blocks, saving the scan launch).
-__global__ void __launch_bounds__(BT) k_cell_write(const unsigned long long* __restrict__ keys,
+template <typename Key>
+__global__ void __launch_bounds__(BT) k_cell_write(const Key* __restrict__ keys,
                                                    const float4* __restrict__ pts, int64_t n,
                                                    float inv_cell,
                                                    const uint32_t* __restrict__ boff,
@@ -598,11 +694,12 @@ __global__ void __launch_bounds__(BT) k_hash_insert(const unsigned long long* __
 // aligned 16-point run (one 16-lane quarter of a wavefront per box), and
 // count the cell runs starting in each block (flag(i): the cell part of
 // key[i] differs from key[i-1]'s).
+template <typename Key>
 __global__ void __launch_bounds__(BT) k_reorder(const float4* __restrict__ orig,
                                                 const uint32_t* __restrict__ vals, int64_t n,
                                                 float4* __restrict__ pts,
                                                 float4* __restrict__ boxes,
-                                                const unsigned long long* __restrict__ keys,
+                                                const Key* __restrict__ keys,
                                                 const BuildMeta* __restrict__ meta,
                                                 uint32_t* __restrict__ bcount) {
     const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
@@ -685,29 +782,35 @@ void scan_words(hipStream_t st, uint32_t* data, int64_t m, uint32_t* tmp) {
 }
 
 size_t sort_count_words(int64_t n) {
+    // (the tiles' histograms and the digits' totals)
     const int64_t nb = (n + RS_TILE - 1) / RS_TILE;
-    const size_t m = (size_t)RADIX * (size_t)(nb > 0 ? nb : 1);
-    return m + m / SCAN_TILE + 64;
+    return (size_t)RADIX * (size_t)(nb > 0 ? nb : 1) + RADIX + 64;
 }
 
-lkc_status sort_pairs(lkc_ctx* ctx, unsigned long long* ka, uint32_t* va, unsigned long long* kb,
-                      uint32_t* vb, int64_t n, int bits, uint32_t* counts, bool* in_b) {
+template <typename Key>
+lkc_status sort_pairs(lkc_ctx* ctx, Key* ka, uint32_t* va, Key* kb, uint32_t* vb, int64_t n,
+                      int bits, uint32_t* counts, bool* in_b) {
     hipStream_t st = ctx->stream;
     const int64_t nb = (n + RS_TILE - 1) / RS_TILE;
-    const int64_t m = (int64_t)RADIX * nb;
-    uint32_t* tmp = counts + m;
-    bool b = false;
     // raw 2: a single tile ranks and counts its own digits (no histogram
     // launch); raw 1: few tiles derive their offsets from the tile-major
     // histograms (no scan launch)
     const int raw = nb == 1 ? 2 : (nb <= RAW_OFFSET_TILES ? 1 : 0);
+    uint32_t* totals = counts + (int64_t)RADIX * nb;
+    const dim3 grid((unsigned)nb);
+    bool b = false;
     for (int shift = 0; shift < bits && n > 1; shift += 8) {
         if (raw != 2)
-            hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(BT), 0, st, ka, n, shift,
+            hipLaunchKernelGGL(k_radix_hist<Key>, grid, dim3(BT), 0, st, (const Key*)ka, n, shift,
                                counts, (int)nb, raw);
-        if (!raw) scan_exclusive(st, counts, m, tmp);
-        hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nb), dim3(BT), 0, st, ka, va, kb, vb,
-                           n, shift, counts, (int)nb, raw);
+        if (raw) {
+            hipLaunchKernelGGL((k_radix_scatter<Key, false>), grid, dim3(BT), 0, st,
+                               (const Key*)ka, va, kb, vb, n, shift, counts, totals, (int)nb, raw);
+        } else {
+            hipLaunchKernelGGL(k_radix_rows, dim3(RADIX), dim3(BT), 0, st, counts, (int)nb, totals);
+            hipLaunchKernelGGL((k_radix_scatter<Key, true>), grid, dim3(BT), 0, st,
+                               (const Key*)ka, va, kb, vb, n, shift, counts, totals, (int)nb, 0);
+        }
         std::swap(ka, kb);
         std::swap(va, vb);
         b = !b;
@@ -716,6 +819,12 @@ lkc_status sort_pairs(lkc_ctx* ctx, unsigned long long* ka, uint32_t* va, unsign
     *in_b = b;
     return LKC_OK;
 }
+
+template lkc_status sort_pairs<uint32_t>(lkc_ctx*, uint32_t*, uint32_t*, uint32_t*, uint32_t*,
+                                         int64_t, int, uint32_t*, bool*);
+template lkc_status sort_pairs<unsigned long long>(lkc_ctx*, unsigned long long*, uint32_t*,
+                                                   unsigned long long*, uint32_t*, int64_t, int,
+                                                   uint32_t*, bool*);
 
 void free_target_memory(lkc_target* t) {
     if (t->point_mem) (void)hipFree(t->point_mem);
@@ -884,11 +993,11 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
     // Steps 2-6 for a sort of `passes` 8-bit passes; every layout parameter
     // is read from the device meta.  With `vout` the hash kernel writes the
     // device view (from `base`) and nothing is read back.
-    auto enqueue = [&](int passes, const TargetView* base) -> lkc_status {
-        unsigned long long *ka = keys_a, *kb = keys_b;
+    auto sorted = [&](auto* ka, auto* kb, int passes) -> lkc_status {
+        using Key = std::remove_pointer_t<decltype(ka)>;
         uint32_t *va = vals_a, *vb = vals_b;
         // ---- 2. keys
-        hipLaunchKernelGGL(k_make_keys, dim3(grid_for(n, BT)), dim3(BT), 0, st, orig, n,
+        hipLaunchKernelGGL(k_make_keys<Key>, dim3(grid_for(n, BT)), dim3(BT), 0, st, orig, n,
                            inv_cell, (const BuildMeta*)meta, ka, va, hash, cap_max);
         // ---- 3. LSD radix sort
         bool in_b = false;
@@ -899,14 +1008,22 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
             std::swap(va, vb);
         }
         // ---- 4. reorder (+ run boxes, run counts per block)
-        hipLaunchKernelGGL(k_reorder, dim3((unsigned)nb_bt), dim3(BT), 0, st, orig, va, n, pts,
-                           boxes, (const unsigned long long*)ka, (const BuildMeta*)meta, bcounts);
+        hipLaunchKernelGGL(k_reorder<Key>, dim3((unsigned)nb_bt), dim3(BT), 0, st, orig, va, n, pts,
+                           boxes, (const Key*)ka, (const BuildMeta*)meta, bcounts);
         // ---- 5. cell runs
         const int raw_runs = nb_bt <= RAW_RUN_BLOCKS ? 1 : 0;
         if (!raw_runs) scan_exclusive(st, bcounts, nb_bt, btmp);
-        hipLaunchKernelGGL(k_cell_write, dim3((unsigned)nb_bt), dim3(BT), 0, st, ka,
-                           (const float4*)pts, n, inv_cell, bcounts, tkeys, tstart, meta,
-                           raw_runs);
+        hipLaunchKernelGGL(k_cell_write<Key>, dim3((unsigned)nb_bt), dim3(BT), 0, st,
+                           (const Key*)ka, (const float4*)pts, n, inv_cell, bcounts, tkeys, tstart,
+                           meta, raw_runs);
+        return LKC_OK;
+    };
+    auto enqueue = [&](int passes, const TargetView* base) -> lkc_status {
+        // (keys of four passes are sorted as 32-bit words: a third of the traffic less)
+        const lkc_status r = passes <= 4
+                                 ? sorted((uint32_t*)keys_a, (uint32_t*)keys_b, passes)
+                                 : sorted(keys_a, keys_b, passes);
+        if (r != LKC_OK) return r;
         // ---- 6. hash (cleared by k_make_keys)
         TargetView* vout = base ? t->view_dev : nullptr;
         int32_t* stw = base ? (int32_t*)((char*)t->view_dev + view_status_offset()) : nullptr;

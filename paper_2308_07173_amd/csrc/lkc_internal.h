@@ -157,8 +157,10 @@ void free_target_memory(lkc_target* t);
 size_t sort_count_words(int64_t n);
 // stable LSD radix sort of (key, val) pairs on the low `bits` key bits;
 // *in_b tells whether the result ended in the b buffers
-lkc_status sort_pairs(lkc_ctx* ctx, unsigned long long* ka, uint32_t* va, unsigned long long* kb,
-                      uint32_t* vb, int64_t n, int bits, uint32_t* counts, bool* in_b);
+// (Key: uint32_t or unsigned long long)
+template <typename Key>
+lkc_status sort_pairs(lkc_ctx* ctx, Key* ka, uint32_t* va, Key* kb, uint32_t* vb, int64_t n,
+                      int bits, uint32_t* counts, bool* in_b);
 
 // exclusive prefix sum of m words in place; tmp holds ceil(m / 4096) + 1 words
 void scan_words(hipStream_t st, uint32_t* data, int64_t m, uint32_t* tmp);

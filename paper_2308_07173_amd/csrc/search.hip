@@ -1980,8 +1980,9 @@ struct QueryKeyArgs {
     int tshift;
     int sub_bits;
     int w[3];   // bits of each axis's clamped cell coordinate
-    unsigned long long* keys;
+    void* keys;                 // Key[q]
     uint32_t* vals;
+    uint32_t* words;            // 16 work words to clear, or NULL
 };
 
 // The cell coordinates' bits interleaved from the lowest level up, x first,
@@ -2005,7 +2006,9 @@ __device__ __forceinline__ unsigned long long morton_compact(const uint32_t (&v)
     return key;
 }
 
+template <typename Key>
 __global__ void __launch_bounds__(256) k_query_keys(QueryKeyArgs a) {
+    if (a.words && blockIdx.x == 0 && threadIdx.x < 16) a.words[threadIdx.x] = 0u;
     __shared__ int s_lo;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x;
     const int64_t i = i0 + threadIdx.x;
@@ -2052,7 +2055,7 @@ __global__ void __launch_bounds__(256) k_query_keys(QueryKeyArgs a) {
     } else {
         key = (1ull << a.tshift) - 1ull;
     }
-    a.keys[i] = ((unsigned long long)tg << a.tshift) | key;
+    ((Key*)a.keys)[i] = (Key)(((unsigned long long)tg << a.tshift) | key);
     a.vals[i] = (uint32_t)i;
 }
 
@@ -2330,6 +2333,7 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     // batch over several targets carries each query's target in the key's
     // top bits (the wavefront-per-query search reads it unsorted).
     int tshift = 0, tbits = 0;
+    bool words32 = false;
     if (keyed) {
         int w[3] = {1, 1, 1};
         for (int t = 0; t < j.n_targets; ++t) {
@@ -2352,17 +2356,25 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
         // (one target: every scan's target is 0, no lookup)
         QueryKeyArgs qa{j.queries, j.n_slots, j.views_dev, j.n_targets > 1 ? j.scans_dev : nullptr,
                         j.hdr_dev, tshift,
-                        sub_bits, {w[0], w[1], w[2]}, sc.ka, sc.va};
-        hipLaunchKernelGGL(k_query_keys, dim3((unsigned)((j.n_slots + 255) / 256)), dim3(256), 0,
-                           st, qa);
+                        sub_bits, {w[0], w[1], w[2]}, sc.ka, sc.va, group ? sc.words : nullptr};
+        // (the sorted keys are read again only for the targets of several)
+        words32 = group && j.n_targets == 1 && tshift <= 32;
+        const dim3 kgrid((unsigned)((j.n_slots + 255) / 256));
+        if (words32)
+            hipLaunchKernelGGL(k_query_keys<uint32_t>, kgrid, dim3(256), 0, st, qa);
+        else
+            hipLaunchKernelGGL(k_query_keys<unsigned long long>, kgrid, dim3(256), 0, st, qa);
     }
     if (group) {
-        hipLaunchKernelGGL(k_set_words, dim3(1), dim3(64), 0, st, sc.words, 16, 0u);
+        if (!j.queries)
+            hipLaunchKernelGGL(k_set_words, dim3(1), dim3(64), 0, st, sc.words, 16, 0u);
         if (j.queries) {
             // sort the queries by their key
             bool in_b = false;
-            s = sort_pairs(ctx, sc.ka, sc.va, sc.kb, sc.vb, j.n_slots, tshift + tbits, sc.counts,
-                           &in_b);
+            s = words32 ? sort_pairs(ctx, (uint32_t*)sc.ka, sc.va, (uint32_t*)sc.kb, sc.vb,
+                                     j.n_slots, tshift, sc.counts, &in_b)
+                        : sort_pairs(ctx, sc.ka, sc.va, sc.kb, sc.vb, j.n_slots, tshift + tbits,
+                                     sc.counts, &in_b);
             if (s != LKC_OK) return s;
             a.order = in_b ? sc.vb : sc.va;
             a.skeys = j.n_targets > 1 ? (in_b ? sc.kb : sc.ka) : nullptr;
