@@ -652,28 +652,16 @@ __device__ __forceinline__ void covariance(float ox, float oy, float oz, int n, 
     cov_regularise(n, eps, out);
 }
 
-// The same arithmetic, in the same order, for at most NMAX neighbours: each
-// neighbour is loaded once, all loads in flight together, and its offset
-// from o kept in registers for the second pass.  Results equal
-// covariance()'s bit for bit.
-template <int NMAX, typename Fetch>
-__device__ __forceinline__ void covariance_n(float ox, float oy, float oz, int n, Fetch fetch,
-                                             float eps, CovOut& out) {
+// The same arithmetic, in the same order, for at most NMAX neighbours whose
+// offsets from o are in registers (all loads were in flight together).
+// Results equal covariance()'s bit for bit.
+template <int NMAX>
+__device__ __forceinline__ void covariance_n(float ox, float oy, float oz, int n,
+                                             const float (&ux)[NMAX], const float (&uy)[NMAX],
+                                             const float (&uz)[NMAX], float eps, CovOut& out) {
     if (n <= 0) {
         cov_empty(out);
         return;
-    }
-    float ux[NMAX], uy[NMAX], uz[NMAX];
-#pragma unroll
-    for (int j = 0; j < NMAX; ++j) {
-        if (j < n) {
-            const float4 t = fetch(j);
-            ux[j] = t.x - ox;
-            uy[j] = t.y - oy;
-            uz[j] = t.z - oz;
-        } else {
-            ux[j] = uy[j] = uz[j] = 0.0f;
-        }
     }
     float sx = 0.f, sy = 0.f, sz = 0.f;
 #pragma unroll
@@ -1267,6 +1255,21 @@ __device__ __forceinline__ void scan_run(const TargetView& T, int s0, int e0, bo
     }
 }
 
+// A lane's row of K words, four to a store (rows are only known to be aligned
+// to a word).  Every lane's row lies in lines of its own, and a store takes a
+// cycle of the address unit for each line: word by word, the two rows of a
+// k = 20 query were 40 of the group search's 49 stores, and the address units
+// busy 66 % of the batched launch (3.76 M queries, 1.17 ms); in quads 41 %
+// (1.07 ms), and the instructions issued bound it again.
+typedef uint32_t row4 __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int K>
+__device__ __forceinline__ void store_row(uint32_t* dst, const uint32_t (&v)[K]) {
+    static_assert(K % 4 == 0, "rows of whole quads");
+#pragma unroll
+    for (int j = 0; j < K; j += 4) *(row4*)(dst + j) = row4{v[j], v[j + 1], v[j + 2], v[j + 3]};
+}
+
 // Write one query's neighbour row from the ascending exact d2 bits D and
 // the points' positions P in the reordered array (K - k pads first, ~0u
 // empty): d2 and the count; the indices too unless the fused covariance
@@ -1280,6 +1283,26 @@ __device__ __forceinline__ int emit_row(const GroupArgs& a, const TargetView& T,
     int32_t* ip = a.ko.idx + qi * k - (K - k);   // entry j is column j - (K - k)
     float* dp = a.ko.d2 + qi * k - (K - k);
     const int lane = lane_id();
+    if (k == K) {
+        // no pads: whole rows
+        uint32_t d[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const bool have = D[j] != ~0u;
+            d[j] = have ? D[j] : __float_as_uint(INF);
+            cnt += have ? 1 : 0;
+            if (FUSED) s_pos[j * WAVE + lane] = P[j];
+        }
+        store_row((uint32_t*)dp, d);
+        if (!FUSED) {
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                d[j] = D[j] != ~0u ? __float_as_uint(gload(T.pts + P[j]).w) : ~0u;
+            store_row((uint32_t*)ip, d);
+        }
+        a.ko.count[qi] = cnt;
+        return cnt;
+    }
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         if (P[j] != ~0u) {   // not a pad
@@ -1300,25 +1323,53 @@ __device__ __forceinline__ int emit_row(const GroupArgs& a, const TargetView& T,
 // caches; the same values as the caller-order copy) by the positions in sp
 // (column c at sp[c * 64], LDS), then the row's indices.  Restrict-qualified
 // so that the gathers of a pass can all be in flight together.
+// (k == K: the row is written whole, -1 past cnt, here; else only its first cnt
+// entries, the rest by emit_row.)
 template <int K, int FUSED>
 __device__ __forceinline__ void cov_gather(const float4* __restrict__ pts,
                                            const uint32_t* __restrict__ sp,
-                                           int32_t* __restrict__ irow, const GroupArgs& a,
-                                           int64_t qi, float qx, float qy, float qz, int cnt) {
+                                           uint32_t* __restrict__ irow, const GroupArgs& a,
+                                           int64_t qi, float qx, float qy, float qz, int k,
+                                           int cnt) {
     CovOut c;
     if (FUSED == 1) {
-        // each neighbour gathered once; its index written on the way
-        const auto fetch = [&](int j) {
-            const float4 t = gload(pts + sp[j * WAVE]);
-            irow[j] = __float_as_int(t.w);
-            return t;
-        };
-        covariance_n<K>(qx, qy, qz, cnt, fetch, a.eps, c);
+        // each neighbour gathered once, its index written on the way (eight
+        // gathers in flight: with all of them the offsets and the indices do
+        // not fit the registers)
+        float ux[K], uy[K], uz[K];
+#pragma unroll
+        for (int j0 = 0; j0 < K; j0 += 4) {
+            uint32_t w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = j0 + u;
+                w[u] = ~0u;
+                ux[j] = uy[j] = uz[j] = 0.0f;
+                if (j < cnt) {
+                    const float4 t = gload(pts + sp[j * WAVE]);
+                    ux[j] = t.x - qx;
+                    uy[j] = t.y - qy;
+                    uz[j] = t.z - qz;
+                    w[u] = __float_as_uint(t.w);
+                }
+            }
+            if (k == K) {
+                store_row(irow + j0, w);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j0 + u < cnt) irow[j0 + u] = w[u];
+            }
+            if (j0 % 8 == 4) __builtin_amdgcn_sched_barrier(0);
+        }
+        covariance_n<K>(qx, qy, qz, cnt, ux, uy, uz, a.eps, c);
     } else {
         const auto fetch = [&](int j) { return gload(pts + sp[j * WAVE]); };
         covariance_weighted(qx, qy, qz, cnt, fetch, a.wt, a.eps, c);
 #pragma unroll 4
-        for (int j = 0; j < cnt; ++j) irow[j] = __float_as_int(gload(pts + sp[j * WAVE]).w);
+        for (int j = 0; j < cnt; ++j) irow[j] = __float_as_uint(gload(pts + sp[j * WAVE]).w);
+        if (k == K)
+            for (int j = cnt; j < k; ++j) irow[j] = ~0u;
     }
     store_cov(a.co, qi, c);
 }
@@ -1327,8 +1378,8 @@ template <int K, int FUSED>
 __device__ __forceinline__ void emit_cov(const GroupArgs& a, const TargetView& T, int64_t qi,
                                          float qx, float qy, float qz, int k, int cnt,
                                          const uint32_t* s_pos) {
-    cov_gather<K, FUSED>(T.pts, s_pos + (K - k) * WAVE + lane_id(), a.ko.idx + qi * k, a, qi, qx,
-                      qy, qz, cnt);
+    cov_gather<K, FUSED>(T.pts, s_pos + (K - k) * WAVE + lane_id(), (uint32_t*)a.ko.idx + qi * k, a, qi, qx,
+                         qy, qz, k, cnt);
 }
 
 // An empty result row (non-finite query, empty target).
