@@ -654,7 +654,11 @@ lkc_status lkc_ctx_set_profile(lkc_ctx *ctx, void *buffer, int64_t n_groups);
  * scans.  Time = median of `reps` (1..100) runs after one warm-up, from HIP
  * events on the context's stream.  Candidates are tried in order (cells
  * outer, shapes inner) and one replaces the best so far only when it is
- * more than 2 % faster, so that repeated tunings agree.
+ * more than 2 % faster, so that repeated tunings agree.  Each is timed in
+ * the search (group or wavefront-per-query) that all q queries would take;
+ * candidates that come to the wavefront-per-query search are one launch,
+ * timed once.  On a part of a set that the group search's rule takes, the
+ * wavefront-per-query search is timed, but chosen only if no other is listed.
  *   cells    host [n_cells] candidate cell sizes (> 0); n_cells = 0 takes
  *            0.5, 0.75, 1, 1.5, 2 m
  *   cfgs     host [n_cfgs] candidate launch shapes; n_cfgs = 0 takes a

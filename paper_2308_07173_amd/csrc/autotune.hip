@@ -10,6 +10,15 @@
 // so that it keeps the local density of whole scans: the group search's
 // cost per query depends on how many queries share a group's neighbourhood,
 // which a thinned random subset would understate.  Host code only.
+//
+// Each candidate is timed in the search that all q queries would take, also
+// where the sample by itself would be given to the other.  Candidates that
+// come to the wavefront-per-query search are the same launch (no option
+// applies to it): it is timed once per cell.  Where the sample is a part of a
+// query set that is large enough for the group search, that search's gain
+// over the wavefront search shows on the whole set only (3.76 M queries: 1.31
+// against 7.74 ms; 118,000 of one scan: 0.38 against 0.31), so there
+// the wavefront search is timed but not chosen.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -163,25 +172,38 @@ lkc_status lkc_autotune(lkc_ctx* ctx, const float* target_points, int64_t n,
 
     float best = INFINITY;
     std::vector<float> t(reps);
+    const lkc_launch_cfg by_rule{0, 0, 0, 0, 0, 0};
+    // (unless it is all there is to choose from)
+    bool skip_wave = ms_q < q && lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&by_rule));
+    bool any_group = false;
+    for (int32_t f = 0; f < n_cfgs; ++f)
+        any_group |= lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&cfgs[f]));
+    skip_wave = skip_wave && any_group;
     for (int32_t c = 0; c < n_cells; ++c) {
         s = lkc_build_target(ctx, target_points, n, cells[c], &buf.target);
         if (s != LKC_OK) return s;
+        float wave_ms = -1.0f;
         for (int32_t f = 0; f < n_cfgs; ++f) {
-            for (int32_t r = -1; r < reps; ++r) {  // r = -1: warm-up
+            const bool wave = !lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&cfgs[f]));
+            lkc_launch_cfg run = cfgs[f];
+            run.algorithm = wave ? 2 : 1;
+            const int32_t runs = wave && wave_ms >= 0.0f ? -1 : reps;
+            for (int32_t r = -1; r < runs; ++r) {  // r = -1: warm-up
                 LKC_HIP_TRY(ctx, hipEventRecord(ev[0], ctx->stream));
                 s = lkc_knn_cov(ctx, buf.target, qs, ms_q, k, radius, plane_eps, idx, d2, cnt,
-                                mean, cov, reg, valid, &cfgs[f]);
+                                mean, cov, reg, valid, &run);
                 if (s != LKC_OK) return s;
                 LKC_HIP_TRY(ctx, hipEventRecord(ev[1], ctx->stream));
                 LKC_HIP_TRY(ctx, hipEventSynchronize(ev[1]));
                 if (r >= 0) LKC_HIP_TRY(ctx, hipEventElapsedTime(&t[r], ev[0], ev[1]));
             }
-            std::sort(t.begin(), t.end());
-            const float med = t[reps / 2];
+            if (runs > 0) std::sort(t.begin(), t.end());
+            const float med = runs > 0 ? t[reps / 2] : wave_ms;
+            if (wave) wave_ms = med;
             if (times_ms) times_ms[(int64_t)c * n_cfgs + f] = med;
             // a later candidate must win by more than the run-to-run noise
             // (2 %), so that repeated tunings pick the same entry
-            if (med < best * 0.98f) {
+            if (!(wave && skip_wave) && med < best * 0.98f) {
                 best = med;
                 result->cell_size = cells[c];
                 result->cfg_index = f;
