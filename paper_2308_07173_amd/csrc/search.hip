@@ -761,6 +761,56 @@ __device__ __forceinline__ void covariance_weighted(float ox, float oy, float oz
     cov_regularise(n, eps, out);
 }
 
+// The same estimates, in the same operations and order, from neighbours whose
+// offsets from o (and weights) have been taken before: fetch(j) returns
+// (t_j - o, w_j).
+template <bool WEIGHTED, typename Fetch>
+__device__ __forceinline__ void covariance_offsets(float ox, float oy, float oz, int n, Fetch fetch,
+                                                   float eps, CovOut& out) {
+    if (n <= 0) {
+        cov_empty(out);
+        return;
+    }
+    float sw = 0.f, sx = 0.f, sy = 0.f, sz = 0.f;
+#pragma unroll 4
+    for (int j = 0; j < n; ++j) {
+        const float4 u = fetch(j);
+        if (WEIGHTED) {
+            sw += u.w;
+            sx = fmaf(u.w, u.x, sx);
+            sy = fmaf(u.w, u.y, sy);
+            sz = fmaf(u.w, u.z, sz);
+        } else {
+            sx += u.x;
+            sy += u.y;
+            sz += u.z;
+        }
+    }
+    const float inv_n = 1.0f / (float)n;
+    const float mx = WEIGHTED ? sx / sw : sx * inv_n, my = WEIGHTED ? sy / sw : sy * inv_n,
+                mz = WEIGHTED ? sz / sw : sz * inv_n;
+    float c[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int j = 0; j < n; ++j) {
+        const float4 u = fetch(j);
+        const float dx = u.x - mx, dy = u.y - my, dz = u.z - mz;
+        const float wx = WEIGHTED ? u.w * dx : dx, wy = WEIGHTED ? u.w * dy : dy,
+                    wz = WEIGHTED ? u.w * dz : dz;
+        c[0] = fmaf(wx, dx, c[0]);
+        c[1] = fmaf(wx, dy, c[1]);
+        c[2] = fmaf(wx, dz, c[2]);
+        c[3] = fmaf(wy, dy, c[3]);
+        c[4] = fmaf(wy, dz, c[4]);
+        c[5] = fmaf(wz, dz, c[5]);
+    }
+#pragma unroll
+    for (int e = 0; e < 6; ++e) out.cov[e] = WEIGHTED ? c[e] / sw : c[e] * inv_n;
+    out.mean[0] = ox + mx;
+    out.mean[1] = oy + my;
+    out.mean[2] = oz + mz;
+    cov_regularise(n, eps, out);
+}
+
 // The plain or the weighted estimate, as W asks.
 template <typename Fetch>
 __device__ __forceinline__ void covariance_any(float ox, float oy, float oz, int n, Fetch fetch,
@@ -907,7 +957,7 @@ struct GroupArgs {
     uint32_t* prof;                   // optional per-group counters (PROF_WORDS each) or NULL
     int split;                        // waves per group (1, 2 or 4)
     int rounds;                       // anchor rounds per group (lanes left fall back)
-    int cov_slots;                    // covariances the wavefront search takes together
+    int cov_slots;                    // rows a wavefront of the wavefront search keeps for their covariances
     int moved;                        // the wavefront search moves its queries by `move`
     RigidF move;
 };
@@ -1883,28 +1933,110 @@ k_group(GroupArgs a) {
     }
 }
 
+// A kept row's query (LDS).
+struct WaveSlot {
+    float x, y, z;
+    int cnt;
+    int32_t qi;
+    union {
+        int tg;       // target; once its points are gathered:
+        float emin;   // smallest weight exponent
+    };
+};
+static_assert(sizeof(WaveSlot) == 24, "WaveSlot layout");
+
+// Words of a neighbour kept for its covariance: its index, then its offset
+// from the query (and its weight).
+__host__ __device__ constexpr int row_words(int fused) { return fused == 2 ? 4 : 3; }
+
+// LDS of one wavefront: the candidate list, the slots, their rows.  With 5,560
+// bytes of slots and rows six workgroups of four fit a CU's 160 KB, of which
+// they take multiples of 1,280 bytes (k = 20: 21 rows; at 5,760 bytes it is
+// five, and the 65k-point match takes 152 us instead of 125).
+constexpr int WAVE_SLOTS = 32, WAVE_ROW_BYTES = 5560;
+
+__host__ __device__ inline int wave_slots(int k, int fused) {
+    const int fit = WAVE_ROW_BYTES / (4 * k * row_words(fused) + (int)sizeof(WaveSlot));
+    return fit < WAVE_SLOTS ? fit : WAVE_SLOTS;
+}
+__host__ __device__ inline size_t wave_lds_bytes(int k, int slots, int fused) {
+    const size_t rows = fused ? (size_t)slots * (4 * k * row_words(fused) + sizeof(WaveSlot)) : 0;
+    return (size_t)WaveList::CAP * 8 + ((rows + 7) & ~(size_t)7);
+}
+
+// Gathers the points of a wavefront's kept rows; offsets and weights in place
+// of the indices.
+template <int FUSED>
+__device__ __forceinline__ void wave_rows(const GroupArgs& a, int k, int ns, WaveSlot* slots,
+                                          float* rows) {
+    constexpr int RW = row_words(FUSED);
+    const int lane = lane_id();
+    wave_lds_fence();
+    const float ik = 1.0f / (float)k;
+#pragma unroll 1
+    for (int t = lane; t < ns * k; t += WAVE) {
+        // (t + 0.5) / k lies at least 0.5 / k from an integer
+        const int sl = (int)(((float)t + 0.5f) * ik), j = t - sl * k;
+        const WaveSlot q = slots[sl];
+        if (j < q.cnt) {
+            float* r = rows + t * RW;
+            const float4 p = gload(a.views[q.tg].orig + __float_as_int(r[0]));
+            r[0] = p.x - q.x;
+            r[1] = p.y - q.y;
+            r[2] = p.z - q.z;
+            if (FUSED == 2) r[3] = weight_exponent(a.wt, dist2(q.x, q.y, q.z, p.x, p.y, p.z));
+        }
+    }
+    wave_lds_fence();
+    if (FUSED == 2) {
+        if (lane < ns) {
+            float emin = INF;
+            for (int j = 0; j < slots[lane].cnt; ++j)
+                emin = fminf(emin, rows[(lane * k + j) * RW + 3]);
+            slots[lane].emin = emin;
+        }
+        wave_lds_fence();
+#pragma unroll 1
+        for (int t = lane; t < ns * k; t += WAVE) {
+            const int sl = (int)(((float)t + 0.5f) * ik), j = t - sl * k;
+            if (j < slots[sl].cnt) rows[t * RW + 3] = expf(slots[sl].emin - rows[t * RW + 3]);
+        }
+        wave_lds_fence();
+    }
+}
+
+// The covariance of one kept row, by one lane.
+template <int FUSED>
+__device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, const float* r) {
+    constexpr int RW = row_words(FUSED);
+    CovOut c;
+    covariance_offsets<FUSED == 2>(
+        q.x, q.y, q.z, q.cnt,
+        [&](int j) {
+            return make_float4(r[j * RW], r[j * RW + 1], r[j * RW + 2],
+                               FUSED == 2 ? r[j * RW + RW - 1] : 0.0f);
+        },
+        a.eps, c);
+    store_cov(a.co, q.qi, c);
+}
+
 // Wavefront-per-query search of the slots in `a.fb_list` (those the group
 // search handed over; their number is only known on the device), or of every
 // slot when there is no list.  Persistent: each XCD takes one contiguous part
 // (its L2 then holds that part of the target) and its wavefronts stride over
-// it.  The rows of up to a.cov_slots queries are kept in LDS and their
-// covariances then taken together, one lane per query (taken by the whole
-// wavefront for each query, they were half the kernel: 40 dependent loads and
-// the eigenvector's instructions, the same in every lane).
+// it.  The rows of up to a.cov_slots queries of a wavefront are kept in LDS;
+// at the end (or when they are full) their points are gathered and their
+// offsets and weights taken with every lane, and the sums and eigenvectors
+// follow for all queries of the workgroup, one lane per query.  (When every
+// wavefront took the sums of its own rows, exponents and weights included,
+// 30,000 queries with Laplacian weights took 94 us; this takes 68.)
 //
 // Bound by the chain of dependent loads of each query (hash slots, points)
 // with few queries, by VALU issue with many (65,536 queries against a 2
 // M-point map: 800 VALU instructions each, 75 % of the issue slots, 0.12 ms).
-// Its predecessor's list (see above) and per-query covariances took 39 us for
-// the 10 k queries a batch of 65,536 or a scan of 118 k hands over; this takes
-// 20.
-constexpr int WAVE_SLOTS = 16;      // covariances taken together, at most
-constexpr int WAVE_ROWS = 320;      // neighbours kept for them, at most
-
-__host__ __device__ inline size_t wave_lds_bytes(int k, int slots, int fused) {
-    return (size_t)WaveList::CAP * 8 + (fused ? (size_t)slots * k * 16 : 0);
-}
-
+// The list of 99,000 queries that the group search hands over in a batch of
+// 3.76 M takes 63 us (the wavefront search before it: 154).
+//
 // ONE: k = 1 without covariances (no list, no LDS).
 template <int FUSED, bool ONE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
@@ -1912,9 +2044,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     const int lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int k = a.sp.k;
-    char* mine = (char*)s_wave + (size_t)wid * wave_lds_bytes(k, a.cov_slots, FUSED);
-    unsigned long long* buf = (unsigned long long*)mine;
-    float4* rows = (float4*)(mine + WaveList::CAP * 8);   // [slot][k]: the index in .x, then the point
+    constexpr int RW = row_words(FUSED);
+    const size_t per_wave = wave_lds_bytes(k, a.cov_slots, FUSED);
+    const auto list_of = [&](int w) { return (unsigned long long*)((char*)s_wave + w * per_wave); };
+    const auto slots_of = [&](int w) { return (WaveSlot*)(list_of(w) + WaveList::CAP); };
+    const auto rows_of = [&](int w) { return (float*)(slots_of(w) + a.cov_slots); };   // [slot][k][RW]
+    unsigned long long* buf = list_of(wid);
+    WaveSlot* slots = slots_of(wid);
+    float* rows = rows_of(wid);
     // (wavefront-uniform, as the compiler has to know: scalar registers and
     // branches for all that follows)
     const int64_t n = a.fb_list ? (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(
@@ -1923,10 +2060,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     const int x = blockIdx.x % 8, nx = gridDim.x / 8;   // (the grid is a multiple of 8)
     const int64_t hi = n * (x + 1) / 8, step = (int64_t)nx * (blockDim.x / WAVE);
     int64_t i = n * x / 8 + (int64_t)(blockIdx.x / 8) * (blockDim.x / WAVE) + wid;
-    // lane s: the query of slot s
-    SlotQuery mq{0, 0.f, 0.f, 0.f, 0};
-    int m_cnt = 0, ns = 0;
-    const float4* m_orig = nullptr;
+    int ns = 0;   // kept rows
 #pragma unroll 1
     for (; i < hi; i += step) {
         const int64_t slot = a.fb_list ? (int64_t)load_uniform(a.fb_list + i) : i;
@@ -1984,38 +2118,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         }
         if (lane == 0) a.ko.count[s.qi] = cnt;
         if (FUSED) {
-            if (in) rows[ns * k + rank].x = __uint_as_float((uint32_t)my);
-            if (lane == ns) {
-                mq = s;
-                m_cnt = cnt;
-                m_orig = a.views[tg].orig;
+            if (in) rows[(ns * k + rank) * RW] = __uint_as_float((uint32_t)my);
+            if (lane == 0)
+                slots[ns] = WaveSlot{s.x, s.y, s.z, cnt, (int32_t)s.qi, {tg}};
+            if (++ns == a.cov_slots && i + step < hi) {
+                wave_rows<FUSED>(a, k, ns, slots, rows);
+                if (lane < ns) wave_cov<FUSED>(a, slots[lane], rows + lane * k * RW);
+                ns = 0;
+                wave_lds_fence();
             }
-            if (++ns < a.cov_slots && i + step < hi) continue;
-            // the points of every kept row, then one lane per query
-            wave_lds_fence();
-            const float ik = 1.0f / (float)k;
-#pragma unroll 1
-            for (int t0 = 0; t0 < ns * k; t0 += WAVE) {   // (every lane stays: shuffles)
-                // (t + 0.5) / k lies at least 0.5 / k from an integer
-                const int t = t0 + lane, sl = (int)(((float)t + 0.5f) * ik) & 63, j = t - sl * k;
-                const int c = __shfl(m_cnt, sl);
-                const float4* o = (const float4*)__shfl((unsigned long long)m_orig, sl);
-                if (t < ns * k && j < c) rows[t] = gload(o + (int32_t)__float_as_uint(rows[t].x));
-            }
-            wave_lds_fence();
-            if (lane < ns) {
-                const float4* r = rows + lane * k;
-                const auto fetch = [&](int j) { return r[j]; };
-                CovOut c;
-                if (FUSED == 1)
-                    covariance(mq.x, mq.y, mq.z, m_cnt, fetch, a.eps, c);
-                else
-                    covariance_weighted(mq.x, mq.y, mq.z, m_cnt, fetch, a.wt, a.eps, c);
-                store_cov(a.co, mq.qi, c);
-            }
-            ns = 0;
-            wave_lds_fence();
         }
+    }
+    if (FUSED) {
+        // the workgroup's rows together (every wavefront gets here)
+        __shared__ int s_ns[4];
+        wave_rows<FUSED>(a, k, ns, slots, rows);
+        if (lane == 0) s_ns[wid] = ns;
+        __syncthreads();
+        int sl = (int)threadIdx.x, w = 0;
+        while (w < 4 && sl >= s_ns[w]) sl -= s_ns[w++];
+        if (w < 4) wave_cov<FUSED>(a, slots_of(w)[sl], rows_of(w) + sl * k * RW);
     }
 }
 
@@ -2485,7 +2607,7 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     const unsigned full = (unsigned)ctx->num_cus * 6;
     const int64_t need = group ? full : (j.n_slots + 3) / 4;
     const dim3 wgrid(((unsigned)std::min<int64_t>(full, need) + 7) & ~7u);
-    a.cov_slots = std::max(1, std::min(WAVE_SLOTS, WAVE_ROWS / j.k));
+    a.cov_slots = wave_slots(j.k, j.fused);
     const size_t lds = 4 * wave_lds_bytes(j.k, a.cov_slots, j.fused);
     if (j.fused == 2)
         hipLaunchKernelGGL((k_wave<2, false>), wgrid, dim3(256), lds, st, a);

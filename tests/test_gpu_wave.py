@@ -85,7 +85,7 @@ def test_dense_cells(lk, n, k):
 @pytest.mark.parametrize("kernel", ["none", "laplacian"])
 def test_wavefront_and_group_search_agree(lk, k, kernel):
     """A scan (dense near the sensor, sparse rings far out) against itself and
-    another, covariances taken 16, 10 and 9 rows at a time."""
+    another: more rows than a wavefront keeps for their covariances at a time."""
     lkc, ctx = lk
     p = workloads.single_scan(seed=21)
     q = np.concatenate([workloads.single_scan(seed=22)[:7001],
