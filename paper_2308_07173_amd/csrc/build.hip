@@ -24,6 +24,7 @@
 // order makes every 16-point run of a dense cell spatially compact, so a
 // search can skip runs by their boxes.  Equal keys keep their original
 // order (the sort is stable), so the layout is deterministic.
+#include <algorithm>
 #include <climits>
 #include <cstring>
 #include <type_traits>
@@ -40,6 +41,7 @@ constexpr int BT = 256;          // threads per block for the build kernels
 constexpr int RS_ITEMS = 8;
 constexpr int RS_TILE = BT * RS_ITEMS;
 constexpr int RADIX = 256;
+constexpr unsigned KEY_BLOCKS = 2048;  // workgroups of k_make_keys, which each combine the parts
 constexpr int SCAN_TILE = 4096;  // entries per workgroup of the multi-block scan
 constexpr int RAW_OFFSET_TILES = 96;  // sorts of up to this many tiles skip the scan launch
 constexpr int RAW_RUN_BLOCKS = 2048;  // cell-run numbering of up to this many blocks skips it too
@@ -89,7 +91,7 @@ __device__ __forceinline__ uint32_t wave_maxu(uint32_t v) {
 }
 
 // Per-block partial of the occupied-cell box, the finiteness flag and the
-// largest |coordinate|; one record per block, combined by k_meta_reduce
+// largest |coordinate|; one record per block, combined by meta_combine
 // (no contended atomics).
 struct MetaPart {
     int cmin[3];
@@ -105,8 +107,8 @@ struct MetaPart {
 // (<= 4) those passes hold; a rebuild passes its previous pass count and the
 // layout fits into it (sub-cell bits only order points inside a cell), or
 // flags BAD_PASSES when even the cell key does not fit.
-__device__ void meta_combine(const MetaPart* __restrict__ parts, int64_t np,
-                             BuildMeta* __restrict__ meta, int fixed_passes) {
+__device__ void meta_combine(const MetaPart* __restrict__ parts, int64_t np, BuildMeta* meta,
+                             int fixed_passes) {
     int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {INT_MIN, INT_MIN, INT_MIN};
     int bad = 0;
     uint32_t ab = 0;
@@ -184,30 +186,34 @@ __device__ void meta_combine(const MetaPart* __restrict__ parts, int64_t np,
     }
 }
 
-// One record per point (orig, w = 0) and the per-block part of the box.
+// One record per point (orig, w = 0) and the per-block part of the box; at most
+// SCAN_PARTS workgroups.
+constexpr int SCAN_PARTS = 512;
 __global__ void __launch_bounds__(BT) k_scan_points(const float* __restrict__ p, int64_t n,
                                                     float inv_cell, float4* __restrict__ orig,
                                                     MetaPart* __restrict__ parts) {
-    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
     int mn[3] = {INT_MAX, INT_MAX, INT_MAX};
     int mx[3] = {INT_MIN, INT_MIN, INT_MIN};
     uint32_t mabs = 0;
     int bad = 0;
-    if (i < n) {
+    for (int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x; i < n; i += (int64_t)gridDim.x * BT) {
         const float x = p[3 * i], y = p[3 * i + 1], z = p[3 * i + 2];
         orig[i] = make_float4(x, y, z, 0.0f);
         if (!finite3(x, y, z)) {
-            bad = BAD_NONFINITE;
+            bad |= BAD_NONFINITE;
         } else {
             // cell coordinates beyond [-2^20, 2^20) would be clamped into an
             // edge cell whose box does not hold the point: refused
             const float f[3] = {floorf(x * inv_cell), floorf(y * inv_cell), floorf(z * inv_cell)};
             for (int a = 0; a < 3; ++a)
-                if (!(f[a] >= -(float)CELL_CLAMP && f[a] < (float)CELL_CLAMP)) bad = BAD_RANGE;
+                if (!(f[a] >= -(float)CELL_CLAMP && f[a] < (float)CELL_CLAMP)) bad |= BAD_RANGE;
             const int c[3] = {cell_coord(x, inv_cell), cell_coord(y, inv_cell),
                               cell_coord(z, inv_cell)};
-            for (int a = 0; a < 3; ++a) mn[a] = mx[a] = c[a];
-            mabs = __float_as_uint(fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))));
+            for (int a = 0; a < 3; ++a) {
+                mn[a] = min(mn[a], c[a]);
+                mx[a] = max(mx[a], c[a]);
+            }
+            mabs = max(mabs, __float_as_uint(fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z)))));
         }
     }
     __shared__ int s_mn[3][BT / WAVE], s_mx[3][BT / WAVE], s_bad[BT / WAVE];
@@ -247,36 +253,51 @@ __global__ void __launch_bounds__(BT) k_scan_points(const float* __restrict__ p,
     }
 }
 
-// One workgroup combines the parts (a separate launch: a last-block ticket
-// in the scan kernel needs a device-scope fence in every block, which costs
-// more than the launch at scan sizes).
+// One workgroup combines the parts, where the host has to read the result
+// before it can launch the sort.
 __global__ void __launch_bounds__(1024) k_meta_reduce(const MetaPart* __restrict__ parts,
                                                       int64_t np, BuildMeta* __restrict__ meta,
                                                       int fixed_passes) {
-    meta_combine(parts, np, meta, fixed_passes);
+    __shared__ BuildMeta m;
+    meta_combine(parts, np, &m, fixed_passes);
+    if (threadIdx.x == 0) *meta = m;
 }
 
 // Sort keys; the threads also clear the hash's slots (all `cap` of them,
-// ahead of the insert, which uses the first 2^hash_bits).
+// ahead of the insert, which uses the first 2^hash_bits).  With `np` every
+// workgroup first combines the parts for itself (16 KB from L2; a launch of
+// one workgroup that did it took 4.3 us, and a ticket for the last
+// workgroup of the scan needs a device-scope fence in every one of them).
 template <typename Key>
 __global__ void __launch_bounds__(BT) k_make_keys(const float4* __restrict__ orig, int64_t n,
-                                                  float inv_cell, const BuildMeta* __restrict__ meta,
+                                                  float inv_cell,
+                                                  const MetaPart* __restrict__ parts, int64_t np,
+                                                  int fixed_passes, BuildMeta* __restrict__ meta,
                                                   Key* __restrict__ keys,
                                                   uint32_t* __restrict__ vals,
                                                   HashSlot* __restrict__ hash, int64_t cap) {
-    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
-    for (int64_t h = i; h < cap; h += (int64_t)gridDim.x * BT) hash[h] = HashSlot{EMPTY_KEY, 0u, 0u};
-    if (i >= n) return;
-    const float4 p = orig[i];
-    const uint32_t cx = (uint32_t)(cell_coord(p.x, inv_cell) - meta->cmin[0]);
-    const uint32_t cy = (uint32_t)(cell_coord(p.y, inv_cell) - meta->cmin[1]);
-    const uint32_t cz = (uint32_t)(cell_coord(p.z, inv_cell) - meta->cmin[2]);
-    const int sb = meta->sub_bits;
-    const unsigned long long sub =
-        morton3(sub_cell(p.x, inv_cell, sb), sub_cell(p.y, inv_cell, sb),
-                sub_cell(p.z, inv_cell, sb));
-    keys[i] = (Key)((morton3(cx, cy, cz) << (3 * sb)) | sub);
-    vals[i] = (uint32_t)i;
+    __shared__ BuildMeta m;
+    const int64_t i0 = (int64_t)blockIdx.x * BT + threadIdx.x, step = (int64_t)gridDim.x * BT;
+    for (int64_t h = i0; h < cap; h += step) hash[h] = HashSlot{EMPTY_KEY, 0u, 0u};
+    if (np > 0) {
+        meta_combine(parts, np, &m, fixed_passes);
+        if (i0 == 0) *meta = m;
+    } else if (threadIdx.x == 0) {
+        m = *meta;
+    }
+    __syncthreads();
+    const int sb = m.sub_bits;
+    for (int64_t i = i0; i < n; i += step) {
+        const float4 p = orig[i];
+        const uint32_t cx = (uint32_t)(cell_coord(p.x, inv_cell) - m.cmin[0]);
+        const uint32_t cy = (uint32_t)(cell_coord(p.y, inv_cell) - m.cmin[1]);
+        const uint32_t cz = (uint32_t)(cell_coord(p.z, inv_cell) - m.cmin[2]);
+        const unsigned long long sub =
+            morton3(sub_cell(p.x, inv_cell, sb), sub_cell(p.y, inv_cell, sb),
+                    sub_cell(p.z, inv_cell, sb));
+        keys[i] = (Key)((morton3(cx, cy, cz) << (3 * sb)) | sub);
+        vals[i] = (uint32_t)i;
+    }
 }
 
 // Per-tile digit histogram, stored digit-major: counts[d * nblocks + b].
@@ -938,7 +959,8 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
     const size_t o_bc = carve(4 * (size_t)(nb_bt > 0 ? nb_bt : 1) + 4);
     const size_t o_bt = carve(4 * (size_t)(nb_bt / SCAN_TILE + 2));
     const size_t o_tk = carve(8 * nn), o_ts = carve(4 * nn + 4);
-    const size_t o_mp = carve(sizeof(MetaPart) * (size_t)(nb_bt > 0 ? nb_bt : 1));
+    const int64_t n_parts = std::min<int64_t>(nb_bt, SCAN_PARTS);
+    const size_t o_mp = carve(sizeof(MetaPart) * (size_t)(n_parts > 0 ? n_parts : 1));
     lkc_status s = ensure_scratch(ctx, off);
     if (s != LKC_OK) return s;
     char* sb = (char*)ctx->build_scratch;
@@ -997,12 +1019,13 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
     // Steps 2-6 for a sort of `passes` 8-bit passes; every layout parameter
     // is read from the device meta.  With `vout` the hash kernel writes the
     // device view (from `base`) and nothing is read back.
-    auto sorted = [&](auto* ka, auto* kb, int passes) -> lkc_status {
+    auto sorted = [&](auto* ka, auto* kb, int passes, int64_t np, int fixed) -> lkc_status {
         using Key = std::remove_pointer_t<decltype(ka)>;
         uint32_t *va = vals_a, *vb = vals_b;
         // ---- 2. keys
-        hipLaunchKernelGGL(k_make_keys<Key>, dim3(grid_for(n, BT)), dim3(BT), 0, st, orig, n,
-                           inv_cell, (const BuildMeta*)meta, ka, va, hash, cap_max);
+        hipLaunchKernelGGL(k_make_keys<Key>, dim3(std::min(grid_for(n, BT), KEY_BLOCKS)), dim3(BT), 0,
+                           st, orig, n, inv_cell, (const MetaPart*)mparts, np, fixed, meta, ka, va,
+                           hash, cap_max);
         // ---- 3. LSD radix sort
         bool in_b = false;
         lkc_status r = sort_pairs(ctx, ka, va, kb, vb, n, 8 * passes, rcounts, &in_b);
@@ -1022,11 +1045,12 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
                            meta, raw_runs);
         return LKC_OK;
     };
-    auto enqueue = [&](int passes, const TargetView* base) -> lkc_status {
+    auto enqueue = [&](int passes, const TargetView* base, int64_t np) -> lkc_status {
+        const int fixed = base ? passes : 0;   // (a view written on the device keeps to the passes)
         // (keys of four passes are sorted as 32-bit words: a third of the traffic less)
         const lkc_status r = passes <= 4
-                                 ? sorted((uint32_t*)keys_a, (uint32_t*)keys_b, passes)
-                                 : sorted(keys_a, keys_b, passes);
+                                 ? sorted((uint32_t*)keys_a, (uint32_t*)keys_b, passes, np, fixed)
+                                 : sorted(keys_a, keys_b, passes, np, fixed);
         if (r != LKC_OK) return r;
         // ---- 6. hash (cleared by k_make_keys)
         TargetView* vout = base ? t->view_dev : nullptr;
@@ -1042,10 +1066,8 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
     };
 
     if (fast) {
-        hipLaunchKernelGGL(k_scan_points, dim3(grid_for(n, BT)), dim3(BT), 0, st, points, n,
+        hipLaunchKernelGGL(k_scan_points, dim3((unsigned)n_parts), dim3(BT), 0, st, points, n,
                            inv_cell, orig, mparts);
-        hipLaunchKernelGGL(k_meta_reduce, dim3(1), dim3(1024), 0, st, (const MetaPart*)mparts,
-                           nb_bt, meta, prev_passes);
         V.pts = pts;
         V.orig = orig;
         V.hash = hash;
@@ -1057,7 +1079,7 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
             V.cmin[a] = 0;
             V.cmax[a] = -1;
         }
-        s = enqueue(prev_passes, &V);
+        s = enqueue(prev_passes, &V, n_parts);
         if (s != LKC_OK) return s;
         t->sort_passes = prev_passes;
         t->host_stale = true;
@@ -1069,10 +1091,8 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
     int hbits = 6;
     if (n > 0) {
         // ---- 1. cell coordinates, bounding box, finiteness, key layout
-        hipLaunchKernelGGL(k_scan_points, dim3(grid_for(n, BT)), dim3(BT), 0, st, points, n,
+        hipLaunchKernelGGL(k_scan_points, dim3((unsigned)n_parts), dim3(BT), 0, st, points, n,
                            inv_cell, orig, mparts);
-        hipLaunchKernelGGL(k_meta_reduce, dim3(1), dim3(1024), 0, st, (const MetaPart*)mparts,
-                           nb_bt, meta, 0);
         LKC_HIP_TRY(ctx, hipGetLastError());
         auto refuse = [&]() {
             V.n = 0;
@@ -1084,19 +1104,24 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
         // A first build reads the box (and the passes it needs) back first;
         // a rebuild runs on with the previous build's passes.
         int passes = prev_passes;
+        int64_t np = n_parts;
         if (passes <= 0) {
+            hipLaunchKernelGGL(k_meta_reduce, dim3(1), dim3(1024), 0, st, (const MetaPart*)mparts,
+                               n_parts, meta, 0);
+            LKC_HIP_TRY(ctx, hipGetLastError());
+            np = 0;
             LKC_HIP_TRY(ctx, hipMemcpyAsync(hmeta, meta, sizeof(BuildMeta),
                                             hipMemcpyDeviceToHost, st));
             LKC_HIP_TRY(ctx, hipStreamSynchronize(st));
             if (hmeta->nonfinite) return refuse();
             passes = hmeta->passes;
         }
-        s = enqueue(passes, nullptr);
+        s = enqueue(passes, nullptr, np);
         if (s != LKC_OK) return s;
         if (hmeta->nonfinite) return refuse();
         if (hmeta->passes > passes) {
             // the key outgrew the previous build's passes: sort again in full
-            s = enqueue(hmeta->passes, nullptr);
+            s = enqueue(hmeta->passes, nullptr, 0);
             if (s != LKC_OK) return s;
         }
         for (int a = 0; a < 3; ++a) {
