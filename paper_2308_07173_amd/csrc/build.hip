@@ -17,6 +17,7 @@
 //   4. reorder       points into that order as float4 (x, y, z, original idx),
 //                    and the bounding box of every aligned 16-point run
 //   5. cell runs     run boundaries of the cell part of the key
+//                    (up to RANK_MAX points: 3-5 by counting, in two launches)
 //   6. hash insert   open addressing, linear probing, capacity 2^ceil(log2 2C);
 //                    the hash key is the row-major compact cell key
 //
@@ -43,6 +44,10 @@ constexpr int RS_TILE = BT * RS_ITEMS;
 constexpr int RADIX = 256;
 constexpr unsigned KEY_BLOCKS = 2048;  // workgroups of k_make_keys, which each combine the parts
 constexpr int SCAN_TILE = 4096;  // entries per workgroup of the multi-block scan
+// Targets of up to this many points are sorted by counting.  A rebuild of 2,048
+// points takes 29 us so and 42 by radix passes, 4,096 31 and 50, 8,192 40 and
+// 53, 12,000 54 and 55, 16,384 57 and 58; the work grows with the square.
+constexpr int RANK_MAX = 8192;
 constexpr int RAW_OFFSET_TILES = 96;  // sorts of up to this many tiles skip the scan launch
 constexpr int RAW_RUN_BLOCKS = 2048;  // cell-run numbering of up to this many blocks skips it too
 
@@ -596,40 +601,67 @@ __global__ void __launch_bounds__(BT) k_radix_scatter(
     }
 }
 
-// Cell runs (their per-block counts come from k_reorder).
-// Pass 2: each run start writes its cell's row-major key (recomputed from the
-// reordered point) and its first position; the last point records the cell
-// count and the hash size.  `boff` holds the blocks' first cell ids, or with
-// `raw` the blocks' run counts, which each block then sums itself (for up
-// to RAW_RUN_BLOCKS blocks, saving the scan launch).
+// Sort and reorder of few points in one launch: a point's place is the number
+// of keys below its own, or equal and earlier, counted directly.  A workgroup
+// places 64 points (one per lane); its 16 wavefronts each count through a
+// sixteenth of the keys, which are the same for all lanes and so come as
+// scalar operands, two instructions a key.  n^2 work, but one launch for the
+// sort passes' and the reorder's.  Bound by launches up to some 4,000 points,
+// by VALU issue above.
 template <typename Key>
-__global__ void __launch_bounds__(BT) k_cell_write(const Key* __restrict__ keys,
-                                                   const float4* __restrict__ pts, int64_t n,
-                                                   float inv_cell,
-                                                   const uint32_t* __restrict__ boff,
-                                                   unsigned long long* __restrict__ ckeys,
-                                                   uint32_t* __restrict__ cstart,
-                                                   BuildMeta* __restrict__ meta, int raw) {
-    __shared__ uint32_t s_w[BT / WAVE], s_b[BT / WAVE];
-    const int sub_shift = 3 * meta->sub_bits;
-    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
-    uint32_t before = 0;
-    if (raw)
-        for (int j = threadIdx.x; j < (int)blockIdx.x; j += BT) before += boff[j];
-    const bool f = i < n && (i == 0 || (keys[i] >> sub_shift) != (keys[i - 1] >> sub_shift));
-    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
-    const unsigned long long bal = __ballot(f);
-    const uint32_t pre = (uint32_t)__popcll(bal & ((1ull << l) - 1ull));
-    for (int sft = WAVE / 2; sft > 0; sft >>= 1) before += (uint32_t)__shfl_xor((int)before, sft);
-    if (l == 0) {
-        s_w[w] = (uint32_t)__popcll(bal);
-        s_b[w] = before;
-    }
+__global__ void __launch_bounds__(1024) k_rank(const float4* __restrict__ orig,
+                                               const Key* __restrict__ keys, int n,
+                                               float4* __restrict__ pts, Key* __restrict__ sorted) {
+    constexpr int NW = 1024 / WAVE, U = 16;
+    __shared__ int s_c[NW][WAVE];
+    const int l = threadIdx.x % WAVE;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int first = (int)blockIdx.x * WAVE, i = first + l;
+    const Key mine = keys[min(i, n - 1)];
+    const int per = (n + NW - 1) / NW;
+    const int lo = min(w * per, n), hi = min(lo + per, n);
+    int c = 0;
+    // the keys of earlier workgroups count when equal, those of later ones not
+    const auto count = [&](int b, int e, auto counts) {
+        int j = b;
+        for (; j + U <= e; j += U) {
+            Key v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = keys[j + u];
+#pragma unroll
+            for (int u = 0; u < U; ++u) c += counts(v[u], j + u) ? 1 : 0;
+        }
+        for (; j < e; ++j) c += counts(keys[j], j) ? 1 : 0;
+    };
+    count(lo, min(hi, first), [&](Key v, int) { return v <= mine; });
+    count(max(lo, first), min(hi, first + WAVE),
+          [&](Key v, int j) { return v < mine || (v == mine && j < i); });
+    count(max(lo, first + WAVE), hi, [&](Key v, int) { return v < mine; });
+    s_c[w][l] = c;
     __syncthreads();
-    uint32_t wo = 0, base = 0;
-    for (int j = 0; j < w; ++j) wo += s_w[j];
-    for (int j = 0; j < BT / WAVE; ++j) base += s_b[j];
-    const uint32_t cid = (raw ? base : boff[blockIdx.x]) + wo + pre;
+    if (w != 0 || i >= n) return;
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) rank += s_c[j][l];
+    const float4 p = orig[i];
+    pts[rank] = make_float4(p.x, p.y, p.z, __int_as_float(i));
+    sorted[rank] = mine;
+}
+
+// Whether sorted point i begins a cell.
+template <typename Key>
+__device__ __forceinline__ bool cell_begins(const Key* __restrict__ keys, int64_t i, int64_t n,
+                                            int sub_shift) {
+    return i < n && (i == 0 || (keys[i] >> sub_shift) != (keys[i - 1] >> sub_shift));
+}
+
+// Cell `cid` begins at sorted point i (`f`): its row-major key, recomputed from
+// the point, and first position; the last point records the cell count and the
+// hash size.
+__device__ __forceinline__ void write_cell(const float4* __restrict__ pts, int64_t i, int64_t n,
+                                           bool f, uint32_t cid, float inv_cell,
+                                           unsigned long long* __restrict__ ckeys,
+                                           uint32_t* __restrict__ cstart, BuildMeta* meta) {
     if (f) {
         const float4 p = pts[i];
         const uint32_t cx = (uint32_t)(cell_coord(p.x, inv_cell) - meta->cmin[0]);
@@ -646,6 +678,95 @@ __global__ void __launch_bounds__(BT) k_cell_write(const Key* __restrict__ keys,
         meta->n_cells = nc;
         meta->hash_bits = hb;
     }
+}
+
+// The bounding box of every aligned 16-point run of the sorted points: one
+// 16-lane quarter of a wavefront per box, lane i's point is p.
+__device__ __forceinline__ void write_box(float4 p, int64_t i, int64_t n,
+                                          float4* __restrict__ boxes) {
+    const int64_t box = i / BOX_PTS;
+    const bool v = i < n;
+    float lo[3] = {v ? p.x : INFINITY, v ? p.y : INFINITY, v ? p.z : INFINITY};
+    float hi[3] = {v ? p.x : -INFINITY, v ? p.y : -INFINITY, v ? p.z : -INFINITY};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+        for (int s = BOX_PTS / 2; s > 0; s >>= 1) {
+            lo[a] = fminf(lo[a], __shfl_xor(lo[a], s));
+            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], s));
+        }
+    }
+    if (i % BOX_PTS == 0 && box * BOX_PTS < n) {
+        boxes[2 * box] = make_float4(lo[0], lo[1], lo[2], 0.f);
+        boxes[2 * box + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
+    }
+}
+
+// After k_rank: run boxes and cells in one launch.  Every workgroup counts the
+// cells that begin before its points itself.
+template <typename Key>
+__global__ void __launch_bounds__(1024) k_cells_few(const Key* __restrict__ keys,
+                                                    const float4* __restrict__ pts, int n,
+                                                    float inv_cell, float4* __restrict__ boxes,
+                                                    unsigned long long* __restrict__ ckeys,
+                                                    uint32_t* __restrict__ cstart,
+                                                    BuildMeta* __restrict__ meta) {
+    constexpr int T = 1024, NW = T / WAVE;
+    __shared__ uint32_t s_w[NW], s_b[NW];
+    const int sub_shift = 3 * meta->sub_bits;
+    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+    const int base = (int)blockIdx.x * T, i = base + (int)threadIdx.x;
+    uint32_t before = 0;
+#pragma unroll 4
+    for (int j = (int)threadIdx.x; j < base; j += T)   // (base is a multiple of T)
+        before += cell_begins(keys, j, n, sub_shift) ? 1u : 0u;
+    for (int sft = WAVE / 2; sft > 0; sft >>= 1) before += (uint32_t)__shfl_xor((int)before, sft);
+    const bool f = cell_begins(keys, i, n, sub_shift);
+    const unsigned long long bal = __ballot(f);
+    if (l == 0) {
+        s_w[w] = (uint32_t)__popcll(bal);
+        s_b[w] = before;
+    }
+    write_box(pts[min(i, n - 1)], i, n, boxes);
+    __syncthreads();
+    uint32_t cid = (uint32_t)__popcll(bal & ((1ull << l) - 1ull));
+    for (int j = 0; j < NW; ++j) cid += s_b[j] + (j < w ? s_w[j] : 0u);
+    write_cell(pts, i, n, f, cid, inv_cell, ckeys, cstart, meta);
+}
+
+// Cell runs (their per-block counts come from k_reorder).
+// Pass 2: the cells are numbered and written.  `boff` holds the blocks' first cell ids, or with
+// `raw` the blocks' run counts, which each block then sums itself (for up
+// to RAW_RUN_BLOCKS blocks, saving the scan launch).
+template <typename Key>
+__global__ void __launch_bounds__(BT) k_cell_write(const Key* __restrict__ keys,
+                                                   const float4* __restrict__ pts, int64_t n,
+                                                   float inv_cell,
+                                                   const uint32_t* __restrict__ boff,
+                                                   unsigned long long* __restrict__ ckeys,
+                                                   uint32_t* __restrict__ cstart,
+                                                   BuildMeta* __restrict__ meta, int raw) {
+    __shared__ uint32_t s_w[BT / WAVE], s_b[BT / WAVE];
+    const int sub_shift = 3 * meta->sub_bits;
+    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
+    uint32_t before = 0;
+    if (raw)
+        for (int j = threadIdx.x; j < (int)blockIdx.x; j += BT) before += boff[j];
+    const bool f = cell_begins(keys, i, n, sub_shift);
+    const int l = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
+    const unsigned long long bal = __ballot(f);
+    const uint32_t pre = (uint32_t)__popcll(bal & ((1ull << l) - 1ull));
+    for (int sft = WAVE / 2; sft > 0; sft >>= 1) before += (uint32_t)__shfl_xor((int)before, sft);
+    if (l == 0) {
+        s_w[w] = (uint32_t)__popcll(bal);
+        s_b[w] = before;
+    }
+    __syncthreads();
+    uint32_t wo = 0, base = 0;
+    for (int j = 0; j < w; ++j) wo += s_w[j];
+    for (int j = 0; j < BT / WAVE; ++j) base += s_b[j];
+    const uint32_t cid = (raw ? base : boff[blockIdx.x]) + wo + pre;
+    write_cell(pts, i, n, f, cid, inv_cell, ckeys, cstart, meta);
 }
 
 // Clears the hash slots in use: 2^bits, or 2^meta->hash_bits with bits = 0.
@@ -729,31 +850,16 @@ __global__ void __launch_bounds__(BT) k_reorder(const float4* __restrict__ orig,
                                                 uint32_t* __restrict__ bcount) {
     const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
     const int sub_shift = 3 * meta->sub_bits;
-    const bool f = i < n && (i == 0 || (keys[i] >> sub_shift) != (keys[i - 1] >> sub_shift));
+    const bool f = cell_begins(keys, i, n, sub_shift);
     const int c = __syncthreads_count(f);
     if (threadIdx.x == 0) bcount[blockIdx.x] = (uint32_t)c;
-    const int64_t box = i / BOX_PTS;
-    const bool v = i < n;
     float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (v) {
+    if (i < n) {
         const uint32_t o = vals[i];
         p = orig[o];
         pts[i] = make_float4(p.x, p.y, p.z, __int_as_float((int)o));
     }
-    float lo[3] = {v ? p.x : INFINITY, v ? p.y : INFINITY, v ? p.z : INFINITY};
-    float hi[3] = {v ? p.x : -INFINITY, v ? p.y : -INFINITY, v ? p.z : -INFINITY};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-#pragma unroll
-        for (int s = BOX_PTS / 2; s > 0; s >>= 1) {
-            lo[a] = fminf(lo[a], __shfl_xor(lo[a], s));
-            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], s));
-        }
-    }
-    if (i % BOX_PTS == 0 && box * BOX_PTS < n) {
-        boxes[2 * box] = make_float4(lo[0], lo[1], lo[2], 0.f);
-        boxes[2 * box + 1] = make_float4(hi[0], hi[1], hi[2], 0.f);
-    }
+    write_box(p, i, n, boxes);
 }
 
 __global__ void k_iota(uint32_t* __restrict__ v, int64_t n) {
@@ -1026,6 +1132,15 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
         hipLaunchKernelGGL(k_make_keys<Key>, dim3(std::min(grid_for(n, BT), KEY_BLOCKS)), dim3(BT), 0,
                            st, orig, n, inv_cell, (const MetaPart*)mparts, np, fixed, meta, ka, va,
                            hash, cap_max);
+        if (n <= RANK_MAX) {
+            // ---- 3.-5. by counting
+            hipLaunchKernelGGL(k_rank<Key>, dim3((unsigned)((n + WAVE - 1) / WAVE)), dim3(1024), 0,
+                               st, orig, (const Key*)ka, (int)n, pts, kb);
+            hipLaunchKernelGGL(k_cells_few<Key>, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), 0,
+                               st, (const Key*)kb, (const float4*)pts, (int)n, inv_cell, boxes,
+                               tkeys, tstart, meta);
+            return LKC_OK;
+        }
         // ---- 3. LSD radix sort
         bool in_b = false;
         lkc_status r = sort_pairs(ctx, ka, va, kb, vb, n, 8 * passes, rcounts, &in_b);
