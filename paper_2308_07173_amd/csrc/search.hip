@@ -308,15 +308,67 @@ __device__ __forceinline__ float box_dist2(const TargetView& T, float qx, float 
 // Squared distance up to which no point lies outside the (2R+1)^3 block of
 // cells around cell cq of query q (0 when not even the block's faces are
 // clear of it).
-__device__ __forceinline__ float block_clear2(const TargetView& T, const float (&q)[3],
-                                              const int (&cq)[3], int R, float margin) {
+__device__ __forceinline__ float block_clear2(float cell, const float (&q)[3], const int (&cq)[3],
+                                              int R, float margin) {
     float f = INF;
     for (int a = 0; a < 3; ++a) {
-        const float lo = (float)(cq[a] - R) * T.cell, hi = (float)(cq[a] + R + 1) * T.cell;
+        const float lo = (float)(cq[a] - R) * cell, hi = (float)(cq[a] + R + 1) * cell;
         f = fminf(f, fminf(q[a] - lo, hi - q[a]));
     }
     f = fmaxf(f - margin, 0.0f);
     return f * f * (1.0f - 1e-6f);
+}
+
+// Slack for the rounding of cell faces up to R + 2 cells from a query (`reach`:
+// the largest |coordinate| of the query and the target).
+__device__ __forceinline__ float wave_margin(float reach, float cell, int R) {
+    return (reach + (float)(R + 2) * cell) * 1e-6f;
+}
+
+// What the wavefront search of a query starts from, all of it uniform.  The
+// plans of a wavefront's next WAVE_PLANS queries are laid out together, a lane
+// each: worked out one query at a time they were a quarter of the
+// instructions of a k = 1 search (the same in every lane), and each began
+// with a load of its own.
+struct alignas(16) WavePlan {
+    float x, y, z;
+    int32_t qi;      // output row
+    int cq[3];       // the query's cell
+    int tgc;         // self queries: the query's own 64-record chunk; else the target
+    int R, rmax;     // first and last ring (rmax < 0: nothing to search)
+    float reach;     // largest |coordinate| of query and target
+    float clear2;    // block_clear2 of the first ring
+};
+constexpr int WAVE_PLANS = 8;
+
+__device__ __forceinline__ WavePlan wave_plan(const TargetView& V, float x, float y, float z,
+                                              int32_t qi, int tgc, int capped, float radius) {
+    WavePlan w;
+    w.x = x;
+    w.y = y;
+    w.z = z;
+    w.qi = qi;
+    w.tgc = tgc;
+    const float cell = V.cell, inv_cell = V.inv_cell;
+    const float q[3] = {x, y, z};
+    int R = 0, rmax = 0;
+    // rings closer than the occupied box hold no cells: start at the first
+    // ring that reaches it, end at the last
+    for (int a = 0; a < 3; ++a) {
+        const int c = cell_coord(q[a], inv_cell), lo = V.cmin[a], hi = V.cmax[a];
+        w.cq[a] = c;
+        R = max(R, max(lo - c, c - hi));
+        rmax = max(rmax, max(c - lo, hi - c));
+    }
+    if (capped) {
+        const float rc = ceilf(radius * inv_cell) + 1.0f;
+        if (rc < (float)rmax) rmax = (int)rc;
+    }
+    w.R = R;
+    w.rmax = finite3(x, y, z) && V.n_cells > 0 ? rmax : -1;
+    w.reach = fmaxf(fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))), V.max_abs);
+    w.clear2 = block_clear2(cell, q, w.cq, 1, wave_margin(w.reach, cell, 1));
+    return w;
 }
 
 // The candidates of one query that hold its k nearest points, whole wavefront
@@ -331,28 +383,14 @@ __device__ __forceinline__ float block_clear2(const TargetView& T, const float (
 // in memory.)
 template <typename List>
 __device__ __forceinline__ void knn_query_wave(const TargetView& T, const TargetView* Tp,
-                                               const WaveQuery& sp, bool self, int capped,
-                                               List& L) {
+                                               const WavePlan& w, bool self, List& L) {
     const int lane = lane_id();
-    const float qx = sp.x, qy = sp.y, qz = sp.z;
-    const int cq[3] = {__builtin_amdgcn_readfirstlane(cell_coord(qx, T.inv_cell)),
-                       __builtin_amdgcn_readfirstlane(cell_coord(qy, T.inv_cell)),
-                       __builtin_amdgcn_readfirstlane(cell_coord(qz, T.inv_cell))};
+    const float qx = w.x, qy = w.y, qz = w.z;
+    const int cq[3] = {w.cq[0], w.cq[1], w.cq[2]};
     const float q[3] = {qx, qy, qz};
-    // rings closer than the occupied box hold no cells: start at the first
-    // ring that reaches it, end at the last
-    int R = 0, rmax = 0;
-    for (int a = 0; a < 3; ++a) {
-        R = max(R, max(T.cmin[a] - cq[a], cq[a] - T.cmax[a]));
-        rmax = max(rmax, max(cq[a] - T.cmin[a], T.cmax[a] - cq[a]));
-    }
-    if (capped) {
-        const float rc = ceilf(sqrtf(L.bound) * T.inv_cell) + 1.0f;
-        if (rc < (float)rmax) rmax = (int)rc;
-    }
-    R = __builtin_amdgcn_readfirstlane(R);
-    rmax = __builtin_amdgcn_readfirstlane(rmax);
-    const float qabs = fmaxf(fabsf(qx), fmaxf(fabsf(qy), fabsf(qz)));
+    const WaveQuery sp{qx, qy, qz, self ? w.tgc : -1};
+    int R = w.R;
+    const int rmax = w.rmax;
     if (self) {
         const int p = sp.skip * WAVE + lane;
         const float4 t = gload(T.pts + p);   // (64 spare records)
@@ -363,7 +401,7 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
     uint32_t st = 0, cn = 0;
     float bd = INF;
     if (R == 0 && rmax >= 1) {
-        const float margin = (fmaxf(qabs, T.max_abs) + 3.0f * T.cell) * 1e-6f;
+        const float margin = wave_margin(w.reach, T.cell, 1);
         // the 27 cells around cq, x fastest
         const int dz = (lane * 57) >> 9, r = lane - 9 * dz, dy = (r * 11) >> 5;
         const int cx = cq[0] + r - 3 * dy - 1, cy = cq[1] + dy - 1, cz = cq[2] + dz - 1;
@@ -379,13 +417,13 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
             if (ballot(want)) scan_cells(T, sp, want, st, cn, margin, L);
             if (pass == 0) L.tighten();
         }
-        if (L.within(block_clear2(T, q, cq, 1, margin))) return;
+        if (L.within(w.clear2)) return;
         L.tighten();
         R = 2;
     }
 #pragma unroll 1
     for (; R <= rmax; ++R) {
-        const float margin = (fmaxf(qabs, T.max_abs) + (float)(R + 2) * T.cell) * 1e-6f;
+        const float margin = wave_margin(w.reach, T.cell, R);
         int lo[3], ext[3];
         int64_t total = 1;
         for (int a = 0; a < 3; ++a) {
@@ -456,7 +494,7 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
                 L.tighten();
             }
         }
-        if (sweep || L.within(block_clear2(T, q, cq, R, margin))) return;
+        if (sweep || L.within(block_clear2(T.cell, q, cq, R, margin))) return;
     }
 }
 
@@ -1897,11 +1935,11 @@ static_assert(sizeof(WaveSlot) == 24, "WaveSlot layout");
 // from the query (and its weight).
 __host__ __device__ constexpr int row_words(int fused) { return fused == 2 ? 4 : 3; }
 
-// LDS of one wavefront: the candidate list, the slots, their rows.  With 5,560
+// LDS of one wavefront: its plans, the candidate list, the slots, their rows.  With 5,300
 // bytes of slots and rows six workgroups of four fit a CU's 160 KB, of which
-// they take multiples of 1,280 bytes (k = 20: 21 rows; at 5,760 bytes it is
-// five, and the 65k-point match takes 152 us instead of 125).
-constexpr int WAVE_SLOTS = 32, WAVE_ROW_BYTES = 5560;
+// they take multiples of 1,280 bytes (k = 20: 20 rows; with a few hundred bytes
+// more it is five, and the 65k-point match took 152 us instead of 125).
+constexpr int WAVE_SLOTS = 32, WAVE_ROW_BYTES = 5300;
 
 __host__ __device__ inline int wave_slots(int k, int fused) {
     const int fit = WAVE_ROW_BYTES / (4 * k * row_words(fused) + (int)sizeof(WaveSlot));
@@ -1909,7 +1947,7 @@ __host__ __device__ inline int wave_slots(int k, int fused) {
 }
 __host__ __device__ inline size_t wave_lds_bytes(int k, int slots, int fused) {
     const size_t rows = fused ? (size_t)slots * (4 * k * row_words(fused) + sizeof(WaveSlot)) : 0;
-    return (size_t)WaveList::CAP * 8 + ((rows + 7) & ~(size_t)7);
+    return WAVE_PLANS * sizeof(WavePlan) + (size_t)WaveList::CAP * 8 + ((rows + 15) & ~(size_t)15);
 }
 
 // Gathers the points of a wavefront's kept rows; offsets and weights in place
@@ -1985,7 +2023,7 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 // The list of 99,000 queries that the group search hands over in a batch of
 // 3.76 M takes 63 us (the wavefront search before it: 154).
 //
-// ONE: k = 1 without covariances (no list, no LDS).
+// ONE: k = 1 without covariances (no list).
 template <int FUSED, bool ONE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
     extern __shared__ unsigned long long s_wave[];
@@ -1993,10 +2031,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int k = a.sp.k;
     constexpr int RW = row_words(FUSED);
+    __shared__ WavePlan s_one[ONE ? 4 * WAVE_PLANS : 1];
     const size_t per_wave = wave_lds_bytes(k, a.cov_slots, FUSED);
-    const auto list_of = [&](int w) { return (unsigned long long*)((char*)s_wave + w * per_wave); };
+    const auto plans_of = [&](int w) { return (WavePlan*)((char*)s_wave + w * per_wave); };
+    const auto list_of = [&](int w) { return (unsigned long long*)(plans_of(w) + WAVE_PLANS); };
     const auto slots_of = [&](int w) { return (WaveSlot*)(list_of(w) + WaveList::CAP); };
     const auto rows_of = [&](int w) { return (float*)(slots_of(w) + a.cov_slots); };   // [slot][k][RW]
+    WavePlan* plans = ONE ? s_one + wid * WAVE_PLANS : plans_of(wid);
     unsigned long long* buf = list_of(wid);
     WaveSlot* slots = slots_of(wid);
     float* rows = rows_of(wid);
@@ -2009,39 +2050,65 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     const int64_t hi = n * (x + 1) / 8, step = (int64_t)nx * (blockDim.x / WAVE);
     int64_t i = n * x / 8 + (int64_t)(blockIdx.x / 8) * (blockDim.x / WAVE) + wid;
     int ns = 0;   // kept rows
+    const bool self = a.queries == nullptr;
+    const float radius = sqrtf(a.sp.r2);
+    int b = WAVE_PLANS;   // the current query's plan
 #pragma unroll 1
     for (; i < hi; i += step) {
-        const int64_t slot = a.fb_list ? (int64_t)load_uniform(a.fb_list + i) : i;
-        int tg = a.skeys ? (int)(load_uniform(a.skeys + slot) >> a.tshift) : 0;
-        tg = __builtin_amdgcn_readfirstlane(tg);
+        if (++b >= WAVE_PLANS) {
+            b = 0;
+            wave_lds_fence();
+            const int64_t li = i + (int64_t)lane * step;
+            if (lane < WAVE_PLANS && li < hi) {
+                const int64_t slot = a.fb_list ? (int64_t)gload(a.fb_list + li) : li;
+                const int tg = a.skeys ? (int)(a.skeys[slot] >> a.tshift) : 0;
+                const TargetView& V = a.views[tg];
+                SlotQuery s{-1, 0.f, 0.f, 0.f, tg};
+                if (!self || slot < V.n) s = load_slot(a, V, slot);
+                if (ONE && a.moved) rigid_apply(a.move, s.x, s.y, s.z);
+                // (a self query of a target that a failed rebuild left empty)
+                const bool none = s.qi < 0;
+                if (none) s.qi = slot;
+                WavePlan w = wave_plan(V, s.x, s.y, s.z, (int32_t)s.qi,
+                                       self ? (int)(slot / WAVE) : tg, a.sp.capped, radius);
+                if (none) w.rmax = -1;
+                plans[lane] = w;
+            }
+            wave_lds_fence();
+        }
+        WavePlan s;
+        {
+            const int4* from = (const int4*)(plans + b);
+            int w[12];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const int4 v = from[e];
+                w[4 * e] = __builtin_amdgcn_readfirstlane(v.x);
+                w[4 * e + 1] = __builtin_amdgcn_readfirstlane(v.y);
+                w[4 * e + 2] = __builtin_amdgcn_readfirstlane(v.z);
+                w[4 * e + 3] = __builtin_amdgcn_readfirstlane(v.w);
+            }
+            static_assert(sizeof w == sizeof s, "WavePlan layout");
+            __builtin_memcpy(&s, w, sizeof s);
+        }
+        const int tg = self ? 0 : s.tgc;
         const TargetView T = load_uniform(a.views + tg);
-        SlotQuery s{-1, 0.f, 0.f, 0.f, tg};
-        const bool self = a.queries == nullptr;
-        if (!self || slot < T.n) s = load_slot(a, T, slot);
-        if (ONE && a.moved) rigid_apply(a.move, s.x, s.y, s.z);
-        s.x = uniform_f(s.x);
-        s.y = uniform_f(s.y);
-        s.z = uniform_f(s.z);
-        s.qi = __builtin_amdgcn_readfirstlane((int)s.qi);
-        const bool search = finite3(s.x, s.y, s.z) && T.n_cells > 0 && s.qi >= 0;
-        // (a self query of a target that a failed rebuild left empty)
-        if (s.qi < 0) s.qi = slot;
-        const WaveQuery q{s.x, s.y, s.z, self ? (int)(slot / WAVE) : -1};
+        const bool search = s.rmax >= 0;
         if (ONE) {
             WaveNearest L{a.sp.r2, INF, IDX_SENTINEL};
-            if (search) knn_query_wave(T, a.views + tg, q, self, a.sp.capped, L);
+            if (search) knn_query_wave(T, a.views + tg, s, self, L);
             const float d = wave_min_dpp(L.d);
             const int32_t best = wave_min_i32(L.d == d ? L.i : IDX_SENTINEL);
             if (lane == 0) {
                 const bool have = best != IDX_SENTINEL;
-                a.ko.idx[s.qi] = have ? best : -1;
+                a.ko.idx[(int64_t)s.qi] = have ? best : -1;
                 a.ko.d2[s.qi] = have ? d : INF;
                 a.ko.count[s.qi] = have ? 1 : 0;
             }
             continue;
         }
         WaveList L{buf, a.sp.r2, 0, k, false};
-        if (search) knn_query_wave(T, a.views + tg, q, self, a.sp.capped, L);
+        if (search) knn_query_wave(T, a.views + tg, s, self, L);
         // each entry's place among the k smallest, by counting
         wave_lds_fence();
         const unsigned long long my = lane < L.n ? buf[lane] : ~0ull;
@@ -2054,8 +2121,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         }
         const int cnt = min(L.n, k);
         const bool in = lane < L.n && rank < k;
-        int32_t* irow = a.ko.idx + s.qi * k;
-        float* drow = a.ko.d2 + s.qi * k;
+        int32_t* irow = a.ko.idx + (int64_t)s.qi * k;
+        float* drow = a.ko.d2 + (int64_t)s.qi * k;
         if (in) {
             irow[rank] = (int32_t)(uint32_t)my;
             drow[rank] = __uint_as_float((uint32_t)(my >> 32));
@@ -2068,7 +2135,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         if (FUSED) {
             if (in) rows[(ns * k + rank) * RW] = __uint_as_float((uint32_t)my);
             if (lane == 0)
-                slots[ns] = WaveSlot{s.x, s.y, s.z, cnt, (int32_t)s.qi, {tg}};
+                slots[ns] = WaveSlot{s.x, s.y, s.z, cnt, s.qi, {tg}};
             if (++ns == a.cov_slots && i + step < hi) {
                 wave_rows<FUSED>(a, k, ns, slots, rows);
                 if (lane < ns) wave_cov<FUSED>(a, slots[lane], rows + lane * k * RW);
