@@ -292,6 +292,23 @@ __device__ __forceinline__ void scan_cells(const TargetView& T, const WaveQuery&
         scan_points(T, q, want, (int)start, total, incl - c, L);
 }
 
+// The points of one cell.
+template <typename List>
+__device__ __forceinline__ void scan_one(const TargetView& T, const WaveQuery& q, int st, int cn,
+                                         List& L) {
+    const int lane = lane_id();
+#pragma unroll 1
+    for (int b0 = 0; b0 < cn; b0 += 2 * WAVE) {
+        const bool two = b0 + WAVE < cn;
+        const int f0 = b0 + lane, f1 = f0 + WAVE;
+        const float4 p0 = gload(T.pts + st + min(f0, cn - 1));
+        float4 p1 = p0;
+        if (two) p1 = gload(T.pts + st + min(f1, cn - 1));
+        L.add(f0 < cn, dist2(q.x, q.y, q.z, p0.x, p0.y, p0.z), __float_as_int(p0.w));
+        if (two) L.add(f1 < cn, dist2(q.x, q.y, q.z, p1.x, p1.y, p1.z), __float_as_int(p1.w));
+    }
+}
+
 // Squared distance from q to the box of cell c, shrunk by `margin` on every
 // side to absorb the rounding of the float cell assignment.
 __device__ __forceinline__ float box_dist2(const TargetView& T, float qx, float qy, float qz,
@@ -411,8 +428,20 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
             bd = box_dist2(T, qx, qy, qz, cx, cy, cz, margin) * (1.0f - 1e-6f);
             if (bd <= L.bound) found = hash_find(T, pack_key(T, cx, cy, cz), st, cn) && cn > 0;
         }
+        int pass = self ? 1 : 0;
+        if (!self) {
+            const int oc = readlane(found ? (int)cn : 0, 13);
+            if (oc <= RUN_SCAN_MIN) {
+                // one cell of few points: no concatenation to work out
+                if (oc > 0) {
+                    scan_one(T, sp, readlane((int)st, 13), oc, L);
+                    L.tighten();
+                }
+                pass = 1;
+            }
+        }
 #pragma unroll 1
-        for (int pass = self ? 1 : 0; pass < 2; ++pass) {
+        for (; pass < 2; ++pass) {
             const bool want = found && (pass == 0 ? own : (self || !own) && bd <= L.bound);
             if (ballot(want)) scan_cells(T, sp, want, st, cn, margin, L);
             if (pass == 0) L.tighten();
