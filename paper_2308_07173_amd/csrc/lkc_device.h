@@ -233,7 +233,6 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
     v = fmaxf(v, dpp_f<0x143, 0xc>(id, v));  // row_bcast:31 (lane 63: wave max)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
-__device__ __forceinline__ float wave_min_dpp(float v) { return -wave_max_dpp(-v); }
 
 // The same for integers.
 template <int CTRL, int ROW_MASK>
@@ -249,6 +248,41 @@ __device__ __forceinline__ int wave_min_i32(int v) {
     v = min(v, dpp_i<0x142, 0xa>(id, v));
     v = min(v, dpp_i<0x143, 0xc>(id, v));
     return __builtin_amdgcn_readlane(v, 63);
+}
+
+__device__ __forceinline__ int wave_max_i32(int v) {
+    const int id = -0x7fffffff - 1;
+    v = max(v, dpp_i<0x111, 0xf>(id, v));
+    v = max(v, dpp_i<0x112, 0xf>(id, v));
+    v = max(v, dpp_i<0x114, 0xf>(id, v));
+    v = max(v, dpp_i<0x118, 0xf>(id, v));
+    v = max(v, dpp_i<0x142, 0xa>(id, v));
+    v = max(v, dpp_i<0x143, 0xc>(id, v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+// Of floats >= 0 (+infinity included, no NaN), which order as their bits do: one
+// instruction a step, where the float maximum takes four (the DPP move and the
+// quieting of its operands apart).
+__device__ __forceinline__ float wave_min_nonneg(float v) {
+    return __builtin_bit_cast(float, wave_min_i32(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ float wave_max_nonneg(float v) {
+    return __builtin_bit_cast(float, wave_max_i32(__builtin_bit_cast(int, v)));
+}
+
+// Of any floats but NaN, through integers in their order.
+__device__ __forceinline__ int float_order(float v) {
+    const int b = __builtin_bit_cast(int, v);
+    return b ^ ((b >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float order_float(int o) {
+    return __builtin_bit_cast(float, o ^ ((o >> 31) & 0x7fffffff));
+}
+__device__ __forceinline__ float wave_min_ordered(float v) {
+    return order_float(wave_min_i32(float_order(v)));
+}
+__device__ __forceinline__ float wave_max_ordered(float v) {
+    return order_float(wave_max_i32(float_order(v)));
 }
 
 // Inclusive prefix sum across the wave: row shifts within the rows of 16

@@ -32,6 +32,7 @@
 // (float32) for the GICP plane regulariser; fused into both searches (one lane
 // per query in the group search, the whole wavefront in the other) and
 // standalone in k_cov.
+#include <climits>
 #include <cmath>
 #include <mutex>
 
@@ -91,7 +92,7 @@ struct WaveList {
         const unsigned long long b = lane + WAVE < n ? buf[lane + WAVE] : ~0ull;
         // (an absent entry's distance is a NaN: below nothing)
         const float da = __uint_as_float((uint32_t)(a >> 32)), db = __uint_as_float((uint32_t)(b >> 32));
-        float lo = 0.0f, up = wave_max_dpp(fmaxf(lane < n ? da : 0.0f, lane + WAVE < n ? db : 0.0f));
+        float lo = 0.0f, up = wave_max_nonneg(fmaxf(lane < n ? da : 0.0f, lane + WAVE < n ? db : 0.0f));
         int c_lo = 0, c_up = n;
         for (int it = 0; it < 6 && c_up > keep; ++it) {
             const float t = lo + (up - lo) * ((float)(k + SLACK_ENTRIES / 2 - c_lo) *
@@ -167,7 +168,7 @@ struct WaveNearest {
             i = ci;
         }
     }
-    __device__ __forceinline__ void tighten() { bound = fminf(bound, wave_min_dpp(d)); }
+    __device__ __forceinline__ void tighten() { bound = fminf(bound, wave_min_nonneg(d)); }
     __device__ __forceinline__ bool within(float d2) { return d2 > bound || ballot(d < d2) != 0; }
 };
 
@@ -1542,13 +1543,12 @@ __device__ __forceinline__ void group_body(const GroupArgs& a, int64_t group, co
                 }
             }
             {
-                const float fx = pend ? (float)cx : INF, fy = pend ? (float)cy : INF,
-                            fz = pend ? (float)cz : INF;
-                const float gx = pend ? (float)cx : -INF, gy = pend ? (float)cy : -INF,
-                            gz = pend ? (float)cz : -INF;
-                const int bx = ((int)wave_min_dpp(fx) + (int)wave_max_dpp(gx)) >> 1;
-                const int by = ((int)wave_min_dpp(fy) + (int)wave_max_dpp(gy)) >> 1;
-                const int bz = ((int)wave_min_dpp(fz) + (int)wave_max_dpp(gz)) >> 1;
+                const auto middle = [&](int c) {
+                    return (wave_min_i32(pend ? c : INT_MAX) + wave_max_i32(pend ? c : INT_MIN)) >> 1;
+                };
+                const int bx = middle(cx);
+                const int by = middle(cy);
+                const int bz = middle(cz);
                 const int c = __popcll(ballot(takes(bx, by, bz)));
                 if (c > best) {
                     ax = bx;
@@ -1563,9 +1563,9 @@ __device__ __forceinline__ void group_body(const GroupArgs& a, int64_t group, co
         const unsigned long long mm = ballot(member);
         pending &= ~mm;
         placed = placed || member;
-        const float bx0 = wave_min_dpp(member ? s.x : INF), bx1 = wave_max_dpp(member ? s.x : -INF);
-        const float by0 = wave_min_dpp(member ? s.y : INF), by1 = wave_max_dpp(member ? s.y : -INF);
-        const float bz0 = wave_min_dpp(member ? s.z : INF), bz1 = wave_max_dpp(member ? s.z : -INF);
+        const float bx0 = wave_min_ordered(member ? s.x : INF), bx1 = wave_max_ordered(member ? s.x : -INF);
+        const float by0 = wave_min_ordered(member ? s.y : INF), by1 = wave_max_ordered(member ? s.y : -INF);
+        const float bz0 = wave_min_ordered(member ? s.z : INF), bz1 = wave_max_ordered(member ? s.z : -INF);
         const float b0[3] = {bx0, by0, bz0}, b1[3] = {bx1, by1, bz1};
         int blo[3], bhi[3], lo[3], ext[3];
         int64_t total = 1;
@@ -2126,7 +2126,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         if (ONE) {
             WaveNearest L{a.sp.r2, INF, IDX_SENTINEL};
             if (search) knn_query_wave(T, a.views + tg, s, self, L);
-            const float d = wave_min_dpp(L.d);
+            const float d = wave_min_nonneg(L.d);
             const int32_t best = wave_min_i32(L.d == d ? L.i : IDX_SENTINEL);
             if (lane == 0) {
                 const bool have = best != IDX_SENTINEL;
