@@ -297,10 +297,10 @@ __global__ void __launch_bounds__(BT) k_make_keys(const float4* __restrict__ ori
         const uint32_t cx = (uint32_t)(cell_coord(p.x, inv_cell) - m.cmin[0]);
         const uint32_t cy = (uint32_t)(cell_coord(p.y, inv_cell) - m.cmin[1]);
         const uint32_t cz = (uint32_t)(cell_coord(p.z, inv_cell) - m.cmin[2]);
-        const unsigned long long sub =
-            morton3(sub_cell(p.x, inv_cell, sb), sub_cell(p.y, inv_cell, sb),
-                    sub_cell(p.z, inv_cell, sb));
-        keys[i] = (Key)((morton3(cx, cy, cz) << (3 * sb)) | sub);
+        // (the sub-cell's bits below the cell's: at most 21 in all)
+        keys[i] = (Key)morton3(cx << sb | sub_cell(p.x, inv_cell, sb),
+                               cy << sb | sub_cell(p.y, inv_cell, sb),
+                               cz << sb | sub_cell(p.z, inv_cell, sb));
         vals[i] = (uint32_t)i;
     }
 }

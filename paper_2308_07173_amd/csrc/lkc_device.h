@@ -152,6 +152,24 @@ __device__ __forceinline__ unsigned long long spread3(uint32_t v) {
     x = (x | x << 2) & 0x1249249249249249ull;
     return x;
 }
+// The same of at most 10 bits, in 32.
+__device__ __forceinline__ uint32_t spread3_10(uint32_t x) {
+    x = (x | x << 16) & 0x030000ffu;
+    x = (x | x << 8) & 0x0300f00fu;
+    x = (x | x << 4) & 0x030c30c3u;
+    x = (x | x << 2) & 0x09249249u;
+    return x;
+}
+// Bit i of at most 31 bits moved to bit 2 i.
+__device__ __forceinline__ unsigned long long spread2(uint32_t v) {
+    unsigned long long x = v;
+    x = (x | x << 16) & 0x0000ffff0000ffffull;
+    x = (x | x << 8) & 0x00ff00ff00ff00ffull;
+    x = (x | x << 4) & 0x0f0f0f0f0f0f0f0full;
+    x = (x | x << 2) & 0x3333333333333333ull;
+    x = (x | x << 1) & 0x5555555555555555ull;
+    return x;
+}
 __device__ __forceinline__ unsigned long long morton3(uint32_t x, uint32_t y, uint32_t z) {
     return spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
 }
