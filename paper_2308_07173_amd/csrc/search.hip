@@ -1325,7 +1325,7 @@ __device__ __forceinline__ void scan_run(const TargetView& T, int s0, int e0, bo
 // to a word).  Every lane's row lies in lines of its own, and a store takes a
 // cycle of the address unit for each line: word by word, the two rows of a
 // k = 20 query were 40 of the group search's 49 stores, and the address units
-// busy 66 % of the batched launch (3.76 M queries, 1.17 ms); in quads 41 %
+// busy 66 % of the batched launch (3.76 M queries, 1.19 ms); in quads 41 %
 // (1.07 ms), and the instructions issued bound it again.
 typedef uint32_t row4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -2048,7 +2048,7 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 //
 // Bound by the chain of dependent loads of each query (hash slots, points)
 // with few queries, by VALU issue with many (65,536 queries against a 2
-// M-point map: 800 VALU instructions each, 75 % of the issue slots, 0.12 ms).
+// M-point map: 0.109 ms; 0.125 before the plans were shared).
 // The list of 99,000 queries that the group search hands over in a batch of
 // 3.76 M takes 63 us (the wavefront search before it: 154).
 //
@@ -2557,21 +2557,23 @@ struct SearchJob {
 };
 
 // Whether the group search takes a launch of n queries.  The group search
-// needs the fewest instructions a query (130 VALU against 800, k = 20 on a
-// voxel map) but sorts the queries first and lasts as long as its slowest
+// needs the fewest instructions a query (130 VALU against some 700, k = 20 on
+// a voxel map) but sorts the queries first and lasts as long as its slowest
 // group; the wavefront search is one launch whose work is even.  Measured,
 // group against wavefront, whole call, k = 20, r = 2 m, 1 m cells:
-//   queries against a 2 M-point map   3,001 (500 k map)  172 /  18 us
-//                                     20,000             185 /  50 us
-//                                     65,536             214 / 127 us
-//                                     100,000            245 / 187 us
-//                                     131,072            250 / 242 us
-//     (k = 5 at 98,304 and 131,072: 178 / 147, 186 / 190 us; a sparse 100 k
-//     map at 100,000 and 131,072: 205 / 224, 208 / 286 us)
-//   a scan against itself (with its rebuild)  20,000     250 / 111 us
-//                                             117,965    386 / 321 us
-//   k = 32, 131,072 queries 391 / 272 us; scan of 117,965 501 / 353 us
-// so the line lies at 384 queries per CU (98,304), at 512 for self queries
+//   queries against a 2 M-point map   3,001 (500 k map)  161 /  16 us
+//                                     20,000             174 /  42 us
+//                                     65,536             203 / 109 us
+//                                     98,304             228 / 161 us
+//                                     131,072            236 / 208 us
+//     (k = 5 at 131,072: 177 / 155 us; a sparse 100 k map, before the
+//     wavefront search shared its plans: 205 / 224 us at 100,000, 208 / 286 at
+//     131,072)
+//   a scan against itself (with its rebuild)  20,000     238 /  99 us
+//                                             117,965    373 / 291 us
+//   k = 32, 131,072 queries 366 / 235 us; scan of 117,965 479 / 330 us
+// so the line lies at 384 queries per CU (98,304; between the dense map, which
+// would have it higher, and the sparse), at 512 for self queries
 // (sorted already, but dense: uneven groups), at 768 above k = 20, where a
 // group's lists leave room for two wavefronts per SIMD only.
 bool takes_group(const lkc_ctx* ctx, int K, int algorithm, bool self, int64_t n) {
