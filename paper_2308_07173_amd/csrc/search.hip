@@ -2050,7 +2050,7 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 // with few queries, by VALU issue with many (65,536 queries against a 2
 // M-point map: 0.109 ms; 0.125 before the plans were shared).
 // The list of 99,000 queries that the group search hands over in a batch of
-// 3.76 M takes 63 us (the wavefront search before it: 154).
+// 3.76 M takes 55 us (the wavefront search before it: 154).
 //
 // ONE: k = 1 without covariances (no list).
 template <int FUSED, bool ONE>
