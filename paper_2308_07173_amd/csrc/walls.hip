@@ -178,14 +178,19 @@ struct ClusterArgs {
     int32_t* par;
     UvMeta* m;
     int64_t n;
+    int64_t first;   // of the points that this launch takes
 };
+
+// Points of one launch of a pass over the pairs: a launch has fewer than 2^32
+// threads, and these passes take UNION_LANES a point.
+constexpr int64_t PAIR_SLICE = (int64_t)1 << 26;
 
 // Calls f(i, j) for this lane's pairs within eps (j < i); returns the lane's
 // point, -1 when there is none.
 template <typename F>
 __device__ __forceinline__ int32_t cluster_pairs(const ClusterArgs& a, F f) {
     const TargetView T = load_uniform(a.views);
-    const int64_t s = ((int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x) / UNION_LANES;
+    const int64_t s = a.first + ((int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x) / UNION_LANES;
     const int c = threadIdx.x % UNION_LANES;
     if (s >= T.n) return -1;
     const float4 p = gload(T.pts + s);
@@ -217,7 +222,7 @@ __global__ void __launch_bounds__(WT) k_cluster_seed(ClusterArgs a) {
         // (a rebuild that failed on the device left the grid empty: every
         // point its own root)
         const int64_t g = (int64_t)blockIdx.x * WT + threadIdx.x;
-        if (g < a.n) a.par[g] = (int32_t)g;
+        if (g < PAIR_SLICE && a.first + g < a.n) a.par[a.first + g] = (int32_t)(a.first + g);
         return;
     }
     int32_t least = INT32_MAX;
@@ -274,14 +279,20 @@ __global__ void __launch_bounds__(WT) k_cluster_union(ClusterArgs a) {
 
 // All passes: the parents of the grid's points, at most two or three joins
 // from their roots.
-void launch_cluster(hipStream_t st, const ClusterArgs& a) {
+void launch_cluster(hipStream_t st, ClusterArgs a) {
     const int64_t n = a.n;
-    const dim3 pairs(grid_of(n * UNION_LANES, WT)), points(grid_of(n, WT));
-    hipLaunchKernelGGL(k_cluster_seed, pairs, dim3(WT), 0, st, a);
+    const dim3 points(grid_of(n, WT));
+    const auto pairs = [&](void (*pass)(ClusterArgs)) {
+        for (a.first = 0; a.first < n; a.first += PAIR_SLICE) {
+            const int64_t here = std::min(PAIR_SLICE, n - a.first);
+            hipLaunchKernelGGL(pass, dim3(grid_of(here * UNION_LANES, WT)), dim3(WT), 0, st, a);
+        }
+    };
+    pairs(k_cluster_seed);
     hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
-    hipLaunchKernelGGL(k_cluster_hook, pairs, dim3(WT), 0, st, a);
+    pairs(k_cluster_hook);
     hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
-    hipLaunchKernelGGL(k_cluster_union, pairs, dim3(WT), 0, st, a);
+    pairs(k_cluster_union);
 }
 
 // Mask compaction in ascending order, in two launches: kept points per tile,
@@ -499,7 +510,7 @@ lkc_status euclid_cluster(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
                              "eps %g is too small for the cloud's extent (|p| up to %g)",
                              (double)eps, (double)grid.view.max_abs);
         hipLaunchKernelGGL(k_uv_init, dim3(1), dim3(64), 0, st, md);
-        launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, nullptr, par, md, m});
+        launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, nullptr, par, md, m, 0});
         hipLaunchKernelGGL(k_cluster_labels, dim3(grid_of(m, WT)), dim3(WT), 0, st, par, m,
                            cidx, labels, md, (const uint8_t*)nullptr,
                            (const TargetView*)grid.view_dev,
@@ -552,7 +563,7 @@ lkc_status euclid_cluster_async(lkc_ctx* ctx, const float* pts, int64_t n, float
     const int32_t* bst =
         grid.host_stale ? (const int32_t*)((const char*)grid.view_dev + view_status_offset())
                         : nullptr;
-    launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, mask, par, md, n});
+    launch_cluster(st, ClusterArgs{grid.view_dev, eps * eps, mask, par, md, n, 0});
     hipLaunchKernelGGL(k_cluster_labels, dim3(grid_of(n, WT)), dim3(WT), 0, st, par, n,
                        (const int32_t*)nullptr, labels, md, mask,
                        (const TargetView*)nullptr, (const int32_t*)nullptr);
