@@ -2884,6 +2884,8 @@ lkc_status launch_knn_self(lkc_ctx* ctx, const lkc_target* t, int32_t k, float r
     return run_search(ctx, j, cfg);
 }
 
+constexpr int64_t COV_SLICE = 1 << 23;   // workgroups of one k_cov launch
+
 lkc_status launch_cov(lkc_ctx* ctx, const lkc_target* t, const float* queries,
                       const int32_t* idx, const int32_t* count, int64_t q, int32_t k, float eps,
                       float* mean, float* cov, float* reg, uint8_t* valid, const CovWeight& wt) {
@@ -2893,15 +2895,21 @@ lkc_status launch_cov(lkc_ctx* ctx, const lkc_target* t, const float* queries,
     const bool weighted = wt.kind != LKC_WEIGHT_NONE;
     const int row = 4 * cov_stride(k, weighted);
     const int nq = 64 * row <= 36 * 1024 ? 64 : 32 * row <= 36 * 1024 ? 32 : 16;
-    const int64_t blocks = (q + nq - 1) / nq;
-    if (blocks > 0x7fffffff) return set_error(ctx, LKC_ERR_INVALID_ARG, "too many queries");
-    const CovPtrs co{mean, cov, reg, valid};
-    if (weighted)
-        hipLaunchKernelGGL(k_cov<true>, dim3((unsigned)blocks), dim3(256), (size_t)nq * row,
-                           ctx->stream, t->view, queries, idx, count, q, k, nq, eps, wt, co);
-    else
-        hipLaunchKernelGGL(k_cov<false>, dim3((unsigned)blocks), dim3(256), (size_t)nq * row,
-                           ctx->stream, t->view, queries, idx, count, q, k, nq, eps, wt, co);
+    if (q >= (int64_t)1 << 32) return set_error(ctx, LKC_ERR_INVALID_ARG, "too many queries");
+    // (a launch has fewer than 2^32 threads)
+    for (int64_t q0 = 0; q0 < q; q0 += COV_SLICE * nq) {
+        const int64_t here = std::min(COV_SLICE * nq, q - q0);
+        const dim3 grid((unsigned)((here + nq - 1) / nq));
+        const CovPtrs co{mean ? mean + 3 * q0 : nullptr, cov ? cov + 9 * q0 : nullptr,
+                         reg ? reg + 9 * q0 : nullptr, valid + q0};
+        const float* qs = queries ? queries + 3 * q0 : nullptr;
+        if (weighted)
+            hipLaunchKernelGGL(k_cov<true>, grid, dim3(256), (size_t)nq * row, ctx->stream, t->view,
+                               qs, idx + q0 * k, count + q0, here, k, nq, eps, wt, co);
+        else
+            hipLaunchKernelGGL(k_cov<false>, grid, dim3(256), (size_t)nq * row, ctx->stream, t->view,
+                               qs, idx + q0 * k, count + q0, here, k, nq, eps, wt, co);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(ctx, e, "covariance launch");
     return LKC_OK;

@@ -48,3 +48,23 @@ def test_clustering_of_more_than_2_27_points(lk):
         assert int(out["status"]) == 0 and int(out["n_clusters"]) == n - len(near)
         assert torch.equal(out["labels"], want)
         del out
+
+
+def test_covariances_of_more_than_2_30_lists(lk):
+    """256 threads for 64 lists would be 2^32 threads from 2^30 lists on."""
+    lkc, ctx = lk
+    p = torch.tensor([[0, 0, 0], [1, 0, 0], [0, 1, 0], [0, 0, 1]], dtype=torch.float32).cuda()
+    t = lkc.lkc_build_target(ctx, p, 1.0)
+    q = (1 << 30) + 131
+    idx = torch.tensor([[0, 1, 2]], dtype=torch.int32, device="cuda").repeat(q, 1)
+    cnt = torch.full((q,), 3, dtype=torch.int32, device="cuda")
+    few = [0, 63, 64, (1 << 30) - 1, 1 << 30, (1 << 30) + 63, q - 1]
+    cnt[few] = 2
+    out = dict(mean=None, cov=None, reg=None,
+               valid=torch.full((q,), 7, dtype=torch.uint8, device="cuda"))
+    lkc.lkc_covariances(ctx, t, idx, cnt, plane_eps=1e-3, out=out)
+    torch.cuda.synchronize()
+    assert not out["valid"][few].any()
+    out["valid"][few] = 1
+    assert bool((out["valid"] == 1).all())
+    t.free()
