@@ -2625,8 +2625,9 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     a.fb_list = sc.fb_list;
     a.fb_count = sc.words;
     a.counters = nullptr;
-    a.prof = (!fixed && group && ctx->prof_buf && (j.n_slots + WAVE - 1) / WAVE <= ctx->prof_groups)
+    a.prof = (!fixed && ctx->prof_buf && (j.n_slots + WAVE - 1) / WAVE <= ctx->prof_groups)
                  ? (uint32_t*)ctx->prof_buf : nullptr;
+    // (cleared before every search, also one that no group takes part in)
     if (a.prof)
         LKC_HIP_TRY(ctx, hipMemsetAsync(a.prof, 0,
                                         sizeof(uint32_t) * PROF_WORDS *
