@@ -185,6 +185,8 @@ lkc_status lkc_autotune(lkc_ctx* ctx, const float* target_points, int64_t n,
         float wave_ms = -1.0f;
         for (int32_t f = 0; f < n_cfgs; ++f) {
             const bool wave = !lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&cfgs[f]));
+            s = lkc::check_query_keys(ctx, buf.target, k, lkc::resolve_cfg(&cfgs[f]));
+            if (s != LKC_OK) return s;
             lkc_launch_cfg run = cfgs[f];
             run.algorithm = wave ? 2 : 1;
             const int32_t runs = wave && wave_ms >= 0.0f ? -1 : reps;

@@ -2556,6 +2556,39 @@ struct SearchJob {
     const RigidF* move;   // k = 1 without covariances, wavefront search: moves the queries
 };
 
+// The layout of the queries' sort keys against n targets.
+struct QueryKeyBits {
+    int w[3];       // bits of each axis's clamped cell coordinate
+    int sub_bits;   // Morton bits per axis of the sub-cell
+    int tshift;     // bits below the target index
+    int tbits;      // bits of the target index
+};
+
+// LKC_ERR_UNSUPPORTED where the keys have too few bits for the targets' boxes:
+// of a search that may sort its queries, for every number of them, so that it
+// does not depend on that number whether a target can be searched.
+lkc_status query_key_bits(lkc_ctx* ctx, const TargetView* views, int n, QueryKeyBits& kb) {
+    kb.w[0] = kb.w[1] = kb.w[2] = 1;
+    for (int t = 0; t < n; ++t) {
+        const TargetView& V = views[t];
+        for (int d = 0; d < 3; ++d)
+            kb.w[d] = std::max(kb.w[d], bitw((uint32_t)(std::max(V.cmax[d] - V.cmin[d], 0) + 2)));
+    }
+    const int wsum = kb.w[0] + kb.w[1] + kb.w[2];
+    // Morton key of the (clamped) query cell, then of its sub-cell (as
+    // many sub-cell bits, from 2 to 4 per axis, as the fewest 8-bit sort
+    // passes holding the key with 2 of them allow)
+    kb.tbits = n > 1 ? bitw((uint32_t)(n - 1)) : 0;
+    const int sub_lo = std::max(0, std::min(2, (63 - kb.tbits - wsum) / 3));
+    const int room = std::min(63, 8 * ((kb.tbits + wsum + 3 * sub_lo + 7) / 8)) - kb.tbits;
+    kb.sub_bits = std::max(sub_lo, std::min(4, (room - wsum) / 3));
+    kb.tshift = wsum + 3 * kb.sub_bits;
+    if (kb.tshift + kb.tbits > 63)
+        return set_error(ctx, LKC_ERR_UNSUPPORTED, "query sort key needs %d bits",
+                         kb.tshift + kb.tbits);
+    return LKC_OK;
+}
+
 // Whether the group search takes a launch of n queries.  The group search
 // needs the fewest instructions a query (130 VALU against some 700, k = 20 on
 // a voxel map) but sorts the queries first and lasts as long as its slowest
@@ -2576,8 +2609,10 @@ struct SearchJob {
 // would have it higher, and the sparse), at 512 for self queries
 // (sorted already, but dense: uneven groups), at 768 above k = 20, where a
 // group's lists leave room for two wavefronts per SIMD only.
+bool may_group(int K, int algorithm) { return K > 0 && algorithm != 2; }
+
 bool takes_group(const lkc_ctx* ctx, int K, int algorithm, bool self, int64_t n) {
-    if (K == 0 || algorithm == 2) return false;
+    if (!may_group(K, algorithm)) return false;
     if (algorithm == 1) return true;
     const int per_cu = K > 20 ? 768 : self ? 512 : 384;
     return n > (int64_t)ctx->num_cus * per_cu;
@@ -2642,31 +2677,18 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     // Separate queries get keys: the group search sorts them by cell, and a
     // batch over several targets carries each query's target in the key's
     // top bits (the wavefront-per-query search reads it unsorted).
-    int tshift = 0, tbits = 0;
+    QueryKeyBits kb{};
+    if (j.queries && (keyed || may_group(K, cfg.algorithm))) {
+        s = query_key_bits(ctx, j.host_views, j.n_targets, kb);
+        if (s != LKC_OK) return s;
+    }
+    const int tshift = kb.tshift, tbits = kb.tbits;
     bool words32 = false;
     if (keyed) {
-        int w[3] = {1, 1, 1};
-        for (int t = 0; t < j.n_targets; ++t) {
-            const TargetView& V = j.host_views[t];
-            for (int d = 0; d < 3; ++d)
-                w[d] = std::max(w[d], bitw((uint32_t)(std::max(V.cmax[d] - V.cmin[d], 0) + 2)));
-        }
-        const int wsum = w[0] + w[1] + w[2];
-        // Morton key of the (clamped) query cell, then of its sub-cell (as
-        // many sub-cell bits, from 2 to 4 per axis, as the fewest 8-bit sort
-        // passes holding the key with 2 of them allow)
-        tbits = j.n_targets > 1 ? bitw((uint32_t)(j.n_targets - 1)) : 0;
-        const int sub_lo = std::max(0, std::min(2, (63 - tbits - wsum) / 3));
-        const int room = std::min(63, 8 * ((tbits + wsum + 3 * sub_lo + 7) / 8)) - tbits;
-        const int sub_bits = std::max(sub_lo, std::min(4, (room - wsum) / 3));
-        tshift = wsum + 3 * sub_bits;
-        if (tshift + tbits > 63)
-            return set_error(ctx, LKC_ERR_UNSUPPORTED, "query sort key needs %d bits",
-                             tshift + tbits);
         // (one target: every scan's target is 0, no lookup)
         QueryKeyArgs qa{j.queries, j.n_slots, j.views_dev, j.n_targets > 1 ? j.scans_dev : nullptr,
                         j.hdr_dev, tshift,
-                        sub_bits, {w[0], w[1], w[2]}, sc.ka, sc.va, group ? sc.words : nullptr};
+                        kb.sub_bits, {kb.w[0], kb.w[1], kb.w[2]}, sc.ka, sc.va, group ? sc.words : nullptr};
         // (the sorted keys are read again only for the targets of several)
         words32 = group && j.n_targets == 1 && tshift <= 32;
         const dim3 kgrid((unsigned)((j.n_slots + 255) / 256));
@@ -2807,6 +2829,11 @@ LaunchCfg resolve_cfg(const lkc_launch_cfg* c) {
 
 bool knn_takes_group(const lkc_ctx* ctx, int32_t k, int64_t q, const LaunchCfg& cfg) {
     return takes_group(ctx, choose_k_tile(k), cfg.algorithm, false, q);
+}
+
+lkc_status check_query_keys(lkc_ctx* ctx, const lkc_target* t, int32_t k, const LaunchCfg& cfg) {
+    QueryKeyBits kb;
+    return may_group(choose_k_tile(k), cfg.algorithm) ? query_key_bits(ctx, &t->view, 1, kb) : LKC_OK;
 }
 
 lkc_status launch_knn(lkc_ctx* ctx, const lkc_target* t, const float* queries, int64_t q,
