@@ -70,7 +70,7 @@ struct BuildMeta {
     int key_bits;           // bits of the sort key
     int passes;             // 8-bit sort passes the key needs
     int hash_bits;          // log2 of the hash capacity (2^bits >= 2 x cells, >= 64)
-    uint32_t pad;
+    int fresh_passes;       // passes of a layout not fitted to an earlier build's
 };
 static_assert(sizeof(BuildMeta) == 64, "BuildMeta layout");
 
@@ -170,17 +170,16 @@ __device__ void meta_combine(const MetaPart* __restrict__ parts, int64_t np, Bui
                 bits[a] = e ? 32 - __clz((int)e) : 0;
                 wmax = max(wmax, bits[a]);
             }
-        int sub, passes;
+        const int sub_lo = max(0, min(2, (63 - 3 * wmax) / 3));
+        int room = min(63, 8 * ((3 * wmax + 3 * sub_lo + 7) / 8));
+        int sub = max(sub_lo, min(4, (room - 3 * wmax) / 3));
+        int passes = (3 * wmax + 3 * sub + 7) / 8;
+        meta->fresh_passes = passes;
         if (fixed_passes > 0) {
-            const int room = min(63, 8 * fixed_passes);
+            room = min(63, 8 * fixed_passes);
             if (3 * wmax > room) vb |= BAD_PASSES;
             sub = max(0, min(4, (room - 3 * wmax) / 3));
             passes = fixed_passes;
-        } else {
-            const int sub_lo = max(0, min(2, (63 - 3 * wmax) / 3));
-            const int room = min(63, 8 * ((3 * wmax + 3 * sub_lo + 7) / 8));
-            sub = max(sub_lo, min(4, (room - 3 * wmax) / 3));
-            passes = (3 * wmax + 3 * sub + 7) / 8;
         }
         meta->nonfinite = vb;
         meta->sh_y = bits[0];
@@ -779,7 +778,7 @@ __global__ void k_hash_clear(HashSlot* __restrict__ h, const BuildMeta* __restri
 
 // The view a build leaves on the device: `base` (pointers, n, cell) with
 // the fields derived on the device; a failed build leaves an empty view.
-// status: {lkc_status, key bits, BAD_* bits}.
+// status: {lkc_status, key bits, BAD_* bits, passes of a fresh layout}.
 __device__ void write_view(const BuildMeta* __restrict__ meta, const TargetView& base,
                            TargetView* __restrict__ out, int32_t* __restrict__ status) {
     TargetView v = base;
@@ -802,6 +801,7 @@ __device__ void write_view(const BuildMeta* __restrict__ meta, const TargetView&
                                       : (int32_t)LKC_OK;
     status[1] = meta->key_bits;
     status[2] = bad;
+    status[3] = meta->fresh_passes;
 }
 
 __global__ void __launch_bounds__(BT) k_hash_insert(const unsigned long long* __restrict__ tkeys,

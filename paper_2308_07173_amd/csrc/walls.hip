@@ -44,7 +44,8 @@ struct UvMeta {      // 64 bytes, at offset 192 of the context's metadata words
     uint32_t spins;  // union-find retries that hit the limit
     uint32_t n_clusters;
     uint32_t kept;   // points selected by the clustering mask
-    uint32_t pad[8];
+    int32_t passes;  // sort passes of the grid, laid out afresh
+    uint32_t pad[7];
 };
 static_assert(sizeof(UvMeta) == 64, "UvMeta layout");
 
@@ -381,7 +382,7 @@ __device__ __forceinline__ int32_t cluster_grid_status(const TargetView* views,
 // a mask, compacted point c labels its original index cidx[c] with the
 // original index of its root (compaction keeps the order, so that is the
 // smallest original index of the component).  With build_status, the grid's
-// status goes into m->bad.
+// status goes into m->bad and its passes into m->passes.
 __global__ void __launch_bounds__(WT) k_cluster_labels(int32_t* __restrict__ par, int64_t n,
                                                        const int32_t* __restrict__ cidx,
                                                        int32_t* __restrict__ label,
@@ -392,7 +393,10 @@ __global__ void __launch_bounds__(WT) k_cluster_labels(int32_t* __restrict__ par
     const int64_t i = (int64_t)blockIdx.x * WT + threadIdx.x;
     if (build_status) {
         const int32_t bad = cluster_grid_status(views, build_status);
-        if (i == 0) m->bad = (uint32_t)bad;
+        if (i == 0) {
+            m->bad = (uint32_t)bad;
+            m->passes = build_status[3];
+        }
         if (bad != (int32_t)LKC_OK) return;   // (the call does it over or fails)
     }
     bool root = false;
@@ -521,6 +525,9 @@ lkc_status euclid_cluster(lkc_ctx* ctx, const float* pts, int64_t n, float eps,
         LKC_HIP_TRY(ctx, hipMemcpyAsync(mh, md, sizeof(UvMeta), hipMemcpyDeviceToHost, st));
         LKC_HIP_TRY(ctx, hipStreamSynchronize(st));
         if (on_device && mh->bad && attempt == 0) continue;
+        // (the next build, with or without a wait, finds the passes of this
+        // cloud, as after a build with a wait, not those of an earlier one)
+        if (on_device) grid.sort_passes = mh->passes;
         if (mh->spins)
             return set_error(ctx, LKC_ERR_HIP, "%u union-find joins exceeded the retry limit",
                              mh->spins);
