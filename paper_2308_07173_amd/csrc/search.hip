@@ -159,6 +159,7 @@ struct WaveList {
 
 // The nearest candidate alone (k = 1): each lane keeps its own best.
 struct WaveNearest {
+    static constexpr int k = 1;
     float bound;               // (uniform)
     float d;
     int32_t i;
@@ -526,6 +527,63 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
         }
         if (sweep || L.within(block_clear2(T.cell, q, cq, R, margin))) return;
     }
+}
+
+// Bounds the k-th distance by the farthest corners of the runs' boxes: ceil(k /
+// 16) whole runs hold k points.  (In the operations of dist2, each of them
+// monotonic: no point of a run is farther than its box's corner, rounding
+// included.)
+template <typename List>
+__device__ __forceinline__ void bound_by_runs(const TargetView& T, const WaveQuery& q, List& L) {
+    const int whole = (int)(T.n / BOX_PTS);
+    float far = INF;   // of this lane's runs the nearest
+#pragma unroll 1
+    for (int r = lane_id(); r < whole; r += WAVE) {
+        const float4 lo = gload(T.boxes + 2 * r);
+        const float4 hi = gload(T.boxes + 2 * r + 1);
+        far = fminf(far, dist2(0.0f, 0.0f, 0.0f, fmaxf(fabsf(lo.x - q.x), fabsf(hi.x - q.x)),
+                               fmaxf(fabsf(lo.y - q.y), fabsf(hi.y - q.y)),
+                               fmaxf(fabsf(lo.z - q.z), fabsf(hi.z - q.z))));
+    }
+    float b = INF;
+#pragma unroll 1
+    for (int held = 0; held < L.k; held += BOX_PTS) {
+        b = wave_min_nonneg(far);
+        const unsigned long long at = ballot(far == b);
+        if (lane_id() == __builtin_ffsll((long long)at) - 1) far = INF;
+    }
+    L.bound = fminf(L.bound, b);
+}
+
+// The same from all points at once, through their 16-point runs (the own chunk
+// of a self query first), for targets of up to RUNS_MAX_N points.  Such a
+// target's rings may be many and nearly empty: how many depends on where the
+// queries lie, which the host does not know, and this is four batches of boxes
+// at most.  40,000 queries, k = 5, no radius, ring by ring and so:
+//   2,048 points 12 m apart                                  2,176 / 57 us
+//   a sweep thinned to 4,096, queries beside it, 8 m off   337 / 54, 728 / 89
+//   4,096 points of a cube, 4 a cell                            54 / 67
+//   6,000 (thinned sweep, cube)                          371 / 61, 55 / 72
+// Up to RUN_SCAN_MIN points are streamed without the boxes.
+constexpr int64_t RUNS_MAX_N = 4096;
+
+template <typename List>
+__device__ __forceinline__ void knn_query_runs(const TargetView& T, const WavePlan& w, bool self,
+                                               List& L) {
+    const int lane = lane_id(), n = (int)T.n;
+    const WaveQuery sp{w.x, w.y, w.z, self ? w.tgc : -1};
+    if (n <= RUN_SCAN_MIN) {
+        scan_one(T, sp, 0, n, L);
+        return;
+    }
+    if (self) {
+        const int p = sp.skip * WAVE + lane;
+        const float4 t = gload(T.pts + p);   // (64 spare records)
+        L.add(p < n, dist2(w.x, w.y, w.z, t.x, t.y, t.z), __float_as_int(t.w));
+        L.tighten();
+    }
+    bound_by_runs(T, sp, L);
+    scan_runs(T, sp, lane == 0, 0, n, 0.0f, L);
 }
 
 // ------------------------------------------------------------- covariance --
@@ -2052,8 +2110,8 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 // The list of 99,000 queries that the group search hands over in a batch of
 // 3.76 M takes 55 us (the wavefront search before it: 154).
 //
-// ONE: k = 1 without covariances (no list).
-template <int FUSED, bool ONE>
+// ONE: k = 1 without covariances (no list).  RUNS: knn_query_runs answers.
+template <int FUSED, bool ONE, bool RUNS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
     extern __shared__ unsigned long long s_wave[];
     const int lane = lane_id();
@@ -2125,7 +2183,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
         const bool search = s.rmax >= 0;
         if (ONE) {
             WaveNearest L{a.sp.r2, INF, IDX_SENTINEL};
-            if (search) knn_query_wave(T, a.views + tg, s, self, L);
+            if (search) {
+                if (RUNS) knn_query_runs(T, s, self, L);
+                else knn_query_wave(T, a.views + tg, s, self, L);
+            }
             const float d = wave_min_nonneg(L.d);
             const int32_t best = wave_min_i32(L.d == d ? L.i : IDX_SENTINEL);
             if (lane == 0) {
@@ -2137,7 +2198,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
             continue;
         }
         WaveList L{buf, a.sp.r2, 0, k, false};
-        if (search) knn_query_wave(T, a.views + tg, s, self, L);
+        if (search) {
+            if (RUNS) knn_query_runs(T, s, self, L);
+            else knn_query_wave(T, a.views + tg, s, self, L);
+        }
         // each entry's place among the k smallest, by counting
         wave_lds_fence();
         const unsigned long long my = lane < L.n ? buf[lane] : ~0ull;
@@ -2625,7 +2689,15 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     if (j.n_slots == 0) return LKC_OK;
     hipStream_t st = ctx->stream;
     const int K = choose_k_tile(j.k);
-    const bool group = takes_group(ctx, K, cfg.algorithm, j.queries == nullptr, j.n_slots);
+    bool few = false, many = false, rings = false;
+    for (int t = 0; t < j.n_targets; ++t) {
+        (j.host_views[t].n <= RUNS_MAX_N ? few : many) = true;
+        rings = rings || !(j.radius <= 2.0f * j.host_views[t].cell);
+    }
+    // (a batch over both kinds of target whose rings may be many: the group
+    // search streams the small ones whole, the rings of a wavefront would not end)
+    const bool group = takes_group(ctx, K, cfg.algorithm, j.queries == nullptr, j.n_slots) ||
+                       (few && many && rings && may_group(K, cfg.algorithm));
     const bool keyed = j.queries && (group || j.n_targets > 1);
     // (the wavefront search of one target needs no scratch)
     Scratch sc{};
@@ -2768,14 +2840,12 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     const dim3 wgrid(((unsigned)std::min<int64_t>(full, need) + 7) & ~7u);
     a.cov_slots = wave_slots(j.k, j.fused);
     const size_t lds = 4 * wave_lds_bytes(j.k, a.cov_slots, j.fused);
-    if (j.fused == 2)
-        hipLaunchKernelGGL((k_wave<2, false>), wgrid, dim3(256), lds, st, a);
-    else if (j.fused == 1)
-        hipLaunchKernelGGL((k_wave<1, false>), wgrid, dim3(256), lds, st, a);
-    else if (j.k == 1)
-        hipLaunchKernelGGL((k_wave<0, true>), wgrid, dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_wave<0, false>), wgrid, dim3(256), lds, st, a);
+    const bool runs = !many;
+    void (*wave)(GroupArgs) = j.fused == 2   ? (runs ? k_wave<2, false, true> : k_wave<2, false, false>)
+                              : j.fused == 1 ? (runs ? k_wave<1, false, true> : k_wave<1, false, false>)
+                              : j.k == 1     ? (runs ? k_wave<0, true, true> : k_wave<0, true, false>)
+                                             : (runs ? k_wave<0, false, true> : k_wave<0, false, false>);
+    hipLaunchKernelGGL(wave, wgrid, dim3(256), j.fused == 0 && j.k == 1 ? 0 : lds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(ctx, e, "search launch");
     if (ctx->timing) LKC_HIP_TRY(ctx, hipEventRecord(ctx->ev[3], st));
