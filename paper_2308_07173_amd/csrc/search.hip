@@ -75,8 +75,17 @@ __device__ __forceinline__ void wave_lds_fence() {
 // exceed: on the surfaces a LiDAR sees the counts grow about linearly with
 // d2, so interpolating between two counts finds it in two or three ballots
 // (a search over the distance's bits takes about twenty).
+//
+// LIM: entries that stay between cuts, 64, or 128 for k > WIDE_K, whose cuts
+// would otherwise have no room between k and LIM: nearly every batch then cut
+// the list, to one entry exactly (k = 64, a self search of 100,000 points in
+// one cell: 38.7 ms, with 128 6.8).
+constexpr int WIDE_K = 56;
+
+template <int LIM>
 struct WaveList {
-    static constexpr int CAP = 2 * WAVE;   // entries (LDS keys)
+    static constexpr int CAP = LIM + WAVE;   // entries (LDS keys)
+    static constexpr int REGS = CAP / WAVE;
     static constexpr int SLACK_ENTRIES = 8;
     unsigned long long* buf;
     float bound;               // (uniform) farther candidates are not among the k nearest
@@ -84,20 +93,36 @@ struct WaveList {
     int k;
     bool dirty;                // (uniform) entries since the last cut
 
-    __device__ __forceinline__ void cut_back() {
+    // Cuts the list back to about k + SLACK_ENTRIES, at most `most`, entries.
+    template <int R>
+    __device__ __forceinline__ void cut(int most) {
         const int lane = lane_id();
-        const int keep = min(k + SLACK_ENTRIES, WAVE);
+        // (k <= WIDE_K with LIM = 64: no entry too many)
+        const int keep = LIM == WAVE ? k + SLACK_ENTRIES : min(k + SLACK_ENTRIES, most);
+        const int aim = LIM == WAVE ? k + SLACK_ENTRIES / 2 : min(k + SLACK_ENTRIES / 2, keep);
         wave_lds_fence();
-        const unsigned long long a = lane < n ? buf[lane] : ~0ull;
-        const unsigned long long b = lane + WAVE < n ? buf[lane + WAVE] : ~0ull;
-        // (an absent entry's distance is a NaN: below nothing)
-        const float da = __uint_as_float((uint32_t)(a >> 32)), db = __uint_as_float((uint32_t)(b >> 32));
-        float lo = 0.0f, up = wave_max_nonneg(fmaxf(lane < n ? da : 0.0f, lane + WAVE < n ? db : 0.0f));
+        unsigned long long e[R];
+        float d[R], far = 0.0f;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool have = lane + r * WAVE < n;
+            e[r] = have ? buf[lane + r * WAVE] : ~0ull;
+            // (an absent entry's distance is a NaN: below nothing)
+            d[r] = __uint_as_float((uint32_t)(e[r] >> 32));
+            far = fmaxf(far, have ? d[r] : 0.0f);
+        }
+        const auto within_d = [&](float t) {
+            int c = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) c += __popcll(ballot(d[r] <= t));
+            return c;
+        };
+        float lo = 0.0f, up = wave_max_nonneg(far);
         int c_lo = 0, c_up = n;
         for (int it = 0; it < 6 && c_up > keep; ++it) {
-            const float t = lo + (up - lo) * ((float)(k + SLACK_ENTRIES / 2 - c_lo) *
-                                              __builtin_amdgcn_rcpf((float)(c_up - c_lo)));
-            const int c = __popcll(ballot(da <= t)) + __popcll(ballot(db <= t));
+            const float t =
+                lo + (up - lo) * ((float)(aim - c_lo) * __builtin_amdgcn_rcpf((float)(c_up - c_lo)));
+            const int c = within_d(t);
             if (c >= k) {
                 up = t;
                 c_up = c;
@@ -106,13 +131,17 @@ struct WaveList {
                 c_lo = c;
             }
         }
-        unsigned long long ma = ballot(da <= up), mb = ballot(db <= up);
-        if (c_up > WAVE) {
+        unsigned long long m[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) m[r] = ballot(d[r] <= up);
+        if (c_up > most) {
             // many equal distances: tell the keys apart bit by bit
             unsigned long long ul = 0, uu = ~0ull >> 1;
-            for (int bit = 62; bit >= 0 && c_up > WAVE; --bit) {
+            for (int bit = 62; bit >= 0 && c_up > most; --bit) {
                 const unsigned long long t = ul | ((1ull << bit) - 1ull);
-                const int c = __popcll(ballot(a <= t)) + __popcll(ballot(b <= t));
+                int c = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) c += __popcll(ballot(e[r] <= t));
                 if (c >= k) {
                     uu = t;
                     c_up = c;
@@ -120,18 +149,22 @@ struct WaveList {
                     ul |= 1ull << bit;
                 }
             }
-            ma = ballot(a <= uu);
-            mb = ballot(b <= uu);
+#pragma unroll
+            for (int r = 0; r < R; ++r) m[r] = ballot(e[r] <= uu);
         }
         if (c_up < n) {
-            if ((ma >> lane) & 1ull) buf[lanes_below(ma)] = a;
-            if ((mb >> lane) & 1ull) buf[__popcll(ma) + lanes_below(mb)] = b;
+            int at = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if ((m[r] >> lane) & 1ull) buf[at + lanes_below(m[r])] = e[r];
+                at += __popcll(m[r]);
+            }
         }
         n = c_up;
         bound = fminf(bound, up);
         dirty = false;
     }
-    // Takes the lanes' candidates; at most 64 entries stay.
+    // Takes the lanes' candidates; at most LIM entries stay.
     __device__ __forceinline__ void add(bool valid, float d, int32_t i) {
         const bool pass = valid && d <= bound;
         const unsigned long long m = ballot(pass);
@@ -140,11 +173,15 @@ struct WaveList {
             buf[n + lanes_below(m)] = ((unsigned long long)__float_as_uint(d) << 32) | (uint32_t)i;
         n += __popcll(m);
         dirty = true;
-        if (n > WAVE) cut_back();
+        if (n > LIM) cut<REGS>(LIM);
     }
     // Tightens the bound once the list holds k entries.
     __device__ __forceinline__ void tighten() {
-        if (dirty && n >= k) cut_back();
+        if (dirty && n >= k) cut<(LIM == WAVE ? REGS : REGS - 1)>(LIM);
+    }
+    // At most a wavefront's entries.
+    __device__ __forceinline__ void finish() {
+        if (LIM > WAVE && n > WAVE) cut<REGS - 1>(WAVE);
     }
     // Whether k candidates are nearer than d2, or the radius is.
     __device__ __forceinline__ bool within(float d2) {
@@ -152,8 +189,14 @@ struct WaveList {
         if (n < k) return false;
         wave_lds_fence();
         const int lane = lane_id();
-        const float d = __uint_as_float(lane < n ? (uint32_t)(buf[lane] >> 32) : ~0u);
-        return __popcll(ballot(d < d2)) >= k;
+        int c = 0;
+#pragma unroll
+        for (int r = 0; r < LIM / WAVE; ++r) {
+            const float d = __uint_as_float(
+                lane + r * WAVE < n ? (uint32_t)(buf[lane + r * WAVE] >> 32) : ~0u);
+            c += __popcll(ballot(d < d2));
+        }
+        return c >= k;
     }
 };
 
@@ -2028,13 +2071,17 @@ __host__ __device__ constexpr int row_words(int fused) { return fused == 2 ? 4 :
 // more it is five, and the 65k-point match took 152 us instead of 125).
 constexpr int WAVE_SLOTS = 32, WAVE_ROW_BYTES = 5300;
 
+// (the room of a longer list is taken from the rows)
+__host__ __device__ inline int wave_list_bytes(int k) {
+    return 8 * (k > WIDE_K ? WaveList<2 * WAVE>::CAP : WaveList<WAVE>::CAP);
+}
 __host__ __device__ inline int wave_slots(int k, int fused) {
-    const int fit = WAVE_ROW_BYTES / (4 * k * row_words(fused) + (int)sizeof(WaveSlot));
+    const int fit = (WAVE_ROW_BYTES + wave_list_bytes(1) - wave_list_bytes(k)) / (4 * k * row_words(fused) + (int)sizeof(WaveSlot));
     return fit < WAVE_SLOTS ? fit : WAVE_SLOTS;
 }
 __host__ __device__ inline size_t wave_lds_bytes(int k, int slots, int fused) {
     const size_t rows = fused ? (size_t)slots * (4 * k * row_words(fused) + sizeof(WaveSlot)) : 0;
-    return WAVE_PLANS * sizeof(WavePlan) + (size_t)WaveList::CAP * 8 + ((rows + 15) & ~(size_t)15);
+    return WAVE_PLANS * sizeof(WavePlan) + (size_t)wave_list_bytes(k) + ((rows + 15) & ~(size_t)15);
 }
 
 // Gathers the points of a wavefront's kept rows; offsets and weights in place
@@ -2110,19 +2157,22 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 // The list of 99,000 queries that the group search hands over in a batch of
 // 3.76 M takes 55 us (the wavefront search before it: 154).
 //
-// ONE: k = 1 without covariances (no list).  RUNS: knn_query_runs answers.
-template <int FUSED, bool ONE, bool RUNS>
+// LIST: the entries its lists keep, 64 or 128; 1: k = 1 without covariances, no
+// list.  RUNS: knn_query_runs answers.
+template <int FUSED, int LIST, bool RUNS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
     extern __shared__ unsigned long long s_wave[];
     const int lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int k = a.sp.k;
+    constexpr bool ONE = LIST == 1;
+    using List = WaveList<ONE ? WAVE : LIST>;
     constexpr int RW = row_words(FUSED);
     __shared__ WavePlan s_one[ONE ? 4 * WAVE_PLANS : 1];
     const size_t per_wave = wave_lds_bytes(k, a.cov_slots, FUSED);
     const auto plans_of = [&](int w) { return (WavePlan*)((char*)s_wave + w * per_wave); };
     const auto list_of = [&](int w) { return (unsigned long long*)(plans_of(w) + WAVE_PLANS); };
-    const auto slots_of = [&](int w) { return (WaveSlot*)(list_of(w) + WaveList::CAP); };
+    const auto slots_of = [&](int w) { return (WaveSlot*)(list_of(w) + List::CAP); };
     const auto rows_of = [&](int w) { return (float*)(slots_of(w) + a.cov_slots); };   // [slot][k][RW]
     WavePlan* plans = ONE ? s_one + wid * WAVE_PLANS : plans_of(wid);
     unsigned long long* buf = list_of(wid);
@@ -2197,12 +2247,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
             }
             continue;
         }
-        WaveList L{buf, a.sp.r2, 0, k, false};
+        List L{buf, a.sp.r2, 0, k, false};
         if (search) {
             if (RUNS) knn_query_runs(T, s, self, L);
             else knn_query_wave(T, a.views + tg, s, self, L);
         }
         // each entry's place among the k smallest, by counting
+        L.finish();
         wave_lds_fence();
         const unsigned long long my = lane < L.n ? buf[lane] : ~0ull;
         buf[lane] = my;
@@ -2841,10 +2892,16 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     a.cov_slots = wave_slots(j.k, j.fused);
     const size_t lds = 4 * wave_lds_bytes(j.k, a.cov_slots, j.fused);
     const bool runs = !many;
-    void (*wave)(GroupArgs) = j.fused == 2   ? (runs ? k_wave<2, false, true> : k_wave<2, false, false>)
-                              : j.fused == 1 ? (runs ? k_wave<1, false, true> : k_wave<1, false, false>)
-                              : j.k == 1     ? (runs ? k_wave<0, true, true> : k_wave<0, true, false>)
-                                             : (runs ? k_wave<0, false, true> : k_wave<0, false, false>);
+    const auto pick = [&](void (*cells)(GroupArgs), void (*all)(GroupArgs)) { return runs ? all : cells; };
+    const bool wide = j.k > WIDE_K;
+    void (*wave)(GroupArgs) =
+        j.fused == 2   ? (wide ? pick(k_wave<2, 128, false>, k_wave<2, 128, true>)
+                               : pick(k_wave<2, 64, false>, k_wave<2, 64, true>))
+        : j.fused == 1 ? (wide ? pick(k_wave<1, 128, false>, k_wave<1, 128, true>)
+                               : pick(k_wave<1, 64, false>, k_wave<1, 64, true>))
+        : j.k == 1     ? pick(k_wave<0, 1, false>, k_wave<0, 1, true>)
+        : wide         ? pick(k_wave<0, 128, false>, k_wave<0, 128, true>)
+                       : pick(k_wave<0, 64, false>, k_wave<0, 64, true>);
     hipLaunchKernelGGL(wave, wgrid, dim3(256), j.fused == 0 && j.k == 1 ? 0 : lds, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(ctx, e, "search launch");
