@@ -2451,7 +2451,9 @@ __global__ void __launch_bounds__(256) k_cov(TargetView T, const float* __restri
     __syncthreads();
     const uint32_t* nb = (const uint32_t*)idx + q0 * k;
     const int last = (int)min(T.n, (int64_t)0x7fffffff) - 1;
-    if (last >= 0) {
+    if (last < 0) {
+        if (tid < here) s_n[tid] = 0;
+    } else if (ballot(lane_id() < here && s_n[lane_id()] > 0)) {   // (not for empty lists alone)
         for (int t0 = tid; t0 < total; t0 += 4 * 256) {
             int v[4];
             float4 p[4];
@@ -2473,8 +2475,6 @@ __global__ void __launch_bounds__(256) k_cov(TargetView T, const float* __restri
                 }
             }
         }
-    } else if (tid < here) {
-        s_n[tid] = 0;
     }
     __syncthreads();
     if (!queries) {
