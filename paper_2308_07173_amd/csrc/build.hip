@@ -17,7 +17,7 @@
 //   4. reorder       points into that order as float4 (x, y, z, original idx),
 //                    and the bounding box of every aligned 16-point run
 //   5. cell runs     run boundaries of the cell part of the key
-//                    (up to RANK_MAX points: 3-5 by counting, in two launches)
+//                    (few points: 3-5 by counting, in two launches)
 //   6. hash insert   open addressing, linear probing, capacity 2^ceil(log2 2C);
 //                    the hash key is the row-major compact cell key
 //
@@ -44,10 +44,15 @@ constexpr int RS_TILE = BT * RS_ITEMS;
 constexpr int RADIX = 256;
 constexpr unsigned KEY_BLOCKS = 2048;  // workgroups of k_make_keys, which each combine the parts
 constexpr int SCAN_TILE = 4096;  // entries per workgroup of the multi-block scan
-// Targets of up to this many points are sorted by counting.  A rebuild of 2,048
-// points takes 29 us so and 42 by radix passes, 4,096 31 and 50, 8,192 40 and
-// 53, 12,000 54 and 55, 16,384 57 and 58; the work grows with the square.
-constexpr int RANK_MAX = 8192;
+// Targets of up to this many points are sorted by counting, whose work grows
+// with the square; fewer where the key is a single radix pass.  A rebuild by
+// passes and by counting, us (keys of one, two and four passes):
+//   2,048   22 / 20   28 / 20   46 / 28
+//   4,096   24 / 24   34 / 24   58 / 31
+//   6,000   24 / 28   35 / 28   58 / 34
+//   8,192   25 / 32   35 / 32   61 / 40
+// 12,000 points of four passes took 55 by counting as by passes, 16,384 57 / 58.
+constexpr int RANK_MAX = 8192, RANK_MAX_ONE_PASS = 4096;
 constexpr int RAW_OFFSET_TILES = 96;  // sorts of up to this many tiles skip the scan launch
 constexpr int RAW_RUN_BLOCKS = 2048;  // cell-run numbering of up to this many blocks skips it too
 
@@ -1132,7 +1137,7 @@ lkc_status build_into(lkc_ctx* ctx, lkc_target* t, const float* points, int64_t 
         hipLaunchKernelGGL(k_make_keys<Key>, dim3(std::min(grid_for(n, BT), KEY_BLOCKS)), dim3(BT), 0,
                            st, orig, n, inv_cell, (const MetaPart*)mparts, np, fixed, meta, ka, va,
                            hash, cap_max);
-        if (n <= RANK_MAX) {
+        if (n <= (passes == 1 ? RANK_MAX_ONE_PASS : RANK_MAX)) {
             // ---- 3.-5. by counting
             hipLaunchKernelGGL(k_rank<Key>, dim3((unsigned)((n + WAVE - 1) / WAVE)), dim3(1024), 0,
                                st, orig, (const Key*)ka, (int)n, pts, kb);
