@@ -15,11 +15,11 @@
 // points closer than eps (d2 <= eps^2, float32, the search's fma order).
 // The points are bucketed in a grid of 1.25 eps cells (built with the target
 // build, so every pair within eps lies in adjacent cells even after float32
-// rounding of the cell coordinates); the points of the 27 surrounding cells
-// with a smaller original index are tested twice: first for the smallest of
-// them, which becomes the point's parent, then to join the two trees of every
-// pair in a lock-free union-find (the larger root is hooked under the smaller
-// with a compare-and-swap, parent reads bypass the per-CU cache).
+// rounding of the cell coordinates).  Passes over the points and, of the 27
+// surrounding cells, those with a smaller original index: the first makes the
+// smallest of them a point's parent, the last joins the two trees of every pair
+// in a lock-free union-find (the larger root is hooked under the smaller with a
+// compare-and-swap, parent reads bypass the per-CU cache).
 // Roots are therefore the smallest index of their component; a final pass
 // writes every point's root as its label.
 #include <algorithm>
@@ -166,12 +166,9 @@ __device__ __forceinline__ void uf_union(int32_t* par, int32_t a, int32_t b, UvM
     atomicAdd(&m->spins, 1u);
 }
 
-// Both passes over the pairs take 32 lanes per reordered point, one to each of
-// the 27 surrounding cells, and test the points of that cell with a smaller
-// original index.  With `mask` (the grid then holds every point, indexed by
-// original index) only kept points join.
-constexpr int UNION_LANES = 32;
-
+// The passes over the pairs test every point against the points of its 27
+// surrounding cells with a smaller original index.  With `mask` (the grid then
+// holds every point, indexed by original index) only kept points join.
 struct ClusterArgs {
     const TargetView* views;
     float e2;
@@ -179,58 +176,160 @@ struct ClusterArgs {
     int32_t* par;
     UvMeta* m;
     int64_t n;
-    int64_t first;   // of the points that this launch takes
+    int chunk;   // reordered points of a wavefront, 2 to 64
 };
 
-// Points of one launch of a pass over the pairs: a launch has fewer than 2^32
-// threads, and these passes take UNION_LANES a point.
-constexpr int64_t PAIR_SLICE = (int64_t)1 << 26;
+// From CLUSTER_MANY points on the chip is full without two points a wavefront,
+// and the steps count.  Wavefronts that are at least half active, with fewer
+// than CLUSTER_SPARSE points a cell, then give each lane a point, whose cells
+// in the box it goes through by itself (unmasked, 1 M points of a map, eps 0.5:
+// 1.48 -> 1.10 ms; a fifth of them kept: 0.61 -> 0.78, so not there).
+constexpr int64_t CLUSTER_MANY = 1 << 19;
+constexpr int CLUSTER_SPARSE = 4;
 
-// Calls f(i, j) for this lane's pairs within eps (j < i); returns the lane's
-// point, -1 when there is none.
-template <typename F>
-__device__ __forceinline__ int32_t cluster_pairs(const ClusterArgs& a, F f) {
-    const TargetView T = load_uniform(a.views);
-    const int64_t s = a.first + ((int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x) / UNION_LANES;
-    const int c = threadIdx.x % UNION_LANES;
-    if (s >= T.n) return -1;
-    const float4 p = gload(T.pts + s);
-    const int32_t i = __float_as_int(p.w);
-    const int dz = (c * 57) >> 9, r = c - 9 * dz, dy = (r * 11) >> 5;   // c / 9, r / 3
-    const int x = cell_coord(p.x, T.inv_cell) + r - 3 * dy - 1;
-    const int y = cell_coord(p.y, T.inv_cell) + dy - 1;
-    const int z = cell_coord(p.z, T.inv_cell) + dz - 1;
-    uint32_t st, cn;
-    if (c < 27 && !(a.mask && !a.mask[i]) && x >= T.cmin[0] && x <= T.cmax[0] &&
-        y >= T.cmin[1] && y <= T.cmax[1] && z >= T.cmin[2] && z <= T.cmax[2] &&
-        hash_find(T, pack_key(T, x, y, z), st, cn)) {
-        for (uint32_t t = st; t < st + cn; ++t) {
-            const float4 q = gload(T.pts + t);
-            const int32_t j = __float_as_int(q.w);
-            if (j < i && (!a.mask || a.mask[j]) &&
-                dist2(p.x, p.y, p.z, q.x, q.y, q.z) <= a.e2)
-                f(i, j);
-        }
+// A volume filled evenly with hardly more points than cells has few pairs and
+// short trees: one pass of joins by itself (1 M points, 0.8 a cell: 0.74 ms,
+// seeded first 0.88).  (A line or a sheet of as many has long ones.)
+__device__ __forceinline__ bool cluster_one_pass(const ClusterArgs& a, const TargetView& T) {
+    if (a.n <= CLUSTER_MANY || a.mask || 4 * T.n >= 7 * (int64_t)T.n_cells) return false;
+    int64_t box = 1;
+    for (int d = 0; d < 3; ++d) {
+        const int ext = T.cmax[d] - T.cmin[d] + 1;
+        if (ext < 3 || box > 4 * (int64_t)T.n_cells) return false;
+        box *= ext;
     }
-    return i;
+    return box <= 4 * (int64_t)T.n_cells;
+}
+
+// Calls f(half, i, j) for the pairs (j < i) within eps of the wavefront's
+// points, done(i, have) after every two of them (own(i) where a lane took its
+// own).  A wavefront looks at its `chunk` points a lane each and takes those
+// that have anything to do two at a time, one to each half of it; a lane probes
+// one of the 27 cells.  Then every lane walks its own cell, or, where that is
+// fewer steps (long cells, a few beside empty ones), all lanes walk one cell
+// after another (118,000 points of a sweep, eps 1: a lane a cell 11.8 ms, so
+// 1.8; a thread a point, in one pass of joins, 8.3).  SEEDED: past the
+// first pass, points that are their own parent have no such pair (only a point
+// without one ever was), and nothing to do.
+template <bool SEEDED, typename F, typename Done, typename Own>
+__device__ __forceinline__ void cluster_pairs(const ClusterArgs& a, F f, Done done, Own own) {
+    const TargetView T = load_uniform(a.views);
+    const int lane = lane_id(), half = lane / 32, c = lane % 32;
+    const int64_t wave = ((int64_t)xcd_tile(blockIdx.x, gridDim.x) * WT + threadIdx.x) / WAVE;
+    const bool two = a.chunk == 2;   // every lane loads its half's point at once
+    const int64_t s = wave * a.chunk + (two ? half : lane);
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    bool active = false;
+    if ((two || lane < a.chunk) && s < T.n) {
+        p = gload(T.pts + s);
+        const int32_t i = __float_as_int(p.w);
+        active = SEEDED && !cluster_one_pass(a, T) ? a.par[i] != i : !a.mask || a.mask[i];
+        if (!SEEDED && !active) a.par[i] = i;
+    }
+    unsigned long long todo = ballot(active);
+    if (a.chunk == WAVE && T.n < CLUSTER_SPARSE * (int64_t)T.n_cells && __popcll(todo) >= WAVE / 2) {
+        if (active) {
+            const int32_t i = __float_as_int(p.w);
+            const int cx = cell_coord(p.x, T.inv_cell), cy = cell_coord(p.y, T.inv_cell),
+                      cz = cell_coord(p.z, T.inv_cell);
+            for (int z = max(cz - 1, T.cmin[2]); z <= min(cz + 1, T.cmax[2]); ++z)
+                for (int y = max(cy - 1, T.cmin[1]); y <= min(cy + 1, T.cmax[1]); ++y)
+                    for (int x = max(cx - 1, T.cmin[0]); x <= min(cx + 1, T.cmax[0]); ++x) {
+                        uint32_t st, cn;
+                        if (!hash_find(T, pack_key(T, x, y, z), st, cn)) continue;
+                        for (uint32_t t = st; t < st + cn; ++t) {
+                            const float4 q = gload(T.pts + t);
+                            const int32_t j = __float_as_int(q.w);
+                            if (j < i && dist2(p.x, p.y, p.z, q.x, q.y, q.z) <= a.e2 &&
+                                (!a.mask || a.mask[j]))
+                                f(0, i, j);
+                        }
+                    }
+            own(i);
+        }
+        return;
+    }
+    const int dz = (c * 57) >> 9, r = c - 9 * dz, dy = (r * 11) >> 5;   // c / 9, r / 3
+    while (todo) {
+        float px = p.x, py = p.y, pz = p.z, pw = p.w;
+        bool have = active;
+        if (two) {
+            todo = 0;
+        } else {
+            const int m0 = __builtin_ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int m1 = todo ? __builtin_ffsll((long long)todo) - 1 : -1;
+            if (todo) todo &= todo - 1;
+            const int m = half ? m1 : m0;
+            have = m >= 0;
+            px = shfl(p.x, m & 63);
+            py = shfl(p.y, m & 63);
+            pz = shfl(p.z, m & 63);
+            pw = shfl(p.w, m & 63);
+        }
+        const int32_t i = __float_as_int(pw);
+        const int x = cell_coord(px, T.inv_cell) + r - 3 * dy - 1;
+        const int y = cell_coord(py, T.inv_cell) + dy - 1;
+        const int z = cell_coord(pz, T.inv_cell) + dz - 1;
+        uint32_t st = 0, cn = 0;
+        if (!have || c >= 27 || x < T.cmin[0] || x > T.cmax[0] || y < T.cmin[1] || y > T.cmax[1] ||
+            z < T.cmin[2] || z > T.cmax[2] || !hash_find(T, pack_key(T, x, y, z), st, cn))
+            cn = 0;
+        const int longest = wave_max_i32((int)cn);
+        const int steps = readlane(wave_incl_scan((int)((cn + WAVE - 1) / WAVE)), WAVE - 1);
+        if (longest <= steps) {
+            for (uint32_t t = st; t < st + cn; ++t) {
+                const float4 q = gload(T.pts + t);
+                const int32_t j = __float_as_int(q.w);
+                if (j < i && dist2(px, py, pz, q.x, q.y, q.z) <= a.e2 && (!a.mask || a.mask[j]))
+                    f(half, i, j);
+            }
+        } else {
+            unsigned long long cells = ballot(cn > 0);
+            while (cells) {
+                const int l = __builtin_ffsll((long long)cells) - 1;
+                cells &= cells - 1;
+                const float ux = readlane(px, l), uy = readlane(py, l), uz = readlane(pz, l);
+                const int32_t ui = readlane(i, l);
+                const int b = readlane((int)st, l), e = b + readlane((int)cn, l);
+                for (int t = b + lane; t < e; t += WAVE) {
+                    const float4 q = gload(T.pts + t);
+                    const int32_t j = __float_as_int(q.w);
+                    if (j < ui && dist2(ux, uy, uz, q.x, q.y, q.z) <= a.e2 &&
+                        (!a.mask || a.mask[j]))
+                        f(l / 32, ui, j);
+                }
+            }
+        }
+        done(i, have);
+    }
 }
 
 // First pass: every point's parent is the smallest of its neighbours (or
 // itself).  No two threads write the same word, so nothing contends, and most
 // of the pairs are then in one tree already.
 __global__ void __launch_bounds__(WT) k_cluster_seed(ClusterArgs a) {
-    if (load_uniform(a.views).n == 0) {
+    const TargetView T = load_uniform(a.views);
+    if (T.n == 0 || cluster_one_pass(a, T)) {
         // (a rebuild that failed on the device left the grid empty: every
         // point its own root)
         const int64_t g = (int64_t)blockIdx.x * WT + threadIdx.x;
-        if (g < PAIR_SLICE && a.first + g < a.n) a.par[a.first + g] = (int32_t)(a.first + g);
+        if (g < a.n) a.par[g] = (int32_t)g;
         return;
     }
-    int32_t least = INT32_MAX;
-    const int32_t i = cluster_pairs(a, [&](int32_t, int32_t j) { least = min(least, j); });
-#pragma unroll
-    for (int h = UNION_LANES / 2; h > 0; h >>= 1) least = min(least, __shfl_xor(least, h));
-    if (i >= 0 && threadIdx.x % UNION_LANES == 0) a.par[i] = min(least, i);
+    int32_t least[2] = {INT32_MAX, INT32_MAX};
+    cluster_pairs<false>(
+        a,
+        [&](int half, int32_t, int32_t j) {
+            least[0] = min(least[0], half ? INT32_MAX : j);
+            least[1] = min(least[1], half ? j : INT32_MAX);
+        },
+        [&](int32_t i, bool have) {
+            const int32_t l0 = wave_min_i32(least[0]), l1 = wave_min_i32(least[1]);
+            if (have && lane_id() % 32 == 0) a.par[i] = min(lane_id() ? l1 : l0, i);
+            least[0] = least[1] = INT32_MAX;
+        },
+        [&](int32_t i) { a.par[i] = min(least[0], i); });
 }
 
 // Points every node at its root: each thread takes its node's grandparent for
@@ -254,11 +353,14 @@ __global__ void __launch_bounds__(WT) k_cluster_flatten(int32_t* __restrict__ pa
 // minimum: nothing is retried, and a root that another pair already gave a
 // smaller one is left alone).
 __global__ void __launch_bounds__(WT) k_cluster_hook(ClusterArgs a) {
-    cluster_pairs(a, [&](int32_t i, int32_t j) {
-        const int32_t u = a.par[i], v = a.par[j];
-        const int32_t hi = max(u, v), lo = min(u, v);
-        if (lo != hi && a.par[hi] > lo) atomicMin(a.par + hi, lo);
-    });
+    cluster_pairs<true>(
+        a,
+        [&](int, int32_t i, int32_t j) {
+            const int32_t u = a.par[i], v = a.par[j];
+            const int32_t hi = max(u, v), lo = min(u, v);
+            if (lo != hi && a.par[hi] > lo) atomicMin(a.par + hi, lo);
+        },
+        [](int32_t, bool) {}, [](int32_t) {});
 }
 
 // Last pass: joins the trees of every pair that are still two.  Two nodes that
@@ -273,27 +375,35 @@ __global__ void __launch_bounds__(WT) k_cluster_hook(ClusterArgs a) {
 // the test of the parents, 85; with a hook before the joins 54 (10
 // seed, 5 + 5 flatten, 13 hook, 21 joins).
 __global__ void __launch_bounds__(WT) k_cluster_union(ClusterArgs a) {
-    cluster_pairs(a, [&](int32_t i, int32_t j) {
-        if (a.par[i] != a.par[j]) uf_union(a.par, i, j, a.m);
-    });
+    cluster_pairs<true>(
+        a,
+        [&](int, int32_t i, int32_t j) {
+            if (a.par[i] != a.par[j]) uf_union(a.par, i, j, a.m);
+        },
+        [](int32_t, bool) {}, [](int32_t) {});
 }
 
 // All passes: the parents of the grid's points, at most two or three joins
 // from their roots.
 void launch_cluster(hipStream_t st, ClusterArgs a) {
     const int64_t n = a.n;
-    const dim3 points(grid_of(n, WT));
-    const auto pairs = [&](void (*pass)(ClusterArgs)) {
-        for (a.first = 0; a.first < n; a.first += PAIR_SLICE) {
-            const int64_t here = std::min(PAIR_SLICE, n - a.first);
-            hipLaunchKernelGGL(pass, dim3(grid_of(here * UNION_LANES, WT)), dim3(WT), 0, st, a);
-        }
-    };
-    pairs(k_cluster_seed);
+    // Two points a wavefront where that leaves the chip room (32,768 wavefronts
+    // are four times what it holds), more of more points: those with nothing
+    // to do are then passed over by the dozen.
+    a.chunk = 2;
+    while (a.chunk < WAVE / 2 && n / a.chunk > 32768) a.chunk *= 2;
+    if (n > CLUSTER_MANY && (!a.mask || n / a.chunk > 65536)) a.chunk = WAVE;
+    const dim3 points(grid_of(n, WT)), pairs(grid_of((n + a.chunk - 1) / a.chunk, WT / WAVE));
+    hipLaunchKernelGGL(k_cluster_seed, pairs, dim3(WT), 0, st, a);
     hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
-    pairs(k_cluster_hook);
-    hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
-    pairs(k_cluster_union);
+    // (a third pass over the pairs pays while the joins are bound by latency:
+    // 300,000 points of a map, eps 0.3, 420 us with the hooks and 470 without;
+    // a million, eps 0.5, 1.67 and 1.48 ms)
+    if (n <= CLUSTER_MANY) {
+        hipLaunchKernelGGL(k_cluster_hook, pairs, dim3(WT), 0, st, a);
+        hipLaunchKernelGGL(k_cluster_flatten, points, dim3(WT), 0, st, a.par, n, a.mask);
+    }
+    hipLaunchKernelGGL(k_cluster_union, pairs, dim3(WT), 0, st, a);
 }
 
 // Mask compaction in ascending order, in two launches: kept points per tile,
