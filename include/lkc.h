@@ -95,8 +95,10 @@ typedef enum lkc_status {
  *                   Auto takes 2 above k = 32 and for launches too small to
  *                   fill the device with groups (up to 384 queries per
  *                   compute unit, 512 of a target against itself, 768 above
- *                   k = 20), else 1; any of the group options below, given,
- *                   asks for 1.  Both give bit-identical results.
+ *                   k = 20; fewer where the target has hardly more points
+ *                   than cells, and for k = 1 of a target against itself),
+ *                   else 1; any of the group options below, given, asks for
+ *                   1.  Both give bit-identical results.
  *  group_reach      cells the group search looks beyond its queries' cells
  *                   (0 = auto: ceil(radius / cell) clamped to [1, 2]; 1..4)
  *  waves_per_block  wavefronts per workgroup (0 = 2; 1..4)
@@ -131,7 +133,8 @@ typedef struct lkc_target_info {
     int32_t cell_min[3];     /* occupied cell bounding box (integer cell coords) */
     int32_t cell_max[3];
     int32_t key_bits;        /* bits of the compact cell key */
-    int32_t sort_passes;     /* 8-bit radix passes the build ran */
+    int32_t sort_passes;     /* 8-bit radix passes of the key (few points are
+                                sorted by counting instead) */
     float cell_size;
     int64_t device_bytes;    /* device memory the target holds */
 } lkc_target_info;

@@ -173,18 +173,19 @@ lkc_status lkc_autotune(lkc_ctx* ctx, const float* target_points, int64_t n,
     float best = INFINITY;
     std::vector<float> t(reps);
     const lkc_launch_cfg by_rule{0, 0, 0, 0, 0, 0};
-    // (unless it is all there is to choose from)
-    bool skip_wave = ms_q < q && lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&by_rule));
-    bool any_group = false;
-    for (int32_t f = 0; f < n_cfgs; ++f)
-        any_group |= lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&cfgs[f]));
-    skip_wave = skip_wave && any_group;
     for (int32_t c = 0; c < n_cells; ++c) {
         s = lkc_build_target(ctx, target_points, n, cells[c], &buf.target);
         if (s != LKC_OK) return s;
+        const auto group_at = [&](const lkc_launch_cfg& cfg) {
+            return lkc::knn_takes_group(ctx, buf.target, k, q, lkc::resolve_cfg(&cfg));
+        };
+        // (unless it is all there is to choose from)
+        bool any_group = false;
+        for (int32_t f = 0; f < n_cfgs; ++f) any_group |= group_at(cfgs[f]);
+        const bool skip_wave = ms_q < q && any_group && group_at(by_rule);
         float wave_ms = -1.0f;
         for (int32_t f = 0; f < n_cfgs; ++f) {
-            const bool wave = !lkc::knn_takes_group(ctx, k, q, lkc::resolve_cfg(&cfgs[f]));
+            const bool wave = !group_at(cfgs[f]);
             s = lkc::check_query_keys(ctx, buf.target, k, lkc::resolve_cfg(&cfgs[f]));
             if (s != LKC_OK) return s;
             lkc_launch_cfg run = cfgs[f];

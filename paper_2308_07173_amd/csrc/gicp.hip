@@ -286,7 +286,7 @@ lkc_status launch_gicp_linearize(lkc_ctx* ctx, const lkc_target* t, const float*
             for (int c = 0; c < 3; ++c) X.r[3 * r + c] = (float)T[4 * r + c];
             X.t[r] = (float)T[4 * r + 3];
         }
-        if (knn_takes_group(ctx, 1, n, cfg)) {
+        if (knn_takes_group(ctx, t, 1, n, cfg)) {
             hipLaunchKernelGGL(k_gicp_transform, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                                st, src, n, X, g.queries);
             s = launch_knn(ctx, t, g.queries, n, 1, max_dist, cidx, g.d2, g.count, cfg);

@@ -222,7 +222,8 @@ lkc_status launch_knn(lkc_ctx* ctx, const lkc_target* t, const float* queries, i
                       const LaunchCfg& cfg, const RigidF* move = nullptr);
 // Refuses what a search of external queries under cfg refuses (their sort keys).
 lkc_status check_query_keys(lkc_ctx* ctx, const lkc_target* t, int32_t k, const LaunchCfg& cfg);
-bool knn_takes_group(const lkc_ctx* ctx, int32_t k, int64_t q, const LaunchCfg& cfg);
+bool knn_takes_group(const lkc_ctx* ctx, const lkc_target* t, int32_t k, int64_t q,
+                     const LaunchCfg& cfg);
 lkc_status launch_knn_self(lkc_ctx* ctx, const lkc_target* t, int32_t k, float radius,
                            float eps, int32_t* idx, float* d2, int32_t* count, float* mean,
                            float* cov, float* reg, uint8_t* valid, const LaunchCfg& cfg);

@@ -2705,31 +2705,49 @@ lkc_status query_key_bits(lkc_ctx* ctx, const TargetView* views, int n, QueryKey
 }
 
 // Whether the group search takes a launch of n queries.  The group search
-// needs the fewest instructions a query (130 VALU against some 700, k = 20 on
+// needs the fewest instructions a query (130 VALU against some 500, k = 20 on
 // a voxel map) but sorts the queries first and lasts as long as its slowest
 // group; the wavefront search is one launch whose work is even.  Measured,
-// group against wavefront, whole call, k = 20, r = 2 m, 1 m cells:
-//   queries against a 2 M-point map   3,001 (500 k map)  161 /  16 us
-//                                     20,000             174 /  42 us
-//                                     65,536             203 / 109 us
-//                                     98,304             228 / 161 us
-//                                     131,072            236 / 208 us
-//     (k = 5 at 131,072: 177 / 155 us; a sparse 100 k map, before the
-//     wavefront search shared its plans: 205 / 224 us at 100,000, 208 / 286 at
-//     131,072)
-//   a scan against itself (with its rebuild)  20,000     238 /  99 us
-//                                             117,965    373 / 291 us
-//   k = 32, 131,072 queries 366 / 235 us; scan of 117,965 479 / 330 us
-// so the line lies at 384 queries per CU (98,304; between the dense map, which
-// would have it higher, and the sparse), at 512 for self queries
-// (sorted already, but dense: uneven groups), at 768 above k = 20, where a
-// group's lists leave room for two wavefronts per SIMD only.
+// group / wavefront, us of the whole call, r = 2 m, 1 m cells:
+//   queries against a map of 2 M points (5.3 a cell)      k = 20    k = 5     k = 32
+//                                       20,000       152 / 38  114 / 31  192 / 41
+//                                       65,536       197 / 101 147 / 79  347 / 112
+//                                       98,304       232 / 149 169 / 117 327 / 175
+//                                      131,072       251 / 200 183 / 155 367 / 224
+//                                      196,608       294 / 291 228 / 226 401 / 335
+//   against one of 100 k (2.2 a cell)
+//                                       65,536       169 / 128 128 / 81  272 / 145
+//                                       98,304       180 / 185 137 / 116 259 / 225
+//                                      131,072       197 / 254 149 / 152 300 / 295
+//                                      163,840       212 / 313 174 / 188 277 / 364
+//     (0.8 m cells, 1.8 a cell, 98,304: 201 / 252, k = 10 175 / 187)
+//   a sweep against itself              60,000       191 / 105           354 / 127
+//                                      117,965       341 / 227 196 / 161 439 / 285
+//                                      131,072       310 / 234 291 / 189 412 / 281
+//                                      163,840       324 / 301           430 / 373
+//   the same with k = 1                 65,536        57 / 70
+// So the line lies at 384 queries per CU (98,304), 320 against targets of fewer
+// than 1.8 points a cell; at 512 for self queries (sorted already, but of uneven
+// density), 128 for their k = 1 (the own chunk answers it); above k = 20, where a
+// group's lists leave room for two wavefronts a SIMD only, at 768, and 512
+// against targets of fewer than 2.5 points a cell.  Against dense targets it is
+// on the safe side.  (A volume of 30 points a cell against itself, 131,072, k =
+// 5: 179 / 190.)
 bool may_group(int K, int algorithm) { return K > 0 && algorithm != 2; }
 
-bool takes_group(const lkc_ctx* ctx, int K, int algorithm, bool self, int64_t n) {
+bool takes_group(const lkc_ctx* ctx, int k, int algorithm, bool self, int64_t n,
+                 const TargetView* views, int n_targets) {
+    const int K = choose_k_tile(k);
     if (!may_group(K, algorithm)) return false;
     if (algorithm == 1) return true;
-    const int per_cu = K > 20 ? 768 : self ? 512 : 384;
+    int64_t points = 0, cells = 0;
+    for (int t = 0; t < n_targets; ++t) {
+        points += views[t].n;
+        cells += views[t].n_cells;
+    }
+    const int per_cu = self     ? (K > 20 ? 768 : k == 1 ? 128 : 512)
+                       : K > 20 ? (2 * points < 5 * cells ? 512 : 768)
+                                : (10 * points < 18 * cells ? 320 : 384);
     return n > (int64_t)ctx->num_cus * per_cu;
 }
 
@@ -2747,7 +2765,8 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     }
     // (a batch over both kinds of target whose rings may be many: the group
     // search streams the small ones whole, the rings of a wavefront would not end)
-    const bool group = takes_group(ctx, K, cfg.algorithm, j.queries == nullptr, j.n_slots) ||
+    const bool group = takes_group(ctx, j.k, cfg.algorithm, j.queries == nullptr, j.n_slots,
+                                   j.host_views, j.n_targets) ||
                        (few && many && rings && may_group(K, cfg.algorithm));
     const bool keyed = j.queries && (group || j.n_targets > 1);
     // (the wavefront search of one target needs no scratch)
@@ -2954,8 +2973,9 @@ LaunchCfg resolve_cfg(const lkc_launch_cfg* c) {
     return r;
 }
 
-bool knn_takes_group(const lkc_ctx* ctx, int32_t k, int64_t q, const LaunchCfg& cfg) {
-    return takes_group(ctx, choose_k_tile(k), cfg.algorithm, false, q);
+bool knn_takes_group(const lkc_ctx* ctx, const lkc_target* t, int32_t k, int64_t q,
+                     const LaunchCfg& cfg) {
+    return takes_group(ctx, k, cfg.algorithm, false, q, &t->view, 1);
 }
 
 lkc_status check_query_keys(lkc_ctx* ctx, const lkc_target* t, int32_t k, const LaunchCfg& cfg) {
