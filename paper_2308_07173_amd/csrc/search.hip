@@ -2142,14 +2142,19 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 
 // Wavefront-per-query search of the slots in `a.fb_list` (those the group
 // search handed over; their number is only known on the device), or of every
-// slot when there is no list.  Persistent: each XCD takes one contiguous part
-// (its L2 then holds that part of the target) and its wavefronts stride over
-// it.  The rows of up to a.cov_slots queries of a wavefront are kept in LDS;
-// at the end (or when they are full) their points are gathered and their
-// offsets and weights taken with every lane, and the sums and eigenvectors
-// follow for all queries of the workgroup, one lane per query.  (When every
-// wavefront took the sums of its own rows, exponents and weights included,
-// 30,000 queries with Laplacian weights took 94 us; this takes 68.)
+// slot when there is no list.  Persistent: the XCDs take chunks of consecutive
+// slots in turn (1 / 256 to 1 / 128 of all), whose part of the target their L2
+// then holds, and an XCD's wavefronts stride over its chunks.  So a stretch of
+// slots that cost far more than others, as in a list that is in cell order,
+// falls to all XCDs (with one contiguous eighth each, 130,000 queries without a
+// radius, k = 20, of 16,000 map points took 4,218 us; so 1,519).
+//
+// The rows of up to a.cov_slots queries of a wavefront are kept in LDS; at the
+// end (or when they are full) their points are gathered and their offsets and
+// weights taken with every lane, and the sums and eigenvectors follow for all
+// queries of the workgroup, one lane per query.  (When every wavefront took the
+// sums of its own rows, exponents and weights included, 30,000 queries with
+// Laplacian weights took 94 us; this took 68.)
 //
 // Bound by the chain of dependent loads of each query (hash slots, points)
 // with few queries, by VALU issue with many (65,536 queries against a 2
@@ -2183,20 +2188,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     const int64_t n = a.fb_list ? (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(
                                       (int)*(volatile uint32_t*)a.fb_count)
                                 : a.n_slots;
-    const int x = blockIdx.x % 8, nx = gridDim.x / 8;   // (the grid is a multiple of 8)
-    const int64_t hi = n * (x + 1) / 8, step = (int64_t)nx * (blockDim.x / WAVE);
-    int64_t i = n * x / 8 + (int64_t)(blockIdx.x / 8) * (blockDim.x / WAVE) + wid;
+    // this XCD's slots: of every 8 chunks of 2^sh one, and an eighth of the rest
+    // (the grid is a multiple of 8)
+    const int x = blockIdx.x % 8, sh = max(2, 56 - __builtin_clzll((unsigned long long)(n | 128)));
+    const int64_t dealt = n >> (sh + 3) << sh, rest = n - 8 * dealt, first = 8 * dealt + rest * x / 8;
+    const int64_t mine = dealt + rest * (x + 1) / 8 - rest * x / 8;
+    const auto query_at = [&](int64_t p) {
+        return p < dealt ? ((p >> sh) << (sh + 3)) + ((int64_t)x << sh) + (p & (((int64_t)1 << sh) - 1))
+                         : first + p - dealt;
+    };
+    const int64_t step = (int64_t)(gridDim.x / 8) * (blockDim.x / WAVE);
+    int64_t p = (int64_t)(blockIdx.x / 8) * (blockDim.x / WAVE) + wid;
     int ns = 0;   // kept rows
     const bool self = a.queries == nullptr;
     const float radius = sqrtf(a.sp.r2);
     int b = WAVE_PLANS;   // the current query's plan
 #pragma unroll 1
-    for (; i < hi; i += step) {
+    for (; p < mine; p += step) {
         if (++b >= WAVE_PLANS) {
             b = 0;
             wave_lds_fence();
-            const int64_t li = i + (int64_t)lane * step;
-            if (lane < WAVE_PLANS && li < hi) {
+            const int64_t lp = p + (int64_t)lane * step, li = query_at(lp);
+            if (lane < WAVE_PLANS && lp < mine) {
                 const int64_t slot = a.fb_list ? (int64_t)gload(a.fb_list + li) : li;
                 const int tg = a.skeys ? (int)(a.skeys[slot] >> a.tshift) : 0;
                 const TargetView& V = a.views[tg];
@@ -2280,7 +2293,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
             if (in) rows[(ns * k + rank) * RW] = __uint_as_float((uint32_t)my);
             if (lane == 0)
                 slots[ns] = WaveSlot{s.x, s.y, s.z, cnt, s.qi, {tg}};
-            if (++ns == a.cov_slots && i + step < hi) {
+            if (++ns == a.cov_slots && p + step < mine) {
                 wave_rows<FUSED>(a, k, ns, slots, rows);
                 if (lane < ns) wave_cov<FUSED>(a, slots[lane], rows + lane * k * RW);
                 ns = 0;
