@@ -599,16 +599,17 @@ __device__ __forceinline__ void bound_by_runs(const TargetView& T, const WaveQue
 }
 
 // The same from all points at once, through their 16-point runs (the own chunk
-// of a self query first), for targets of up to RUNS_MAX_N points.  Such a
-// target's rings may be many and nearly empty: how many depends on where the
-// queries lie, which the host does not know, and this is four batches of boxes
-// at most.  40,000 queries, k = 5, no radius, ring by ring and so:
+// of a self query first), for targets of up to RUNS_MAX_N points and sparse ones
+// of up to RUNS_SPARSE_N (takes_runs).  Such a target's rings may be many and
+// nearly empty: how many depends on where the queries lie, which the host does
+// not know, and this is four (16) batches of boxes at most.  40,000 queries,
+// k = 5, no radius, ring by ring and so:
 //   2,048 points 12 m apart                                  2,176 / 57 us
 //   a sweep thinned to 4,096, queries beside it, 8 m off   337 / 54, 728 / 89
 //   4,096 points of a cube, 4 a cell                            54 / 67
 //   6,000 (thinned sweep, cube)                          371 / 61, 55 / 72
 // Up to RUN_SCAN_MIN points are streamed without the boxes.
-constexpr int64_t RUNS_MAX_N = 4096;
+constexpr int64_t RUNS_MAX_N = 4096, RUNS_SPARSE_N = 16384;
 
 template <typename List>
 __device__ __forceinline__ void knn_query_runs(const TargetView& T, const WavePlan& w, bool self,
@@ -2764,6 +2765,24 @@ bool takes_group(const lkc_ctx* ctx, int k, int algorithm, bool self, int64_t n,
     return n > (int64_t)ctx->num_cus * per_cu;
 }
 
+// Whether a query's rings of cells may be many.
+bool many_rings(const TargetView& V, float radius) { return !(radius <= 2.0f * V.cell); }
+
+// Whether the wavefront search takes a target as a whole (knn_query_runs):
+// small ones, and larger ones of which a box is mostly empty cells, where rings
+// may be many.  40,000 queries without a radius, by rings and so, us:
+//   10,000 points 10 m apart (800 cells of the box a point)  k = 5 2,410 / 93
+//   10,000 of a map (21)     k = 1 36 / 69   k = 5 332 / 72   k = 20 904 / 80
+//   16,000 of a sweep (11)   k = 1 98 / 109  k = 5 161 / 107  k = 20 532 / 106
+//   16,000 of a cube (1)     k = 1 40 / 108  k = 5 72 / 113   k = 20 123 / 129
+bool takes_runs(const TargetView& V, int k, float radius) {
+    if (V.n <= RUNS_MAX_N) return true;
+    if (V.n > RUNS_SPARSE_N || k < 4 || !many_rings(V, radius)) return false;
+    double box = 1.0;   // (of a rebuild without a wait not known: 0)
+    for (int d = 0; d < 3; ++d) box *= (double)V.cmax[d] - (double)V.cmin[d] + 1.0;
+    return box >= 8.0 * (double)V.n;
+}
+
 // `fixed`: scratch the caller provides (then nothing is allocated and the
 // per-group profile is off).
 lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
@@ -2773,8 +2792,8 @@ lkc_status run_search(lkc_ctx* ctx, const SearchJob& j, const LaunchCfg& cfg,
     const int K = choose_k_tile(j.k);
     bool few = false, many = false, rings = false;
     for (int t = 0; t < j.n_targets; ++t) {
-        (j.host_views[t].n <= RUNS_MAX_N ? few : many) = true;
-        rings = rings || !(j.radius <= 2.0f * j.host_views[t].cell);
+        (takes_runs(j.host_views[t], j.k, j.radius) ? few : many) = true;
+        rings = rings || many_rings(j.host_views[t], j.radius);
     }
     // (a batch over both kinds of target whose rings may be many: the group
     // search streams the small ones whole, the rings of a wavefront would not end)

@@ -165,3 +165,39 @@ def test_sparse_target_without_a_radius_costs_no_more_than_groups(lk, n):
     group = _ms(lambda: lkc.lkc_knn_cov(ctx, t, q, 5, INF, 1e-3, cfg=GROUP))
     assert wave < 2.0 * group, (wave, group)
     t.free()
+
+
+@pytest.mark.parametrize("k", [3, 4, 20, 64])
+@pytest.mark.parametrize("n", [4097, 10000, 16384, 16385])
+def test_sparse_targets_of_more_points(lk, n, k):
+    """Either side of the size up to which a sparse target is taken as a whole
+    (k >= 4, no radius or a large one)."""
+    lkc, ctx = lk
+    p = workloads.random_cloud(n, n, scale=100.0)
+    q = np.concatenate([workloads.random_cloud(300, 1, scale=100.0), p[:40]])
+    t = lkc.lkc_build_target(ctx, dev(p), 1.0)
+    for radius in (INF, 25.0, 1.5):
+        a = host(lkc.lkc_knn_cov(ctx, t, dev(q), k, radius, 1e-3, cfg=WAVE))
+        parity.check_knn(p, q, k, radius, a["idx"], a["d2"], a["count"])
+        s = host(lkc.lkc_knn_cov_self(ctx, t, k, radius, 1e-3, cfg=WAVE))
+        parity.check_knn(p, p, k, radius, s["idx"], s["d2"], s["count"], rows=np.arange(0, n, 97))
+        if k <= 32:
+            for key, v in host(lkc.lkc_knn_cov(ctx, t, dev(q), k, radius, 1e-3, cfg=GROUP)).items():
+                assert np.array_equal(a[key], v), key
+    t.free()
+
+
+def test_sparse_target_of_ten_thousand_points(lk):
+    """By rings 36 times the target of 4,096 points as sparse, which is taken as
+    a whole; so 1.4 times."""
+    lkc, ctx = lk
+    q = dev(workloads.random_cloud(40000, 1, scale=100.0))
+
+    def ms(n):
+        t = lkc.lkc_build_target(ctx, dev(workloads.random_cloud(n, n, scale=100.0)), 1.0)
+        r = _ms(lambda: lkc.lkc_knn_cov(ctx, t, q, 5, INF, 1e-3))
+        t.free()
+        return r
+
+    few, more = ms(4096), ms(10000)
+    assert more < 5.0 * few, (few, more)
