@@ -16,9 +16,9 @@
 // come to the wavefront-per-query search are the same launch (no option
 // applies to it): it is timed once per cell.  Where the sample is a part of a
 // query set that is large enough for the group search, that search's gain
-// over the wavefront search shows on the whole set only (3.76 M queries: 1.31
-// against 7.74 ms; 118,000 of one scan: 0.38 against 0.31), so there
-// the wavefront search is timed but not chosen.
+// over the wavefront search shows on the whole set only (3.76 M queries: 1.57
+// against 5.41 ms; 117,500 of them: 0.23 against 0.18), so there the wavefront
+// search is timed but not chosen.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

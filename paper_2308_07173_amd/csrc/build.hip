@@ -876,8 +876,6 @@ inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 inline unsigned grid_for(int64_t n, int bt) { return (unsigned)((n + bt - 1) / bt); }
 
-int bit_width(uint32_t v) { return v ? 32 - __builtin_clz(v) : 0; }
-
 lkc_status ensure_scratch(lkc_ctx* ctx, size_t bytes) {
     if (ctx->build_scratch_bytes >= bytes) return LKC_OK;
     if (ctx->build_scratch) {

@@ -212,15 +212,6 @@ __device__ __forceinline__ T readlane(T v, int lane) {
     return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-// value of lane-1 (lane 0 gets `fill`), one DPP move across the whole wave
-template <typename T>
-__device__ __forceinline__ T shift_up1(T v, T fill) {
-    static_assert(sizeof(T) == 4, "32-bit only");
-    return __builtin_bit_cast(
-        T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, fill), __builtin_bit_cast(int, v),
-                                       0x138 /* wave_shr:1 */, 0xf, 0xf, false));
-}
-
 template <typename T>
 __device__ __forceinline__ T shfl_xor(T v, int mask) {
     static_assert(sizeof(T) == 4, "32-bit only");

@@ -12,26 +12,27 @@
 //     the group streams the point runs of its block of cells once, each
 //     candidate broadcast to all lanes, and answers every lane whose result
 //     the block proves exact;
-//   * the wavefront-per-query search (k_wave, and the whole search with
-//     algorithm 2) answers the rest: cells in Chebyshev rings around the
-//     query's cell, lanes enumerating a ring's cells in parallel and probing
-//     the cell hash; the surviving runs streamed 64 candidates at a time
-//     (one coalesced read); the running top-k one sorted list spread over
-//     the lanes (entry j in lane j), few qualifying candidates inserted one
-//     by one (a ballot finds the slot, a DPP wave shift opens it), many
-//     merged by a 64-lane bitonic network; it stops once the unvisited
-//     region lies beyond the k-th distance (or the radius), and a query
-//     whose rings would outgrow the occupied cells finishes with one sweep
-//     of the cell table, so uncapped searches stay bounded.
+//   * the wavefront-per-query search (k_wave: the whole search with algorithm 2
+//     and of launches that takes_group leaves to it) answers the rest: the 27
+//     cells around the query probed a lane each, then Chebyshev rings, lanes
+//     enumerating a ring's cells in parallel and probing the cell hash; the
+//     surviving runs streamed 64 candidates at a time (one coalesced read) and
+//     appended with one ballot to an unordered list of keys in LDS, which is
+//     cut back by a distance that enough of them do not exceed and sorted once
+//     at the end by counting; it stops once the unvisited region lies beyond
+//     the k-th distance (or the radius), and a query whose rings would outgrow
+//     the occupied cells finishes with one sweep of the cell table, so uncapped
+//     searches stay bounded.  Small targets, and sparse ones of middling size,
+//     are taken as a whole, through the boxes of their 16-point runs.
 // Ordering everywhere is lexicographic on (float32 d2, original index), so
 // both kernels, every launch shape and every visiting order give the same
 // bits.
 //
 // Covariance -- two passes over the neighbours relative to the query point
 // (centred, 1/n), then the smallest eigenvector of the 3x3 in closed form
-// (float32) for the GICP plane regulariser; fused into both searches (one lane
-// per query in the group search, the whole wavefront in the other) and
-// standalone in k_cov.
+// (float32) for the GICP plane regulariser; fused into both searches and
+// standalone in k_cov, one lane per query in each (k_wave and k_cov gather the
+// neighbours, and take the weights, with all lanes beforehand).
 #include <climits>
 #include <cmath>
 #include <mutex>
@@ -55,9 +56,6 @@ struct SearchParams {
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-__device__ __forceinline__ float uniform_f(float v) {
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 // Orders this wavefront's LDS writes before its later reads by other lanes
 // (the LDS serves a wavefront in order: only the compiler has to be told).
@@ -839,8 +837,8 @@ __device__ __forceinline__ float weight_exponent(const CovWeight& W, float d2) {
 // makes the sum >= 1.  Three passes relative to o: the smallest exponent,
 // the weighted mean, the weighted centred second moment; both divided by
 // the weight sum.  Validity and the regulariser are those of the plain
-// estimate.  Shared by every kernel that computes it, so the standalone and
-// fused results agree bit for bit.
+// estimate.  For k_group; covariance_offsets takes the same operations in the
+// same order elsewhere, so that the results agree bit for bit.
 template <typename Fetch>
 __device__ __forceinline__ void covariance_weighted(float ox, float oy, float oz, int n,
                                                     Fetch fetch, const CovWeight& W, float eps,
@@ -987,27 +985,6 @@ struct KnnPtrs {
 constexpr int GROUP_W = 2;       // lanes within this many cells of a round's anchor take part
 constexpr int64_t WHOLE_N = 4096;  // targets this small are streamed whole by every group
 
-__device__ __forceinline__ unsigned long long lane_key(float d, int32_t idx) {
-    return ((unsigned long long)(__float_as_uint(d) + 1u) << 32) | (uint32_t)idx;
-}
-__device__ __forceinline__ float key_d2(unsigned long long key) {
-    return __uint_as_float((uint32_t)(key >> 32) - 1u);
-}
-
-// Insert x (known to be below kk[K-1]) into the ascending list kk.
-template <int K>
-__device__ __forceinline__ void lane_insert(unsigned long long (&kk)[K], unsigned long long x) {
-    bool c_hi = x < kk[K - 1];
-#pragma unroll
-    for (int j = K - 1; j >= 1; --j) {
-        const bool c_lo = x < kk[j - 1];
-        const unsigned long long t = c_hi ? x : kk[j];
-        kk[j] = c_lo ? kk[j - 1] : t;
-        c_hi = c_lo;
-    }
-    kk[0] = c_hi ? x : kk[0];
-}
-
 // Batcher's odd-even merge sort on P = 2^ceil(log2 K) inputs, keeping the
 // comparators between the first K (the others would compare with +inf
 // padding and never swap).  Built at compile time.
@@ -1028,31 +1005,6 @@ struct SortNet {
                         }
     }
 };
-
-// Sort the list kk ascending in registers.
-template <int K>
-__device__ __forceinline__ void sort_keys(unsigned long long (&kk)[K]) {
-    constexpr SortNet<K> net{};
-#pragma unroll
-    for (int c = 0; c < net.n; ++c) {
-        const unsigned long long x = kk[net.a[c]], y = kk[net.b[c]];
-        const bool sw = y < x;
-        kk[net.a[c]] = sw ? y : x;
-        kk[net.b[c]] = sw ? x : y;
-        __builtin_amdgcn_sched_barrier(0);   // in order: bounded register use
-    }
-}
-
-__device__ __forceinline__ float wave_minf(float v) {
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) v = fminf(v, shfl_xor(v, s));
-    return v;
-}
-__device__ __forceinline__ float wave_maxf(float v) {
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) v = fmaxf(v, shfl_xor(v, s));
-    return v;
-}
 
 struct GroupArgs {
     const TargetView* views;          // device array, one per target
@@ -2159,15 +2111,15 @@ __device__ __forceinline__ void wave_cov(const GroupArgs& a, const WaveSlot& q, 
 //
 // Bound by the chain of dependent loads of each query (hash slots, points)
 // with few queries, by VALU issue with many (65,536 queries against a 2
-// M-point map: 0.109 ms; 0.125 before the plans were shared).
+// M-point map: 0.107 ms; 0.125 before the plans were shared).
 // The list of 99,000 queries that the group search hands over in a batch of
-// 3.76 M takes 55 us (the wavefront search before it: 154).
+// 3.76 M takes 54 us (the wavefront search before it: 154).
 //
 // LIST: the entries its lists keep, 64 or 128; 1: k = 1 without covariances, no
 // list.  RUNS: knn_query_runs answers.
 template <int FUSED, int LIST, bool RUNS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_wave(GroupArgs a) {
-    extern __shared__ unsigned long long s_wave[];
+    alignas(16) extern __shared__ unsigned long long s_wave[];
     const int lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
     const int k = a.sp.k;
@@ -2415,11 +2367,6 @@ __global__ void __launch_bounds__(256) k_query_keys(QueryKeyArgs a) {
     }
     ((Key*)a.keys)[i] = (Key)(((unsigned long long)tg << a.tshift) | key);
     a.vals[i] = (uint32_t)i;
-}
-
-__global__ void k_zero_u32(uint32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
 }
 
 // LDS words of one query's neighbours in k_cov: an odd number, so that lanes
@@ -2719,27 +2666,27 @@ lkc_status query_key_bits(lkc_ctx* ctx, const TargetView* views, int n, QueryKey
 }
 
 // Whether the group search takes a launch of n queries.  The group search
-// needs the fewest instructions a query (130 VALU against some 500, k = 20 on
-// a voxel map) but sorts the queries first and lasts as long as its slowest
-// group; the wavefront search is one launch whose work is even.  Measured,
+// needs the fewest instructions a query (some 125 VALU against 660, k = 20 on a
+// map) but sorts the queries first and lasts as long as its slowest group; the
+// wavefront search is one launch whose work is even.  Measured,
 // group / wavefront, us of the whole call, r = 2 m, 1 m cells:
 //   queries against a map of 2 M points (5.3 a cell)      k = 20    k = 5     k = 32
-//                                       20,000       152 / 38  114 / 31  192 / 41
-//                                       65,536       197 / 101 147 / 79  347 / 112
-//                                       98,304       232 / 149 169 / 117 327 / 175
-//                                      131,072       251 / 200 183 / 155 367 / 224
-//                                      196,608       294 / 291 228 / 226 401 / 335
+//                                       20,000       153 / 38  113 / 32  192 / 42
+//                                       65,536       196 / 106 147 / 81  347 / 115
+//                                       98,304       233 / 154 170 / 118 329 / 178
+//                                      131,072       252 / 202 182 / 154 367 / 223
+//                                      196,608       293 / 294 230 / 225 402 / 331
 //   against one of 100 k (2.2 a cell)
-//                                       65,536       169 / 128 128 / 81  272 / 145
-//                                       98,304       180 / 185 137 / 116 259 / 225
-//                                      131,072       197 / 254 149 / 152 300 / 295
-//                                      163,840       212 / 313 174 / 188 277 / 364
-//     (0.8 m cells, 1.8 a cell, 98,304: 201 / 252, k = 10 175 / 187)
-//   a sweep against itself              60,000       191 / 105           354 / 127
-//                                      117,965       341 / 227 196 / 161 439 / 285
-//                                      131,072       310 / 234 291 / 189 412 / 281
-//                                      163,840       324 / 301           430 / 373
-//   the same with k = 1                 65,536        57 / 70
+//                                       65,536       170 / 125 127 / 78  273 / 148
+//                                       98,304       181 / 184 137 / 115 258 / 226
+//                                      131,072       196 / 244 149 / 151 300 / 290
+//                                      163,840       213 / 296 174 / 185 276 / 363
+//     (0.8 m cells, 1.8 a cell, 98,304: 199 / 240, k = 10 173 / 175)
+//   a sweep against itself              60,000       191 / 106 114 / 85  352 / 122
+//                                      117,965       340 / 218 194 / 182 438 / 262
+//   two sweeps against themselves      131,072       334 / 271 227 / 185 545 / 318
+//                                      163,840       404 / 312 285 / 241 557 / 380
+//   a sweep against itself, k = 1       65,536        59 / 68
 // So the line lies at 384 queries per CU (98,304), 320 against targets of fewer
 // than 1.8 points a cell; at 512 for self queries (sorted already, but of uneven
 // density), 128 for their k = 1 (the own chunk answers it); above k = 20, where a
@@ -3101,7 +3048,8 @@ lkc_status launch_cov(lkc_ctx* ctx, const lkc_target* t, const float* queries,
     // on a CU (long weighted lists)
     const bool weighted = wt.kind != LKC_WEIGHT_NONE;
     const int row = 4 * cov_stride(k, weighted);
-    const int nq = 64 * row <= 36 * 1024 ? 64 : 32 * row <= 36 * 1024 ? 32 : 16;
+    const int nq = 64 * row <= 36 * 1024 ? 64 : 32;
+    static_assert(32 * 4 * cov_stride(LKC_MAX_K, true) <= 36 * 1024, "k_cov's LDS");
     if (q >= (int64_t)1 << 32) return set_error(ctx, LKC_ERR_INVALID_ARG, "too many queries");
     // (a launch has fewer than 2^32 threads)
     for (int64_t q0 = 0; q0 < q; q0 += COV_SLICE * nq) {

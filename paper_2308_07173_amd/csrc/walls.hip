@@ -370,10 +370,10 @@ __global__ void __launch_bounds__(WT) k_cluster_hook(ClusterArgs a) {
 // The passes are bound by latency: the chains of probes, candidates and parent
 // walks.  One pass of joins over single points, one thread per point (a few
 // thousand kept points of a scan leave most of the chip idle), took 323 us for
-// the 30,011 voxels of a scan; the same with 32 lanes per point and its chains
-// halved 104, nearly all of it parent walks; seeded and flattened first, with
-// the test of the parents, 85; with a hook before the joins 54 (10
-// seed, 5 + 5 flatten, 13 hook, 21 joins).
+// the 30,011 voxels of a scan, of which those on walls take part; the same with
+// 32 lanes per point and its chains halved 104, nearly all of it parent walks;
+// seeded and flattened first, with the test of the parents, 85; with a hook
+// before the joins 54 (9 seed, 5 + 5 flatten, 14 hook, 20 joins).
 __global__ void __launch_bounds__(WT) k_cluster_union(ClusterArgs a) {
     cluster_pairs<true>(
         a,
