@@ -91,16 +91,19 @@ struct WaveList {
     int k;
     bool dirty;                // (uniform) entries since the last cut
 
-    // Cuts the list back to about k + SLACK_ENTRIES, at most `most`, entries.
-    template <int R>
+    // Cuts the list back to about k + SLACK_ENTRIES, at most `most`, entries;
+    // CLOSE: to about k, from between the nearest entry and the farthest (a query
+    // far from the target has all its candidates there).
+    template <int R, bool CLOSE = false>
     __device__ __forceinline__ void cut(int most) {
+        constexpr int SLACK = CLOSE ? 0 : SLACK_ENTRIES;
         const int lane = lane_id();
         // (k <= WIDE_K with LIM = 64: no entry too many)
-        const int keep = LIM == WAVE ? k + SLACK_ENTRIES : min(k + SLACK_ENTRIES, most);
-        const int aim = LIM == WAVE ? k + SLACK_ENTRIES / 2 : min(k + SLACK_ENTRIES / 2, keep);
+        const int keep = LIM == WAVE ? k + SLACK : min(k + SLACK, most);
+        const int aim = LIM == WAVE ? k + SLACK / 2 : min(k + SLACK / 2, keep);
         wave_lds_fence();
         unsigned long long e[R];
-        float d[R], far = 0.0f;
+        float d[R], far = 0.0f, near = INF;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const bool have = lane + r * WAVE < n;
@@ -108,6 +111,7 @@ struct WaveList {
             // (an absent entry's distance is a NaN: below nothing)
             d[r] = __uint_as_float((uint32_t)(e[r] >> 32));
             far = fmaxf(far, have ? d[r] : 0.0f);
+            near = fminf(near, have ? d[r] : INF);
         }
         const auto within_d = [&](float t) {
             int c = 0;
@@ -117,6 +121,14 @@ struct WaveList {
         };
         float lo = 0.0f, up = wave_max_nonneg(far);
         int c_lo = 0, c_up = n;
+        if (CLOSE) {
+            lo = wave_min_nonneg(near);
+            c_lo = within_d(lo);
+            if (c_lo >= k) {
+                up = lo;
+                c_up = c_lo;
+            }
+        }
         for (int it = 0; it < 6 && c_up > keep; ++it) {
             const float t =
                 lo + (up - lo) * ((float)(aim - c_lo) * __builtin_amdgcn_rcpf((float)(c_up - c_lo)));
@@ -177,6 +189,14 @@ struct WaveList {
     __device__ __forceinline__ void tighten() {
         if (dirty && n >= k) cut<(LIM == WAVE ? REGS : REGS - 1)>(LIM);
     }
+    // The same where the bound decides which cells of a ring are probed: one of
+    // the (k + 8)-th distance lets many more pass when k is small (32,768 points
+    // 10 m apart against themselves, k = 5: 560 loads a query, 1,538 us; so
+    // 1,265.  40,000 queries 8 m off 10,000 points of a sweep, k = 1: 1,088, so
+    // 806).
+    __device__ __forceinline__ void tighten_close() {
+        if (dirty && n >= k) cut<(LIM == WAVE ? REGS : REGS - 1), true>(LIM);
+    }
     // At most a wavefront's entries.
     __device__ __forceinline__ void finish() {
         if (LIM > WAVE && n > WAVE) cut<REGS - 1>(WAVE);
@@ -211,6 +231,7 @@ struct WaveNearest {
         }
     }
     __device__ __forceinline__ void tighten() { bound = fminf(bound, wave_min_nonneg(d)); }
+    __device__ __forceinline__ void tighten_close() { tighten(); }
     __device__ __forceinline__ bool within(float d2) { return d2 > bound || ballot(d < d2) != 0; }
 };
 
@@ -490,7 +511,7 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
             if (pass == 0) L.tighten();
         }
         if (L.within(w.clear2)) return;
-        L.tighten();
+        L.tighten_close();
         R = 2;
     }
 #pragma unroll 1
@@ -563,7 +584,7 @@ __device__ __forceinline__ void knn_query_wave(const TargetView& T, const Target
             }
             if (ballot(found)) {
                 scan_cells(T, sp, found, st, cn, margin, L);
-                L.tighten();
+                L.tighten_close();
             }
         }
         if (sweep || L.within(block_clear2(T.cell, q, cq, R, margin))) return;
