@@ -623,10 +623,10 @@ __device__ __forceinline__ void bound_by_runs(const TargetView& T, const WaveQue
 // nearly empty: how many depends on where the queries lie, which the host does
 // not know, and this is four (16) batches of boxes at most.  40,000 queries,
 // k = 5, no radius, ring by ring and so:
-//   2,048 points 12 m apart                                  2,176 / 57 us
-//   a sweep thinned to 4,096, queries beside it, 8 m off   337 / 54, 728 / 89
-//   4,096 points of a cube, 4 a cell                            54 / 67
-//   6,000 (thinned sweep, cube)                          371 / 61, 55 / 72
+//   2,048 points 12 m apart                                  2,277 / 57 us
+//   a sweep thinned to 4,096, queries beside it, 8 m off   350 / 53, 728 / 89
+//   4,096 points of a cube, 4 a cell                            54 / 66
+//   6,000 (thinned sweep, cube)                          320 / 63, 56 / 72
 // Up to RUN_SCAN_MIN points are streamed without the boxes.
 constexpr int64_t RUNS_MAX_N = 4096, RUNS_SPARSE_N = 16384;
 
@@ -2739,10 +2739,10 @@ bool many_rings(const TargetView& V, float radius) { return !(radius <= 2.0f * V
 // Whether the wavefront search takes a target as a whole (knn_query_runs):
 // small ones, and larger ones of which a box is mostly empty cells, where rings
 // may be many.  40,000 queries without a radius, by rings and so, us:
-//   10,000 points 10 m apart (800 cells of the box a point)  k = 5 2,410 / 93
-//   10,000 of a map (21)     k = 1 36 / 69   k = 5 332 / 72   k = 20 904 / 80
-//   16,000 of a sweep (11)   k = 1 98 / 109  k = 5 161 / 107  k = 20 532 / 106
-//   16,000 of a cube (1)     k = 1 40 / 108  k = 5 72 / 113   k = 20 123 / 129
+//   10,000 points 10 m apart (800 cells of the box a point)  k = 5 2,499 / 91
+//   10,000 of a map (21)     k = 1 37 / 69   k = 5 298 / 72   k = 20 1,115 / 80
+//   16,000 of a sweep (11)   k = 1 93 / 109  k = 5 155 / 107  k = 20 673 / 106
+//   16,000 of a cube (1)     k = 1 41 / 108  k = 5 65 / 113   k = 20 124 / 129
 bool takes_runs(const TargetView& V, int k, float radius) {
     if (V.n <= RUNS_MAX_N) return true;
     if (V.n > RUNS_SPARSE_N || k < 4 || !many_rings(V, radius)) return false;
